@@ -44,6 +44,7 @@ if ROOT not in sys.path:
 
 HBM_PEAK_GBPS = 8000.0                          # MI355X HBM3E, published
 ALU_PEAK_TFLOPS = {"f32": 157.3, "f64": 78.6}   # published vector peaks (fp32 figure assumes packed FMA)
+SPLIT_PEAK_TFLOPS = 2516.6 / 6                  # dense bf16 MFMA peak, six bf16 products per fp32 product ("...split3mx" kernels)
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "measured_traffic.json")
 COLD_COPIES = 4                                 # distinct input tensors a single-pass case rotates through
 
@@ -141,6 +142,10 @@ def time_groups(timer, enqueue_group, launches_per_group: int, min_seconds: floa
     return per_launch
 
 
+def arithmetic_peak(kname, tag):
+    return SPLIT_PEAK_TFLOPS if kname.endswith("split3mx") else ALU_PEAK_TFLOPS[tag]
+
+
 def kernel_entry(case, kname, launch_ms, launches, traffic, extra=None):
     esz = np.dtype(case.dtype).itemsize
     alg_bytes = case.points * 2 * esz
@@ -149,12 +154,14 @@ def kernel_entry(case, kname, launch_ms, launches, traffic, extra=None):
     gbps = alg_bytes / (launch_ms * 1e-3) / 1e9
     tflops = flops / (launch_ms * 1e-3) / 1e12
     t_hbm = alg_bytes / (HBM_PEAK_GBPS * 1e9)
-    t_alu = flops / (ALU_PEAK_TFLOPS[tag] * 1e12)
+    peak = arithmetic_peak(kname, tag)
+    t_alu = flops / (peak * 1e12)
     k = {"case": case.name, "kernel": kname, "launch_ms": launch_ms, "launches_per_step": launches,
          "sweeps_per_launch": case.steps / launches, "gstencil_per_s": case.points * case.steps / (launch_ms * launches) / 1e6,
-         "hbm_GBps": gbps, "hbm_frac": gbps / HBM_PEAK_GBPS, "alu_TFLOPs": tflops, "alu_frac": tflops / ALU_PEAK_TFLOPS[tag],
+         "hbm_GBps": gbps, "hbm_frac": gbps / HBM_PEAK_GBPS, "alu_TFLOPs": tflops, "alu_frac": tflops / peak,
          # arithmetic-bound kernels whose products run on the matrix cores ("...mx") are priced
-         # against the dense fp32 MFMA peak, which equals the published fp32 vector peak
+         # against the dense fp32 MFMA peak, which equals the published fp32 vector peak, those of the bf16 split
+         # against a sixth of the dense bf16 MFMA peak
          "bound": "hbm" if t_hbm >= t_alu else ("mfma" if kname.split("+")[0].endswith("mx") else "alu"),
          "traffic": traffic.get(f"{kname}@{grid_tag(case.shape)}")}
     if extra:
@@ -327,7 +334,8 @@ def bench_default(ssam, wl, torch, args) -> int:
     if dom["bound"] == "hbm":
         roof = {"bound": "hbm", "achieved": dom["hbm_GBps"], "peak": HBM_PEAK_GBPS, "unit": "GB/s", "frac": dom["hbm_frac"]}
     else:
-        roof = {"bound": dom["bound"], "achieved": dom["alu_TFLOPs"], "peak": ALU_PEAK_TFLOPS["f32"], "unit": "TFLOP/s", "frac": dom["alu_frac"]}
+        roof = {"bound": dom["bound"], "achieved": dom["alu_TFLOPs"], "peak": arithmetic_peak(dom["kernel"], "f32"), "unit": "TFLOP/s",
+                "frac": dom["alu_frac"]}
     roof.update({"traffic": dom["traffic"], "kernel": dom["kernel"], "case": dom["case"], "launch_ms_mean": dom_ms,
                  "launches_timed": len(dom_events)})
     total_pts = sum(c.points for c in cases)

@@ -19,7 +19,8 @@ extern "C" {
  * integer launch parameter for subsequent calls, process-wide.  Names: "rows_per_wave",
  * "valid_lanes", "planes_per_wave", "xcd_remap", "force_generic", "variant" (an alternative
  * compiled instance of the same shape, where one exists; e.g. 5 = the vector-unit instance of a dense
- * fp32 filter whose default instance evaluates its products on the matrix cores), "march_axis" (3D: 0 = march along z,
+ * fp32 filter whose default instance evaluates its products on the matrix cores, 0 = its instance on the
+ * fp32 matrix instructions where the default is the one on the bf16 ones), "march_axis" (3D: 0 = march along z,
  * 1 = march along y), "fuse_sweeps" (ssam_stencil_iterate: 0 or 1 = always one sweep per launch, n >= 2 = at most n),
  * "embed_waste" (a 2D filter shape without a compiled instance runs inside the smallest compiled
  * square box that holds it, zero-padded; a value n >= 0 allows that only while the box has at most

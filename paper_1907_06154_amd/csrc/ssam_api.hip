@@ -8,6 +8,7 @@
 
 #include "ssam_device.h"
 #include "ssam_host.h"
+#include "ssam_kernel2d_split.h"
 
 namespace ssam {
 
@@ -216,6 +217,24 @@ const Instance2D* pick2d(const Problem2D& p, bool stencil_semantics, int want_va
     return best;
 }
 
+// Whether a dense fp32 filter goes to the bf16 matrix-core kernel instead of `inst` (its own instance), `box` (the square box
+// it would run in) or, with neither, the direct kernel.  That kernel's time hardly depends on the shape below 9x9 (8192^2:
+// 138-147 us for 6x6 .. 9x9), so the line lies where the other instances reach it: boxes up to 6x6 and the flat shapes with
+// instances of their own (3x11, 11x3, 1 x n) stay bandwidth-bound on the vector unit (104 us at 6x6); 7x7 takes 127 us
+// there and is only faster here on smaller pictures (1024^2: 11.2 -> 8.9 us, 4096^2: 36.7 and 39.4) and on rows that are
+// not whole 16-byte pieces (4003x3001: 44.3 -> 32.5); from 8x8 on (145 us, equal) it is faster everywhere.  Pictures of a
+// few tiles gain nothing, and a strip narrower than a wave's 64 columns would be mostly empty.
+bool split_is_faster(const Problem2D& p, const Instance2D* inst, const Instance2D* box, const Tuning& tu)
+{
+    const long points = (long)p.W * p.H;
+    if (p.dtype != SSAM_F32 || tu.force_generic > 0 || tu.variant >= 0 || tu.embed_waste >= 0) return false;
+    if (points < 16384 || p.W < 64) return false;
+    if (inst && (inst->budget != 2 || inst->M < 7 || inst->N < 7)) return false;
+    const int edge = inst ? inst->M : box ? box->M : SSAM_MAX_FILTER;
+    if (edge == 7) return p.W % 4 != 0 || points < (4L << 20);
+    return edge > 7;
+}
+
 int run2d(const Problem2D& p, bool stencil_semantics, Geometry* geo, bool dry, std::string* name)
 {
     const Tuning tu = current_tuning();
@@ -227,39 +246,46 @@ int run2d(const Problem2D& p, bool stencil_semantics, Geometry* geo, bool dry, s
         if (!inst && v != 0)   // no such alternative for this shape: use the default instance
             inst = p.dtype == SSAM_F32 ? pick2d<float>(p, stencil_semantics, 0) : pick2d<double>(p, stencil_semantics, 0);
     }
-    if (inst) {
-        if (name) *name = inst->name;
-        return status_of(inst->launch(p, tu, geo, dry));
-    }
     // No instance of this exact shape (a non-square filter, an anchor off the centre, unequal
     // radii): embed it in the smallest compiled square box whose centre anchor leaves enough room
     // on every side.  The added zero weights cost arithmetic, but even a 1x20 filter inside the 20x20
     // box measured faster than the direct kernel, so there is no limit unless "embed_waste" sets one.
-    if (tu.force_generic <= 0) {
+    const Instance2D* box = nullptr;
+    if (!inst && tu.force_generic <= 0) {
         const int need_lo = p.ax > p.ay ? p.ax : p.ay;
         const int hi_x = p.M - 1 - p.ax, hi_y = p.N - 1 - p.ay;
         const int need_hi = hi_x > hi_y ? hi_x : hi_y;
-        const Instance2D* box = nullptr;
         for (const Instance2D& i : registry2d()) {
             if (i.dtype != p.dtype || i.M != i.N || i.budget != 2 || i.variant != 0 || i.sweeps != 1) continue;
             if (i.AX != i.M / 2 || i.M / 2 < need_lo || i.M - 1 - i.M / 2 < need_hi) continue;
             if (!box || i.M < box->M) box = &i;
         }
-        if (box && (tu.embed_waste < 0 || box->M * box->N <= tu.embed_waste * p.M * p.N)) {
-            const int K = box->M, c = K / 2;
-            const size_t es = elem(p.dtype);
-            std::vector<char> padded((size_t)K * K * es, 0);
-            const char* src = static_cast<const char*>(p.w);
-            for (int n = 0; n < p.N; ++n)
-                memcpy(&padded[((size_t)(n + c - p.ay) * K + (c - p.ax)) * es], src + (size_t)n * p.M * es,
-                       (size_t)p.M * es);
-            Problem2D q = p;
-            q.M = q.N = K;
-            q.ax = q.ay = c;
-            q.w = padded.data();
-            if (name) *name = std::string(box->name) + "+embedded";
-            return status_of(box->launch(q, tu, geo, dry));   // weights are copied into the launch arguments
+        if (box && tu.embed_waste >= 0 && box->M * box->N > tu.embed_waste * p.M * p.N) box = nullptr;
+    }
+    if (split_is_faster(p, inst, box, tu)) {
+        const hipError_t e = launch2d_split(p, tu, geo, dry);
+        if (e != hipErrorNotSupported) {
+            if (name) *name = "float_M" + std::to_string(p.M) + "N" + std::to_string(p.N) + "_b2_v4p4split3mx";
+            return status_of(e);
         }
+    }
+    if (inst) {
+        if (name) *name = inst->name;
+        return status_of(inst->launch(p, tu, geo, dry));
+    }
+    if (box) {
+        const int K = box->M, c = K / 2;
+        const size_t es = elem(p.dtype);
+        std::vector<char> padded((size_t)K * K * es, 0);
+        const char* src = static_cast<const char*>(p.w);
+        for (int n = 0; n < p.N; ++n)
+            memcpy(&padded[((size_t)(n + c - p.ay) * K + (c - p.ax)) * es], src + (size_t)n * p.M * es, (size_t)p.M * es);
+        Problem2D q = p;
+        q.M = q.N = K;
+        q.ax = q.ay = c;
+        q.w = padded.data();
+        if (name) *name = std::string(box->name) + "+embedded";
+        return status_of(box->launch(q, tu, geo, dry));   // weights are copied into the launch arguments
     }
     if (name) *name = "generic_direct";
     if (geo) {

@@ -1,0 +1,123 @@
+"""Dense fp32 filters on the bf16 matrix cores (every value as the exact sum of three bf16 values) against the CPU
+oracle, at the sizes where the kernel can go wrong: patch widths around whole pieces of eight columns and around the
+four-column tail piece, every band count, filters evaluated in several launches, strips of one to three 64-column parts
+with ragged right edges, tiles of one band, the smallest width, anchors at the corners.
+
+Tolerance, in units of sum|w| * max|in|: one rounding of 2^-24 per table piece added to a sum (at most 30), the sums of 32
+products inside an instruction (at most 32 more), and less than 2^-24 for the partial products left out."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads as wl
+from parity_util import normalised_error
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+TOL = (30 + 32 + 1) * 2.0 ** -24
+
+
+@pytest.fixture(scope="module")
+def ssam():
+    import paper_1907_06154_amd as s
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    s.lib()
+    yield s
+    s.ssam_set_tuning("rows_per_wave", -1)
+
+
+def run(ssam, img, filt, boundary, anchor=None):
+    out = ssam.ssam_conv2d(torch.from_numpy(img).cuda(), filt, boundary, anchor)
+    torch.cuda.synchronize()
+    return out.cpu().numpy()
+
+
+def name_of(ssam, img, filt, boundary):
+    return ssam.ssam_describe("conv2d", img.shape, filt, boundary).split()[0]
+
+
+@pytest.mark.parametrize("M,N", [(8, 8), (9, 9), (8, 1), (1, 8), (13, 5), (14, 13), (17, 16), (18, 17), (20, 20), (21, 21),
+                                 (5, 21), (22, 22), (30, 9), (29, 14), (32, 32)])
+@pytest.mark.parametrize("boundary", ["clamp", "zero"])
+def test_shapes_and_edges(ssam, M, N, boundary):
+    filt = wl.seeded_filter(M, N, 900 + 32 * M + N, np.float32)
+    for k, (H, W) in enumerate([(256, 64), (127, 131), (90, 193), (33, 515), (3, 6000)]):
+        img = wl.uniform_field((H, W), -1.0, 1.0, 910 + k, np.float32)
+        anchor = [None, (0, 0), (M - 1, N - 1)][k % 3]
+        print(f"split {M}x{N} {boundary} {H}x{W} anchor {anchor}", flush=True)
+        assert "split3mx" in name_of(ssam, img, filt, boundary)
+        got = run(ssam, img, filt, boundary, anchor)
+        err = normalised_error(got, oracle.conv2d(img, filt, boundary, anchor), filt, 1.0)
+        assert err <= TOL, (M, N, boundary, H, W, err)
+
+
+@pytest.mark.parametrize("rows", [4, 8, 20, 36])
+def test_tile_heights(ssam, rows):
+    """Tiles shorter and taller than the filter: the steps above, inside and below a tile."""
+    img = wl.uniform_field((150, 260), -1.0, 1.0, 930, np.float32)
+    ssam.ssam_set_tuning("rows_per_wave", rows)
+    try:
+        for M, N in ((9, 9), (8, 21), (12, 3)):
+            filt = wl.seeded_filter(M, N, 931, np.float32)
+            print(f"split rows {rows} {M}x{N}", flush=True)
+            err = normalised_error(run(ssam, img, filt, "zero"), oracle.conv2d(img, filt, "zero"), filt, 1.0)
+            assert err <= TOL, (rows, M, N, err)
+    finally:
+        ssam.ssam_set_tuning("rows_per_wave", -1)
+
+
+@pytest.mark.parametrize("M", [9, 20, 25])
+def test_values_the_split_does_not_carry(ssam, M):
+    """Infinities, NaN and very large inputs: the outputs in their reach are those of plain multiply-adds, every other
+    output is untouched.  Tiny inputs keep their precision."""
+    filt = wl.seeded_filter(M, M, 940, np.float32)
+    img = wl.uniform_field((140, 300), -1.0, 1.0, 941, np.float32)
+    clean = run(ssam, img, filt, "clamp")
+    for value in (np.inf, -np.inf, np.nan, 1e30, -3e38):
+        for y, x in ((70, 150), (0, 0), (139, 299), (64, 191)):
+            dirty = img.copy()
+            dirty[y, x] = value
+            print(f"split {M} value {value} at {y},{x}", flush=True)
+            got, want = run(ssam, dirty, filt, "zero"), oracle.conv2d(dirty, filt, "zero")
+            with np.errstate(invalid="ignore"):
+                assert np.array_equal(np.isnan(got), np.isnan(want)) and np.array_equal(np.isinf(got), np.isinf(want))
+                fine = np.isfinite(want)
+                tol = M * M * 2.0 ** -24 * (np.abs(filt).sum() + (abs(value) * np.abs(filt).max() if np.isfinite(value) else 0.0) *
+                                            (np.abs(want) > 1e3))
+            assert np.all(np.abs(got[fine].astype(np.float64) - want[fine]) <= np.broadcast_to(tol, want.shape)[fine])
+    assert np.array_equal(run(ssam, img, filt, "clamp"), clean)
+    for scale in (2.0 ** -100, 2.0 ** -60, 2.0 ** 60):      # exact powers of two change nothing but the exponent
+        got = run(ssam, img * np.float32(scale), filt, "clamp")
+        assert np.array_equal(got, clean * np.float32(scale)), scale
+
+
+def test_filters_of_any_scale(ssam):
+    img = wl.uniform_field((140, 300), -1.0, 1.0, 951, np.float32)
+    filt = wl.seeded_filter(10, 10, 952, np.float32)
+    base = run(ssam, img, filt, "zero")
+    for e in (-80, 80):
+        assert np.array_equal(run(ssam, img, filt * np.float32(2.0 ** e), "zero"), base * np.float32(2.0 ** e))
+    # beyond the kernel's range, not finite, or nothing but zeros: the other kernels take the filter
+    for f in (filt * np.float32(2.0 ** 100), filt * np.float32(2.0 ** -100), np.zeros_like(filt)):
+        assert "split3mx" not in name_of(ssam, img, f, "zero")
+        want = oracle.conv2d(img, f, "zero")
+        assert normalised_error(run(ssam, img, f, "zero"), want, f, 1.0) <= TOL
+
+
+def test_capture_and_replay(ssam):
+    """A filter evaluated in several launches, recorded in a graph: every replay gives the eager result."""
+    filt = wl.seeded_filter(25, 25, 960, np.float32)
+    a = torch.from_numpy(wl.uniform_field((300, 400), 0.0, 1.0, 961, np.float32)).cuda()
+    out = torch.empty_like(a)
+    eager = ssam.ssam_conv2d(a, filt, "clamp").cpu().numpy()
+    graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=torch.cuda.Stream()):
+        ssam.ssam_conv2d(a, filt, "clamp", d_out=out)
+    for replay in range(3):
+        out.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(out.cpu().numpy(), eager), replay
+        assert np.array_equal(ssam.ssam_conv2d(a, filt, "clamp").cpu().numpy(), eager)
