@@ -9,6 +9,7 @@
 #include "ssam_device.h"
 #include "ssam_host.h"
 #include "ssam_kernel2d_split.h"
+#include "ssam_kernel3d_split.h"
 
 namespace ssam {
 
@@ -367,6 +368,28 @@ int run_fused(const Problem3D& p, int max_sweeps, Geometry* geo, bool dry, std::
     return 0;
 }
 
+// Whether a dense fp32 3D box of these extents goes to the bf16 matrix-core kernel.  compiled: the vector-unit box instance it
+// would run in has radius R (0: none, it would run on the direct kernel).  Radius 1 is bandwidth-bound there (3x3x3 on 512^3:
+// 199 us); from radius 2 on that kernel is faster at every size measured (5x5x5: 64^3 56 -> 17 us, 512^3 576 -> 400; 7x7x7: 199
+// -> 24, 1580 -> 1090).  The direct kernel keeps what is too little work to fill the machine (64^3 with 80 .. 150 taps: 20 .. 32
+// us there, 25 .. 33 here); rows of less than half a wave's 64 columns and very small grids stay where they were.
+bool split3d_is_faster(int W, int H, int D, int M, int N, int K, int compiled, const Tuning& tu)
+{
+    const long points = (long)W * H * D;
+    if (tu.force_generic > 0 || tu.variant >= 0 || tu.embed_waste >= 0 || tu.march_axis == 1) return false;
+    if (points < 65536 || W < 32 || compiled == 1) return false;
+    return compiled >= 2 || (double)points * M * N * K > 5e7;
+}
+
+std::string split3d_name(int M, int N, int K)
+{
+    if (M == N && N == K && M % 2 == 1) {
+        const std::string r = std::to_string(M / 2);
+        return "float_r" + r + r + r + "_b3_split3mx";
+    }
+    return "float_M" + std::to_string(M) + "N" + std::to_string(N) + "K" + std::to_string(K) + "_b3_split3mx";
+}
+
 int run3d(const Problem3D& p_in, Geometry* geo, bool dry, std::string* name)
 {
     const Tuning tu = current_tuning();
@@ -403,6 +426,16 @@ int run3d(const Problem3D& p_in, Geometry* geo, bool dry, std::string* name)
     // its own: the radius-4 star, 25 taps, beats the radius-3 box, 343); whichever is tried first, a
     // launcher that does not take this grid (hipErrorNotSupported) leaves the turn to the other.
     const bool cube_first = cube && cube != inst && (!inst || taps(*cube) < taps(*inst));
+    const Instance3D* first = cube_first ? cube : inst;
+    if (p.dtype == SSAM_F32 && first && first->budget == 3 &&
+        split3d_is_faster(p.W, p.H, p.D, 2 * p.rx + 1, 2 * p.ry + 1, 2 * p.rz + 1, first->rx, tu)) {
+        const hipError_t e = launch3d_split((const float*)p.in, (float*)p.out, p.W, p.H, p.D, (const float*)p.c, 2 * p.rx + 1,
+                                            2 * p.ry + 1, 2 * p.rz + 1, p.rx, p.ry, p.rz, p.boundary, p.stream, tu, geo, dry);
+        if (e != hipErrorNotSupported) {
+            if (name) *name = split3d_name(2 * p.rx + 1, 2 * p.ry + 1, 2 * p.rz + 1) + (cube_first ? "+embedded" : "");
+            return status_of(e);
+        }
+    }
     for (int attempt = 0; attempt < 2; ++attempt) {
         const bool use_cube = (attempt == 0) == cube_first;
         if (!use_cube && inst) {
@@ -461,16 +494,25 @@ int run_conv3d(const void* in, void* out, int W, int H, int D, const void* f, in
     // zero padding costs arithmetic: a cube with more than 8 times the filter's taps (or the "embed_waste"
     // override) is left to the direct kernel
     const long waste = tu.embed_waste > 0 ? tu.embed_waste : 8;
-    if (R >= 1 && R <= 3 && tu.force_generic <= 0 && tu.embed_waste != 0 &&
-        (long)(2 * R + 1) * (2 * R + 1) * (2 * R + 1) <= waste * M * N * K) {
+    const bool cube = R >= 1 && R <= 3 && tu.force_generic <= 0 && tu.embed_waste != 0 &&
+                      (long)(2 * R + 1) * (2 * R + 1) * (2 * R + 1) <= waste * M * N * K;
+    if (dtype == SSAM_F32 && split3d_is_faster(W, H, D, M, N, K, cube ? R : 0, tu)) {
+        const hipError_t e = launch3d_split((const float*)in, (float*)out, W, H, D, (const float*)f, M, N, K, ax, ay, az, boundary,
+                                            stream, tu, geo, dry);
+        if (e != hipErrorNotSupported) {
+            if (name) *name = split3d_name(M, N, K);
+            return status_of(e);
+        }
+    }
+    if (cube) {
         const int S = 2 * R + 1;
-        std::vector<char> cube((size_t)S * S * S * es, 0);
+        std::vector<char> padded((size_t)S * S * S * es, 0);
         const char* src = static_cast<const char*>(f);
         for (int k = 0; k < K; ++k)
             for (int n = 0; n < N; ++n)
-                memcpy(&cube[((((size_t)(k - az + R) * S) + (n - ay + R)) * S + (R - ax)) * es],
+                memcpy(&padded[((((size_t)(k - az + R) * S) + (n - ay + R)) * S + (R - ax)) * es],
                        src + ((size_t)k * N + n) * M * es, (size_t)M * es);
-        Problem3D p{in, out, W, H, D, cube.data(), R, R, R, boundary, dtype, stream};
+        Problem3D p{in, out, W, H, D, padded.data(), R, R, R, boundary, dtype, stream};
         p.dense = true;
         std::string inner;
         const int rc = run3d(p, geo, dry, &inner);

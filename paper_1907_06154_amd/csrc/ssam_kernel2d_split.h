@@ -209,8 +209,62 @@ __global__ __launch_bounds__(NW* kWave) __attribute__((amdgpu_waves_per_eu(2))) 
 
     unsigned bad = 0;      // bit k: the band staged k steps ago holds a value the split does not carry
 
+    // Stores output band o, which the step before has completed.  touched: `bad` as it was after that step.
+    auto store_band = [&](auto inside_tag, int o, unsigned touched) __attribute__((always_inline)) {
+        constexpr bool INSIDE = decltype(inside_tag)::value;
+        if ((touched & ((1u << NB) - 1)) == 0) {
+            const int y = y0 + 4 * o + kg;
+            float* rowp = a.out + (size_t)y * W;
+            if (y < y1) {
+#pragma unroll
+                for (int n = 0; n < NX; ++n) {
+                    const int x = x0 + 64 * n + 4 * j;
+                    v4f v = (acc[NB - 1][n] + low[NB - 1][n]) * a.out_scale;
+                    if (INSIDE || x + 4 <= W) {
+                        f32x4u* const p = reinterpret_cast<f32x4u*>(rowp + x);
+                        if (a.accumulate) v += (v4f)*p;
+                        __builtin_nontemporal_store((f32x4u)v, p);
+                    } else {
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            if (x + e < W) rowp[x + e] = a.accumulate ? rowp[x + e] + v[e] : v[e];
+                    }
+                }
+            }
+        } else {
+            // plain multiply-adds: an input in reach is not finite, or too large to be split
+            for (int n = 0; n < NX; ++n) {
+                const int x = x0 + 64 * n + lane;
+                if (x >= W) continue;
+                float s[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+                for (int k = 0; k < N + 3; ++k) {
+                    const int y = y0 + 4 * o + k - a.ay;
+                    const bool row_in = y >= 0 && y < H;
+                    const float* rowp = in + (size_t)min(max(y, 0), H - 1) * W;
+                    for (int m = 0; m < M; ++m) {
+                        const int xx = x + m - a.ax;
+                        const float f = rowp[min(max(xx, 0), W - 1)];
+                        const float v = (clamp || (row_in && xx >= 0 && xx < W)) ? f : 0.0f;
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            if (k >= e && k - e < N) s[e] = fma_t(v, wts[(k - e) * M + m], s[e]);
+                    }
+                }
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int y = y0 + 4 * o + e;
+                    if (y < y1) {
+                        float* const p = a.out + (size_t)y * W + x;
+                        *p = a.accumulate ? *p + s[e] : s[e];
+                    }
+                }
+            }
+            __builtin_amdgcn_s_waitcnt(0);   // nothing of this branch is left for the waits of the march to allow for
+        }
+    };
+
     // One step: input band t (in `raw`) is patch band pb of output band t - pb, for every pb; band t + AHEAD is requested.
-    // EDGE: some of those output bands may lie outside the tile.  STORE: output band t - NB + 1 is complete.
+    // EDGE: some of those output bands may lie outside the tile.  STORE: output band t - NB is complete and is stored.
     auto step = [&](auto inside_tag, auto edge_tag, auto store_tag, int t, float (&raw)[RND][4]) __attribute__((always_inline)) {
         constexpr bool INSIDE = decltype(inside_tag)::value, EDGE = decltype(edge_tag)::value, STORE = decltype(store_tag)::value;
         // ---- registers -> three bf16 parts in LDS
@@ -257,6 +311,10 @@ __global__ __launch_bounds__(NW* kWave) __attribute__((amdgpu_waves_per_eu(2))) 
             bad = (bad << 1) | (__any(!(top < kSplitLimit)) ? 1u : 0u);
         }
         wave_lds_fence();
+        // The stores go before the loads: requests complete in order, so the wait for a band's loads is also one for the
+        // stores before them, and these are then as old as the loads (stored at the end of a step and waited for at the
+        // start of the next one, they held up every step).
+        if constexpr (STORE) store_band(inside_tag, t - NB, bad >> 1);
         if (t + AHEAD < nt) load_band(t + AHEAD, raw);
 
         // The six products of one table piece with one staged piece.  FIRST: the sums of output band t - pb move on from
@@ -332,59 +390,6 @@ __global__ __launch_bounds__(NW* kWave) __attribute__((amdgpu_waves_per_eu(2))) 
             });
         }
         wave_lds_fence();
-
-        if constexpr (STORE) {
-            const int o = t - NB + 1;
-            if ((bad & ((1u << NB) - 1)) == 0) {
-                const int y = y0 + 4 * o + kg;
-                float* rowp = a.out + (size_t)y * W;
-                if (y < y1) {
-#pragma unroll
-                    for (int n = 0; n < NX; ++n) {
-                        const int x = x0 + 64 * n + 4 * j;
-                        v4f v = (acc[NB - 1][n] + low[NB - 1][n]) * a.out_scale;
-                        if (INSIDE || x + 4 <= W) {
-                            f32x4u* const p = reinterpret_cast<f32x4u*>(rowp + x);
-                            if (a.accumulate) v += (v4f)*p;
-                            __builtin_nontemporal_store((f32x4u)v, p);
-                        } else {
-#pragma unroll
-                            for (int e = 0; e < 4; ++e)
-                                if (x + e < W) rowp[x + e] = a.accumulate ? rowp[x + e] + v[e] : v[e];
-                        }
-                    }
-                }
-            } else {
-                // plain multiply-adds: an input in reach is not finite, or too large to be split
-                for (int n = 0; n < NX; ++n) {
-                    const int x = x0 + 64 * n + lane;
-                    if (x >= W) continue;
-                    float s[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-                    for (int k = 0; k < N + 3; ++k) {
-                        const int y = y0 + 4 * o + k - a.ay;
-                        const bool row_in = y >= 0 && y < H;
-                        const float* rowp = in + (size_t)min(max(y, 0), H - 1) * W;
-                        for (int m = 0; m < M; ++m) {
-                            const int xx = x + m - a.ax;
-                            const float f = rowp[min(max(xx, 0), W - 1)];
-                            const float v = (clamp || (row_in && xx >= 0 && xx < W)) ? f : 0.0f;
-#pragma unroll
-                            for (int e = 0; e < 4; ++e)
-                                if (k >= e && k - e < N) s[e] = fma_t(v, wts[(k - e) * M + m], s[e]);
-                        }
-                    }
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const int y = y0 + 4 * o + e;
-                        if (y < y1) {
-                            float* const p = a.out + (size_t)y * W + x;
-                            *p = a.accumulate ? *p + s[e] : s[e];
-                        }
-                    }
-                }
-                __builtin_amdgcn_s_waitcnt(0);   // nothing of this branch is left for the waits of the march to allow for
-            }
-        }
     };
 
     typedef std::true_type Yes;
@@ -396,13 +401,14 @@ __global__ __launch_bounds__(NW* kWave) __attribute__((amdgpu_waves_per_eu(2))) 
             if (nt > 1) load_band(1, raw[1]);
         }
         int t = 0;
-        // the first NB - 1 bands complete no output
-        for (; t + 1 < NB - 1; t += 2) {
+        // nothing to store yet
+        const int warm = min(NB, nt);
+        for (; t + 1 < warm; t += 2) {
             step(inside, Yes{}, No{}, t, raw[0]);
             step(inside, Yes{}, No{}, t + 1, raw[AHEAD - 1]);
         }
-        constexpr int S0 = AHEAD == 2 ? (NB - 1) & 1 : 0, S1 = AHEAD == 2 ? S0 ^ 1 : 0;
-        if constexpr (((NB - 1) & 1) == 1) {
+        constexpr int S0 = AHEAD == 2 ? NB & 1 : 0, S1 = AHEAD == 2 ? S0 ^ 1 : 0;
+        if (t < warm) {
             step(inside, Yes{}, No{}, t, raw[0]);
             ++t;
         }
@@ -414,6 +420,7 @@ __global__ __launch_bounds__(NW* kWave) __attribute__((amdgpu_waves_per_eu(2))) 
             step(inside, Yes{}, Yes{}, t, raw[S0]);
             if (t + 1 < nt) step(inside, Yes{}, Yes{}, t + 1, raw[S1]);
         }
+        store_band(inside, nout - 1, bad);
     };
     if (inside_x) march(Yes{});
     else march(No{});

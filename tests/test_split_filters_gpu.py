@@ -121,3 +121,79 @@ def test_capture_and_replay(ssam):
         torch.cuda.synchronize()
         assert np.array_equal(out.cpu().numpy(), eager), replay
         assert np.array_equal(ssam.ssam_conv2d(a, filt, "clamp").cpu().numpy(), eager)
+
+
+# ---- three dimensions -------------------------------------------------------------------------------------------------
+# One rounding per chain added to a sum (at most 28), up to 18 inside a chain, the sums of 32 products inside an
+# instruction, the parts of a filter added up in the output (at most 8), the partial products left out.
+TOL3 = (28 + 18 + 32 + 8 + 1) * 2.0 ** -24
+
+
+def run3(ssam, vol, filt, boundary, anchor=None):
+    out = ssam.ssam_conv3d(torch.from_numpy(vol).cuda(), filt, boundary, anchor)
+    torch.cuda.synchronize()
+    return out.cpu().numpy()
+
+
+@pytest.mark.parametrize("M,N,K", [(5, 5, 5), (4, 4, 4), (7, 7, 7), (6, 5, 3), (2, 9, 6), (9, 2, 8), (10, 4, 4), (14, 3, 5),
+                                   (17, 17, 2), (9, 9, 9), (5, 1, 1), (1, 6, 1), (4, 13, 2), (8, 8, 16)])
+@pytest.mark.parametrize("boundary", ["clamp", "zero"])
+def test_volumes(ssam, M, N, K, boundary):
+    rng = np.random.default_rng(970 + M + 20 * N + 400 * K)
+    filt = rng.uniform(-1.0, 1.0, (K, N, M)).astype(np.float32)
+    for i, (D, H, W) in enumerate([(40, 41, 64), (17, 70, 67), (9, 60, 131), (70, 33, 36), (1, 40, 1700)]):
+        vol = wl.uniform_field((D, H, W), -1.0, 1.0, 980 + i, np.float32)
+        anchor = [None, (0, 0, 0), (M - 1, N - 1, K - 1)][i % 3]
+        name = ssam.ssam_describe("conv3d", vol.shape, filt, boundary).split()[0]
+        print(f"split {M}x{N}x{K} {boundary} {vol.shape} anchor {anchor} {name}", flush=True)
+        err = normalised_error(run3(ssam, vol, filt, boundary, anchor), oracle.conv3d(vol, filt, boundary, anchor), filt, 1.0)
+        assert err <= TOL3, (M, N, K, boundary, vol.shape, err)
+
+
+@pytest.mark.parametrize("planes", [1, 3, 5, 16])
+def test_volume_chunks(ssam, planes):
+    """z-chunks shorter and taller than the filter."""
+    vol = wl.uniform_field((66, 50, 70), -1.0, 1.0, 990, np.float32)
+    ssam.ssam_set_tuning("planes_per_wave", planes)
+    try:
+        for shape in ((5, 5, 5), (7, 9, 4)):
+            filt = np.random.default_rng(991).uniform(-1.0, 1.0, shape).astype(np.float32)
+            assert "split3mx" in ssam.ssam_describe("conv3d", vol.shape, filt, "zero")
+            for boundary in ("clamp", "zero"):
+                print(f"split volume planes {planes} {shape} {boundary}", flush=True)
+                err = normalised_error(run3(ssam, vol, filt, boundary), oracle.conv3d(vol, filt, boundary), filt, 1.0)
+                assert err <= TOL3, (planes, shape, err)
+    finally:
+        ssam.ssam_set_tuning("planes_per_wave", -1)
+
+
+@pytest.mark.parametrize("radii", [(2, 2, 2), (3, 3, 3), (2, 1, 1), (1, 3, 2)])
+def test_dense_stencils(ssam, radii):
+    coef = wl.seeded_coefficients(wl.mask_box(*radii), 995, np.float32)
+    fld = wl.uniform_field((30, 45, 66), -1.0, 1.0, 996, np.float32)
+    assert "split3mx" in ssam.ssam_describe("stencil3d", fld.shape, coef, "zero")
+    for boundary in ("clamp", "zero"):
+        got = ssam.ssam_stencil3d(torch.from_numpy(fld).cuda(), coef, boundary).cpu().numpy()
+        assert normalised_error(got, oracle.stencil(fld, coef, boundary), coef, 1.0) <= TOL3
+    a = torch.from_numpy(fld).cuda()
+    res = ssam.ssam_stencil_iterate(a, torch.empty_like(a), coef, 3, "zero").cpu().numpy()
+    assert normalised_error(res, oracle.iterate(fld, coef, 3, "zero"), coef, 1.0) <= 3 * TOL3
+
+
+def test_volume_values_the_split_does_not_carry(ssam):
+    filt = np.random.default_rng(997).uniform(-1.0, 1.0, (5, 5, 5)).astype(np.float32)
+    vol = wl.uniform_field((30, 45, 66), -1.0, 1.0, 998, np.float32)
+    clean = run3(ssam, vol, filt, "clamp")
+    for value in (np.inf, np.nan, 1e30):
+        for at in ((15, 20, 30), (0, 0, 0), (29, 44, 65)):
+            dirty = vol.copy()
+            dirty[at] = value
+            print(f"split volume value {value} at {at}", flush=True)
+            got, want = run3(ssam, dirty, filt, "zero"), oracle.conv3d(dirty, filt, "zero")
+            assert np.array_equal(np.isnan(got), np.isnan(want)) and np.array_equal(np.isinf(got), np.isinf(want))
+            fine = np.isfinite(want) & (np.abs(want) < 1e3)
+            assert np.all(np.abs(got[fine].astype(np.float64) - want[fine]) <= 125 * 2.0 ** -24 * np.abs(filt).sum())
+            big = np.isfinite(want) & (np.abs(want) >= 1e3)
+            assert np.all(np.abs(got[big].astype(np.float64) - want[big]) <= 125 * 2.0 ** -24 * 1e30)
+    for scale in (2.0 ** -100, 2.0 ** 60):
+        assert np.array_equal(run3(ssam, vol * np.float32(scale), filt, "clamp"), clean * np.float32(scale))
