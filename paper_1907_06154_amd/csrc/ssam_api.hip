@@ -10,6 +10,7 @@
 #include "ssam_host.h"
 #include "ssam_kernel2d_split.h"
 #include "ssam_kernel3d_split.h"
+#include "ssam_kernel_dense.h"
 
 namespace ssam {
 
@@ -154,6 +155,32 @@ hipError_t launch_generic(const T* in, T* out, int W, int H, int D, const T* c, 
     return hipSuccess;
 }
 
+// What no compiled shape takes.  fp64 boxes without a zero (or whose zeros are taps) run on the register-tiled kernel; sparse
+// tap lists and fp32 on the one-point-per-thread kernel.
+hipError_t launch_direct(const void* in, void* out, int W, int H, int D, const void* c, int M, int N, int K, int ax, int ay, int az,
+                         int boundary, bool skip_zero, int dtype, hipStream_t stream, const Tuning& tu, Geometry* geo, bool dry)
+{
+    if (geo) {
+        *geo = Geometry();
+        geo->blocks = ceil_div(W, 64) * ceil_div(H, 4) * D;
+    }
+    if (dtype == SSAM_F32) {
+        if (dry) return hipSuccess;
+        return launch_generic<float>((const float*)in, (float*)out, W, H, D, (const float*)c, M, N, K, ax, ay, az, boundary, skip_zero,
+                                     stream);
+    }
+    const double* w = static_cast<const double*>(c);
+    bool dense = tu.force_generic <= 0 && (long)M * N * K >= 9;
+    for (long i = 0; dense && skip_zero && i < (long)M * N * K; ++i) dense = w[i] != 0.0;
+    if (dense) {
+        const hipError_t e = launch_dense((const double*)in, (double*)out, W, H, D, w, M, N, K, ax, ay, az, boundary, stream, tu,
+                                          nullptr, dry);
+        if (e != hipErrorNotSupported) return e;
+    }
+    if (dry) return hipSuccess;
+    return launch_generic<double>((const double*)in, (double*)out, W, H, D, w, M, N, K, ax, ay, az, boundary, skip_zero, stream);
+}
+
 // ---- plain copy (measurement aid) ---------------------------------------------------------
 // 16 bytes per lane, grid-stride: a reference rate for 1-read-1-write kernels (tile-shaped
 // access with streaming stores exceeds it), and the known-size reference the hardware traffic
@@ -289,17 +316,8 @@ int run2d(const Problem2D& p, bool stencil_semantics, Geometry* geo, bool dry, s
         return status_of(box->launch(q, tu, geo, dry));   // weights are copied into the launch arguments
     }
     if (name) *name = "generic_direct";
-    if (geo) {
-        *geo = Geometry();
-        geo->blocks = ceil_div(p.W, 64) * ceil_div(p.H, 4);
-    }
-    if (dry) return SSAM_OK;
-    hipError_t e = p.dtype == SSAM_F32
-                       ? launch_generic<float>((const float*)p.in, (float*)p.out, p.W, p.H, 1, (const float*)p.w, p.M,
-                                               p.N, 1, p.ax, p.ay, 0, p.boundary, stencil_semantics, p.stream)
-                       : launch_generic<double>((const double*)p.in, (double*)p.out, p.W, p.H, 1, (const double*)p.w,
-                                                p.M, p.N, 1, p.ax, p.ay, 0, p.boundary, stencil_semantics, p.stream);
-    return status_of(e);
+    return status_of(launch_direct(p.in, p.out, p.W, p.H, 1, p.w, p.M, p.N, 1, p.ax, p.ay, 0, p.boundary, stencil_semantics, p.dtype,
+                                   p.stream, tu, geo, dry));
 }
 
 template <typename T>
@@ -462,19 +480,8 @@ int run3d(const Problem3D& p_in, Geometry* geo, bool dry, std::string* name)
         }
     }
     if (name) *name = "generic_direct";
-    if (geo) {
-        *geo = Geometry();
-        geo->blocks = ceil_div(p.W, 64) * ceil_div(p.H, 4) * p.D;
-    }
-    const int M = 2 * p.rx + 1, N = 2 * p.ry + 1, K = 2 * p.rz + 1;
-    if (dry) return SSAM_OK;
-    hipError_t e = p.dtype == SSAM_F32
-                       ? launch_generic<float>((const float*)p.in, (float*)p.out, p.W, p.H, p.D, (const float*)p.c, M,
-                                               N, K, p.rx, p.ry, p.rz, p.boundary, !p.dense, p.stream)
-                       : launch_generic<double>((const double*)p.in, (double*)p.out, p.W, p.H, p.D,
-                                                (const double*)p.c, M, N, K, p.rx, p.ry, p.rz, p.boundary, !p.dense,
-                                                p.stream);
-    return status_of(e);
+    return status_of(launch_direct(p.in, p.out, p.W, p.H, p.D, p.c, 2 * p.rx + 1, 2 * p.ry + 1, 2 * p.rz + 1, p.rx, p.ry, p.rz,
+                                   p.boundary, !p.dense, p.dtype, p.stream, tu, geo, dry));
 }
 
 // 3D filter of extents (M, N, K) anchored at (ax, ay, az).  A cube of odd extent anchored at its
@@ -494,8 +501,12 @@ int run_conv3d(const void* in, void* out, int W, int H, int D, const void* f, in
     // zero padding costs arithmetic: a cube with more than 8 times the filter's taps (or the "embed_waste"
     // override) is left to the direct kernel
     const long waste = tu.embed_waste > 0 ? tu.embed_waste : 8;
-    const bool cube = R >= 1 && R <= 3 && tu.force_generic <= 0 && tu.embed_waste != 0 &&
-                      (long)(2 * R + 1) * (2 * R + 1) * (2 * R + 1) <= waste * M * N * K;
+    bool cube = R >= 1 && R <= 3 && tu.force_generic <= 0 && tu.embed_waste != 0 &&
+                (long)(2 * R + 1) * (2 * R + 1) * (2 * R + 1) <= waste * M * N * K;
+    // fp64: the radius-3 cube costs 343 taps whatever it holds and is slow on small grids; the direct kernel is faster for fewer
+    // taps (5x6x4: 64^3 264 -> 80 us, 256^3 561 -> 447) and, for the full cube, on grids of up to a few million points (64^3
+    // 264 -> 150 us; 256^3 561 and 791)
+    if (dtype == SSAM_F64 && R == 3 && tu.variant < 0 && ((long)M * N * K < 200 || (long)W * H * D < (4L << 20))) cube = false;
     if (dtype == SSAM_F32 && split3d_is_faster(W, H, D, M, N, K, cube ? R : 0, tu)) {
         const hipError_t e = launch3d_split((const float*)in, (float*)out, W, H, D, (const float*)f, M, N, K, ax, ay, az, boundary,
                                             stream, tu, geo, dry);
@@ -522,17 +533,7 @@ int run_conv3d(const void* in, void* out, int W, int H, int D, const void* f, in
         }
     }
     if (name) *name = "generic_direct";
-    if (geo) {
-        *geo = Geometry();
-        geo->blocks = ceil_div(W, 64) * ceil_div(H, 4) * D;
-    }
-    if (dry) return SSAM_OK;
-    const hipError_t e = dtype == SSAM_F32
-                             ? launch_generic<float>((const float*)in, (float*)out, W, H, D, (const float*)f, M, N, K, ax, ay,
-                                                     az, boundary, false, stream)
-                             : launch_generic<double>((const double*)in, (double*)out, W, H, D, (const double*)f, M, N, K,
-                                                      ax, ay, az, boundary, false, stream);
-    return status_of(e);
+    return status_of(launch_direct(in, out, W, H, D, f, M, N, K, ax, ay, az, boundary, false, dtype, stream, tu, geo, dry));
 }
 
 // Everything but the grid pointers (the planning query has none).
