@@ -185,6 +185,16 @@ inline int balanced_rows(int H, int P, int strips, int slots, int min_rows, bool
     return best_rows;
 }
 
+// Rows per tile (a multiple of P) that give a grid of `strips` strips at most two waves per SIMD (2048 in all).  Up to there a
+// wave's own latency is what a launch takes, and a tile of half the rows takes little more than half the time, however many
+// rows above it are computed twice; with more waves that redundancy costs what it says.  (320x1312 fp32 box, clamp, 19 sweeps: 111
+// us with tiles of at least 32 rows, 52 like this; 500x500 fp64 11x11: 23.7 -> 9.1.)
+inline int few_waves_rows(int H, int P, int strips)
+{
+    const int ytiles = 2048 / strips;
+    return ytiles < 1 ? H + P : ceil_div(ceil_div(H, ytiles), P) * P;
+}
+
 // Planes per z-chunk of the 3D march: `preferred` where the grid is large enough to fill the wave
 // slots with it, otherwise fewer (never under `fewest`), so that a small grid still spreads over
 // the machine; every chunk re-reads its leading planes, which is why large grids keep `preferred`.

@@ -79,27 +79,38 @@ __global__ __launch_bounds__(kBlock) void ssam2d_kernel(const Args2D<T, Mask::kN
     const unsigned keep_cols = clamp ? ~0u : ~(left_mask | right_mask);
     const unsigned keep_rows = clamp ? ~0u : 0u;   // mask applied to a row outside the grid
 
-    // A tile is "interior" when every row and column it touches lies inside the grid and can be
-    // accessed as aligned vectors: then loads and stores need no check at all.  Every other
-    // tile takes the general path, which applies the boundary rule (wave-uniform row logic,
-    // per-lane selects for columns) and also serves grids whose rows are not V-aligned.
+    // A tile is "interior" when every row and column it touches lies inside the grid: then loads and
+    // stores need no check at all (and no alignment beyond the element's).  Every other tile takes a
+    // general path, which applies the boundary rule (wave-uniform row logic, per-lane selects for columns).
     const int nchunks = (y1 - y0 + P - 1) / P;
-    const bool interior = vec_ok && xw0 >= 0 && xw0 + used_lanes * V <= W && (y1 - y0) % P == 0 &&
+    const bool interior = xw0 >= 0 && xw0 + used_lanes * V <= W && (y1 - y0) % P == 0 &&
                           y0 - a.ay >= 0 && y0 + nchunks * P - 1 - a.ay + N - 1 < H;
 
     auto march = [&](auto mode_tag) __attribute__((always_inline)) {
-        constexpr int MODE = decltype(mode_tag)::value;   // 0 interior, 1 general with vectors, 2 general by element
+        // 0 interior; general: 1 rows of whole vectors, 2 rows of any length from V on, 3 by element (rows shorter than V)
+        constexpr int MODE = decltype(mode_tag)::value;
         constexpr bool EDGE = MODE != 0;
-        constexpr bool VEC = MODE != 2;
+        constexpr bool VEC = MODE != 3;
+        unsigned keep_elem[V];      // mode 2: a lane's vector may end beyond the row
+#pragma unroll
+        for (int i = 0; i < V; ++i) keep_elem[i] = (clamp || (xl >= 0 && xl + i < W)) ? ~0u : 0u;
 
         auto load_row = [&](int y, T (&dst)[V]) __attribute__((always_inline)) {
             if constexpr (!EDGE) {
-                load_vec<T, V, (NT & kStreamLoads) != 0>(in + (size_t)y * W + xl, dst);
+                load_vec_elem<T, V, (NT & kStreamLoads) != 0>(in + (size_t)y * W + xl, dst);
             } else {
                 const bool row_in = y >= 0 && y < H;          // wave-uniform
                 const int yy = min(max(y, 0), H - 1);
                 const T* rowp = in + (size_t)yy * W;
-                if constexpr (VEC) {
+                if constexpr (MODE == 2) {
+                    const int xv = min(max(xl, 0), W - V);
+                    load_vec_elem<T, V, (NT & kStreamLoads) != 0>(rowp + xv, dst);
+                    const T first = dst[0];
+                    shift_columns(dst, xl - xv);
+                    const unsigned keep = row_in ? ~0u : keep_rows;
+#pragma unroll
+                    for (int i = 0; i < V; ++i) dst[i] = keep_if(pick(dst[i], first, left_pick), keep & keep_elem[i]);
+                } else if constexpr (VEC) {
                     // x: W and xc are multiples of V, so a lane's V columns are all in or all out
                     const int xv = min(max(xl, 0), W - V);
                     load_vec<T, V, (NT & kStreamLoads) != 0>(rowp + xv, dst);
@@ -127,10 +138,12 @@ __global__ __launch_bounds__(kBlock) void ssam2d_kernel(const Args2D<T, Mask::kN
                 for (int p = 0; p < P; ++p) {
                     T* rowp = a.out + (size_t)(y + p) * W;
                     if constexpr (!EDGE) {
-                        store_vec<T, V, (NT & kStreamStores) != 0>(rowp + xc, acc[p]);
+                        store_vec_elem<T, V, (NT & kStreamStores) != 0>(rowp + xc, acc[p]);
                     } else if (y + p < y1) {
-                        if constexpr (VEC) {
+                        if constexpr (MODE == 1) {
                             store_vec<T, V, (NT & kStreamStores) != 0>(rowp + xc, acc[p]);
+                        } else if (VEC && xc + V <= W) {
+                            store_vec_elem<T, V, (NT & kStreamStores) != 0>(rowp + xc, acc[p]);
                         } else {
 #pragma unroll
                             for (int i = 0; i < V; ++i)
@@ -195,7 +208,8 @@ __global__ __launch_bounds__(kBlock) void ssam2d_kernel(const Args2D<T, Mask::kN
     // the mode is wave-uniform and fixed for the whole march, so no load sits behind a branch
     if (interior) march(std::integral_constant<int, 0>{});
     else if (vec_ok) march(std::integral_constant<int, 1>{});
-    else march(std::integral_constant<int, 2>{});
+    else if (W >= V) march(std::integral_constant<int, 2>{});
+    else march(std::integral_constant<int, 3>{});
 }
 
 template <typename T, int V, int P, class Mask, bool PREFETCH, int NT, int ENGINE = 0>
@@ -220,7 +234,8 @@ hipError_t launch2d(const Problem2D& pr, const Tuning& tu, Geometry* geo, bool d
         // fill the machine's wave slots a whole number of times (a partly filled last round costs
         // a full one).  Measured on 8192^2, 20x20: 57 -> 73 GStencil/s.
         static const int slots = wave_slots(reinterpret_cast<const void*>(&ssam2d_kernel<T, V, P, Mask, PREFETCH, NT, ENGINE>));
-        rows = balanced_rows(pr.H, P, g.strips_x, slots, 3 * (N - 1), sizeof(T) == 8);
+        const int few = few_waves_rows(pr.H, P, g.strips_x);
+        rows = few < 3 * (N - 1) ? few : balanced_rows(pr.H, P, g.strips_x, slots, 3 * (N - 1), sizeof(T) == 8);
     } else {
         // bandwidth-bound: the shortest tiles measured best -- one or two groups per wave, about twice the
         // N-1 rows a tile re-reads at its top (8192^2: 3x3 fp32 839 -> 918 GStencil/s from 32 to 8 rows,

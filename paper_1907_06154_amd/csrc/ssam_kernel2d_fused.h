@@ -21,8 +21,16 @@
 
 namespace ssam {
 
+// Waves per SIMD asked of the compiler: four sweeps of radius 2 sit at the edge of 168 registers, and one more costs the third
+// wave (8192^2 fp64 box, clamp: 763 -> 880 us).  (The fp32 star is beyond it and would spill 29.)
+template <typename T, class Mask, int S>
+constexpr int fused_waves()
+{
+    return Mask::kN == 5 && S == 4 && (sizeof(T) == 8 || Mask::kNW >= 25) ? 3 : 1;
+}
+
 template <typename T, int V, int P, class Mask, int S, int NT>
-__global__ __launch_bounds__(kBlock) void ssam2d_fused_kernel(const Args2D<T, Mask::kNW> a)
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(fused_waves<T, Mask, S>()))) void ssam2d_fused_kernel(const Args2D<T, Mask::kNW> a)
 {
     constexpr int N = Mask::kN;
     constexpr int R = Mask::kAY;          // rows above the centre
@@ -62,15 +70,22 @@ __global__ __launch_bounds__(kBlock) void ssam2d_fused_kernel(const Args2D<T, Ma
     // from y0 on.  Sweep k's rows are complete from row ys + (S-1+k)*R on (its kept rows start
     // as zeros), which the warm-up groups put at or above y0 for the last sweep.
     const int nchunks = (y1 - y0 + P - 1) / P;
-    const bool interior = vec_ok && xw0 >= 0 && xw0 + used_lanes * V <= W && (y1 - y0) % P == 0 &&
+    // Edge tiles of rows that are not whole vectors: fp32 takes vectors and shifts them, fp64 two elements one by one -- its
+    // edge path gains nothing from vectors, and two more paths cost registers (radius-2 box, clamp: 4096^2 232 -> 250 us).
+    constexpr bool kShift = sizeof(T) == 4;
+    // (fp64 of radius 2 and more under the clamp rule on rows that are not whole vectors: every tile takes the general path;
+    // two paths in the instruction cache at a time cost more than it saves, 4003x3001 radius-4 star 149 and 162 us)
+    const bool interior = (vec_ok || sizeof(T) == 4 || !clamp || R == 1) && xw0 >= 0 && xw0 + used_lanes * V <= W && (y1 - y0) % P == 0 &&
                           ys + (S - 2) * R >= 0 && y0 + (nchunks - 1) * P + S * R + P - 1 < H;
 
     auto march = [&](auto mode_tag) __attribute__((always_inline)) {
-        // 0 interior; edge tiles: 1 vectors / 2 by element with zero padding, 3 / 4 the same with the clamp rule
+        // 0 interior; edge tiles: 1 rows of whole vectors, 2 rows of any length from V on, 3 by element, with zero padding;
+        // 4 .. 6 the same with the clamp rule
         constexpr int MODE = decltype(mode_tag)::value;
         constexpr bool EDGE = MODE != 0;
-        constexpr bool VEC = MODE != 2 && MODE != 4;
-        constexpr bool CLAMP = MODE >= 3;
+        constexpr bool VEC = MODE == 0 || MODE == 1 || MODE == 4;
+        constexpr bool ELEM = MODE == 3 || MODE == 6;
+        constexpr bool CLAMP = MODE >= 4;
 
         unsigned col_keep[V], col_left[V], col_right[V];   // all-ones where the column lies inside / left of / right of the grid
 #pragma unroll
@@ -87,7 +102,7 @@ __global__ __launch_bounds__(kBlock) void ssam2d_fused_kernel(const Args2D<T, Ma
 
         auto load_row = [&](int y, T (&dst)[V]) __attribute__((always_inline)) {
             if constexpr (!EDGE) {
-                load_vec<T, V, (NT & kStreamLoads) != 0>(in + (size_t)y * W + xl, dst);
+                load_vec_elem<T, V, (NT & kStreamLoads) != 0>(in + (size_t)y * W + xl, dst);
             } else {
                 const unsigned row_keep = (y >= 0 && y < H) ? ~0u : 0u;   // wave-uniform
                 const T* rowp = in + (size_t)min(max(y, 0), H - 1) * W;
@@ -103,10 +118,18 @@ __global__ __launch_bounds__(kBlock) void ssam2d_fused_kernel(const Args2D<T, Ma
 #pragma unroll
                         for (int i = 0; i < V; ++i) dst[i] = keep_if(dst[i], col_keep[0] & row_keep);
                     }
-                } else {
+                } else if constexpr (ELEM) {
 #pragma unroll
                     for (int i = 0; i < V; ++i)
                         dst[i] = keep_if(rowp[min(max(xc + i, 0), W - 1)], CLAMP ? ~0u : (col_keep[i] & row_keep));
+                } else {
+                    const int xv = min(max(xl, 0), W - V);
+                    load_vec_elem<T, V, (NT & kStreamLoads) != 0>(rowp + xv, dst);
+                    const T first = dst[0];
+                    shift_columns(dst, xl - xv);
+#pragma unroll
+                    for (int i = 0; i < V; ++i)
+                        dst[i] = CLAMP ? pick(dst[i], first, col_left[0]) : keep_if(dst[i], col_keep[i] & row_keep);
                 }
             }
         };
@@ -117,10 +140,12 @@ __global__ __launch_bounds__(kBlock) void ssam2d_fused_kernel(const Args2D<T, Ma
                 for (int p = 0; p < P; ++p) {
                     T* rowp = a.out + (size_t)(y + p) * W;
                     if constexpr (!EDGE) {
-                        store_vec<T, V, (NT & kStreamStores) != 0>(rowp + xc, acc[p]);
+                        store_vec_elem<T, V, (NT & kStreamStores) != 0>(rowp + xc, acc[p]);
                     } else if (y + p < y1) {
                         if constexpr (VEC) {
                             store_vec<T, V, (NT & kStreamStores) != 0>(rowp + xc, acc[p]);
+                        } else if (!ELEM && xc + V <= W) {
+                            store_vec_elem<T, V, (NT & kStreamStores) != 0>(rowp + xc, acc[p]);
                         } else {
 #pragma unroll
                             for (int i = 0; i < V; ++i)
@@ -245,9 +270,11 @@ __global__ __launch_bounds__(kBlock) void ssam2d_fused_kernel(const Args2D<T, Ma
 
     if (interior) march(std::integral_constant<int, 0>{});
     else if (!clamp && vec_ok) march(std::integral_constant<int, 1>{});
-    else if (!clamp) march(std::integral_constant<int, 2>{});
-    else if (vec_ok) march(std::integral_constant<int, 3>{});
-    else march(std::integral_constant<int, 4>{});
+    else if (!clamp && kShift && W >= V) march(std::integral_constant<int, kShift ? 2 : 3>{});
+    else if (!clamp) march(std::integral_constant<int, 3>{});
+    else if (vec_ok) march(std::integral_constant<int, 4>{});
+    else if (kShift && W >= V) march(std::integral_constant<int, kShift ? 5 : 6>{});
+    else march(std::integral_constant<int, 6>{});
 }
 
 template <typename T, int V, int P, class Mask, int S, int NT>
@@ -259,15 +286,27 @@ hipError_t launch2d_fused(const Problem2D& pr, const Tuning& tu, Geometry* geo, 
     Geometry g;
     plan_strips(pr.W, V, HL, HL, tu.valid_lanes, &g, true);
     g.P = P;
-    // The deep instances are arithmetic-bound: every wave takes about the same time, so the tile
-    // count should fill the machine's wave slots a whole number of times; tiles at least 8 groups
-    // tall keep the warm-up groups at each tile's top a small part of the work.
+    // The deep instances are arithmetic-bound: every interior wave takes about the same time, so the tile count should fill the
+    // machine's wave slots a whole number of times; tall tiles keep the warm-up groups at a tile's top a small part of the work.
+    // But edge tiles take longer, under the clamp rule half as long again, and one round of tall tiles ends with the machine
+    // waiting for the two edge strips: two rounds with zero padding, three under the clamp rule, where the tiles stay tall
+    // enough (8192^2 fp64 box, eight sweeps: zero 313 us with tiles of 304 rows, 301 with 128; clamp 450 with 304, 331 with 96;
+    // 4003x3001: clamp 113 with 56, 100 with 24, zero 77 either way).  From radius 2 on the warm-up groups cost more than that
+    // (box of radius 2, clamp, 4096^2: 234 us with one round, 252 with three).
     int rows;
     if (tu.rows_per_wave > 0) {
         rows = tu.rows_per_wave;
     } else {
         static const int slots = wave_slots(reinterpret_cast<const void*>(&ssam2d_fused_kernel<T, V, P, Mask, S, NT>));
-        rows = balanced_rows(pr.H, P, g.strips_x, slots, 8 * P);
+        const int few = few_waves_rows(pr.H, P, g.strips_x);
+        const bool clamp = pr.boundary == SSAM_BOUNDARY_CLAMP;
+        rows = few < 8 * P ? few : balanced_rows(pr.H, P, g.strips_x, slots, 8 * P);
+        for (int k = clamp ? 3 : 2; N == 3 && few >= 8 * P && k >= 2; --k) {
+            const int r = ceil_div(ceil_div(pr.H, slots * k / g.strips_x > 0 ? slots * k / g.strips_x : 1), P) * P;
+            if (r < (clamp ? 24 : 96) || r >= rows) continue;
+            rows = r;
+            break;
+        }
     }
     rows = ceil_div(rows, P) * P;
     if (rows > ceil_div(pr.H, P) * P) rows = ceil_div(pr.H, P) * P;
