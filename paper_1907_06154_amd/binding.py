@@ -1,4 +1,5 @@
-"""Thin ctypes binding of libssam.so: argument marshalling only.
+"""Thin binding of libssam.so: argument marshalling only (the compute entry points through the small
+extension module _marshal, everything else through ctypes).
 
 Every step of the computation runs in the HIP kernels behind the C ABI (include/ssam.h).
 torch is used for device memory and streams.  There is no CPU fallback: if the library is
@@ -15,6 +16,7 @@ import numpy as np
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.environ.get("SSAM_LIB_PATH") or os.path.join(_HERE, "libssam.so")   # override: A/B builds
 _lib: Optional[ctypes.CDLL] = None
+_fast = None        # the extension module, bound to the library's entry points
 
 SSAM_F32, SSAM_F64 = 0, 1
 SSAM_BOUNDARY_ZERO, SSAM_BOUNDARY_CLAMP = 0, 1
@@ -32,7 +34,7 @@ class SsamError(RuntimeError):
 
 def lib() -> ctypes.CDLL:
     """Loads libssam.so (built by paper_1907_06154_amd.build); raises if it is not there."""
-    global _lib
+    global _lib, _fast
     if _lib is None:
         if not os.path.exists(LIB_PATH):
             raise FileNotFoundError(
@@ -67,6 +69,10 @@ def lib() -> ctypes.CDLL:
             if name not in ("ssam_status_string", "ssam_scan_workspace_bytes"):
                 getattr(L, name).restype = ci
         L.ssam_scan_workspace_bytes.restype = ctypes.c_size_t
+        from . import _marshal
+        _marshal.bind(*(ctypes.cast(getattr(L, n), vp).value for n in
+                        ("ssam_conv2d", "ssam_conv3d", "ssam_stencil2d", "ssam_stencil3d", "ssam_stencil_iterate", "ssam_scan")))
+        _fast = _marshal
         _lib = L
     return _lib
 
@@ -101,10 +107,13 @@ def _device_tensor(t, name: str):
     return t
 
 
-def _stream_ptr(stream) -> ctypes.c_void_p:
+def _stream_ptr(stream) -> int:
+    """The stream's handle; without one, the calling thread's current stream on its current device (asked for
+    by handle: building a torch.cuda.Stream object takes a microsecond)."""
+    if stream is not None:
+        return stream.cuda_stream
     import torch
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _host_coef(coef, code: int) -> np.ndarray:
@@ -126,8 +135,9 @@ def ssam_conv2d(d_in, filt, boundary: str = "clamp", anchor: Optional[Tuple[int,
     if d_out is None:
         d_out = torch.empty_like(d_in)
     _device_tensor(d_out, "d_out")
-    st = lib().ssam_conv2d(d_in.data_ptr(), d_out.data_ptr(), W, H, f.ctypes.data, M, N, ax, ay,
-                           BOUNDARY[boundary], code, _stream_ptr(stream))
+    if _fast is None:
+        lib()
+    st = _fast.conv2d(d_in.data_ptr(), d_out.data_ptr(), W, H, f, ax, ay, BOUNDARY[boundary], code, _stream_ptr(stream))
     _check(st, "ssam_conv2d")
     return d_out
 
@@ -146,8 +156,9 @@ def ssam_conv3d(d_in, filt, boundary: str = "clamp", anchor: Optional[Tuple[int,
     if d_out is None:
         d_out = torch.empty_like(d_in)
     _device_tensor(d_out, "d_out")
-    st = lib().ssam_conv3d(d_in.data_ptr(), d_out.data_ptr(), W, H, D, f.ctypes.data, M, N, K, ax, ay, az,
-                           BOUNDARY[boundary], code, _stream_ptr(stream))
+    if _fast is None:
+        lib()
+    st = _fast.conv3d(d_in.data_ptr(), d_out.data_ptr(), W, H, D, f, ax, ay, az, BOUNDARY[boundary], code, _stream_ptr(stream))
     _check(st, "ssam_conv3d")
     return d_out
 
@@ -169,12 +180,13 @@ def ssam_stencil2d(d_in, coef, boundary: str = "zero", d_out=None, stream=None):
     H, W = d_in.shape
     code = _dtype_code(d_in)
     c = _host_coef(coef, code)
-    rx, ry, _ = _radii(c, 2)
+    _radii(c, 2)
     if d_out is None:
         d_out = torch.empty_like(d_in)
     _device_tensor(d_out, "d_out")
-    st = lib().ssam_stencil2d(d_in.data_ptr(), d_out.data_ptr(), W, H, c.ctypes.data, rx, ry,
-                              BOUNDARY[boundary], code, _stream_ptr(stream))
+    if _fast is None:
+        lib()
+    st = _fast.stencil2d(d_in.data_ptr(), d_out.data_ptr(), W, H, c, BOUNDARY[boundary], code, _stream_ptr(stream))
     _check(st, "ssam_stencil2d")
     return d_out
 
@@ -186,12 +198,13 @@ def ssam_stencil3d(d_in, coef, boundary: str = "zero", d_out=None, stream=None):
     D, H, W = d_in.shape
     code = _dtype_code(d_in)
     c = _host_coef(coef, code)
-    rx, ry, rz = _radii(c, 3)
+    _radii(c, 3)
     if d_out is None:
         d_out = torch.empty_like(d_in)
     _device_tensor(d_out, "d_out")
-    st = lib().ssam_stencil3d(d_in.data_ptr(), d_out.data_ptr(), W, H, D, c.ctypes.data, rx, ry, rz,
-                              BOUNDARY[boundary], code, _stream_ptr(stream))
+    if _fast is None:
+        lib()
+    st = _fast.stencil3d(d_in.data_ptr(), d_out.data_ptr(), W, H, D, c, BOUNDARY[boundary], code, _stream_ptr(stream))
     _check(st, "ssam_stencil3d")
     return d_out
 
@@ -207,16 +220,16 @@ def ssam_stencil_iterate(d_a, d_b, coef, steps: int, boundary: str = "zero", str
     c = _host_coef(coef, code)
     if d_a.dim() == 2:
         (H, W), D = d_a.shape, 1
-        rx, ry, rz = _radii(c, 2)
+        _radii(c, 2)
     else:
         D, H, W = d_a.shape
-        rx, ry, rz = _radii(c, 3)
-    result = ctypes.c_void_p(0)
-    st = lib().ssam_stencil_iterate(d_a.data_ptr(), d_b.data_ptr(), W, H, D, c.ctypes.data, rx, ry, rz,
-                                    BOUNDARY[boundary], code, int(steps), _stream_ptr(stream),
-                                    ctypes.byref(result))
+        _radii(c, 3)
+    if _fast is None:
+        lib()
+    st, result = _fast.iterate(d_a.data_ptr(), d_b.data_ptr(), W, H, D, c, BOUNDARY[boundary], code, int(steps),
+                               _stream_ptr(stream))
     _check(st, "ssam_stencil_iterate")
-    return d_a if result.value == d_a.data_ptr() else d_b
+    return d_a if result == d_a.data_ptr() else d_b
 
 
 def ssam_set_tuning(name: str, value: int) -> None:
@@ -280,16 +293,16 @@ def ssam_scan(d_in, d_out=None, d_work=None, stream=None):
     if d_out.shape != d_in.shape or d_out.dtype != d_in.dtype:
         raise ValueError("d_out must match d_in in shape and dtype")
     n = d_in.numel()
-    need = int(lib().ssam_scan_workspace_bytes(n, code))
+    need = int(lib().ssam_scan_workspace_bytes(n, code)) if d_work is None or _fast is None else 0
     if d_work is None and need:
         d_work = torch.empty(need, dtype=torch.uint8, device=d_in.device)
         if stream is not None:
             # the workspace dies when this function returns while the kernels that use it are still
             # queued on `stream`: tell the caching allocator, or it may hand the block out again
             d_work.record_stream(stream)
-    wp, wb = (d_work.data_ptr(), d_work.numel() * d_work.element_size()) if d_work is not None else (None, 0)
-    _check(lib().ssam_scan(d_in.data_ptr() if n else None, d_out.data_ptr() if n else None, n, code,
-                           wp, wb, _stream_ptr(stream)), "ssam_scan")
+    wp, wb = (d_work.data_ptr(), d_work.numel() * d_work.element_size()) if d_work is not None else (0, 0)
+    _check(_fast.scan(d_in.data_ptr() if n else 0, d_out.data_ptr() if n else 0, n, code, wp, wb, _stream_ptr(stream)),
+           "ssam_scan")
     return d_out
 
 

@@ -10,12 +10,14 @@ import glob
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libssam.so")
+MARSHAL = os.path.join(HERE, "_marshal.so")   # argument marshalling of the binding, a module of this interpreter
 
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
@@ -64,9 +66,17 @@ def build(verbose: bool = False, jobs: int = 8, extra=(), lib: str = LIB, increm
     link_extra = [a for a in extra if "sanitize" in a]      # a sanitizer build links its runtime too
     cmd = ["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", *link_extra, "-o", lib, *objs]
     subprocess.run(cmd, check=True)
+    build_marshal()
     if verbose:
         print(f"built {lib} from {len(srcs)} translation units")
     return lib
+
+
+def build_marshal() -> None:
+    tmp = MARSHAL + ".tmp"
+    subprocess.run(["gcc", "-O2", "-shared", "-fPIC", "-I" + sysconfig.get_paths()["include"], "-o", tmp,
+                    os.path.join(CSRC, "ssam_marshal.c")], check=True)
+    os.replace(tmp, MARSHAL)
 
 
 if __name__ == "__main__":

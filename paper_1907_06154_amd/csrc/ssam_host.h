@@ -150,6 +150,20 @@ inline int wave_slots(const void* kernel)
     return cus * blocks_per_cu * 4;
 }
 
+// Blocks of `threads` threads of `kernel` the device holds at once; `fallback` blocks per compute unit of 256 without a
+// device.  Launchers ask once per kernel: the three queries took longer than planning and launching a small grid.
+inline int device_blocks(const void* kernel, int threads, int fallback)
+{
+    int blocks_per_cu = 0, dev = 0, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0 ||
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks_per_cu, kernel, threads, 0) != hipSuccess || blocks_per_cu <= 0) {
+        (void)hipGetLastError();
+        return 256 * fallback;
+    }
+    return cus * blocks_per_cu;
+}
+
 // Rows per tile (a multiple of P, at least min_rows) such that strips * ceil(H / rows) tiles fill
 // `slots` wave slots k times as exactly as possible, k = 1 .. 4.  Among fills within 2 % of each other
 // the tallest tiles win (they amortise the rows re-read at tile tops); with prefer_short the shortest win

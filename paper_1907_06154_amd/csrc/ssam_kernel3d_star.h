@@ -513,17 +513,8 @@ hipError_t launch3d_star(const Problem3D& pr, const Tuning& tu, Geometry* geo, b
         // The longest z-chunks that still give every compute unit its share of blocks: each chunk
         // re-reads 2R planes, and one round of equally long blocks finishes together (512^3, radius 4:
         // fp32 202 -> 195 us from 64 to 128 planes, fp64 406 -> 364 us from 64 to 256).
-        int blocks_per_cu = 0, dev = 0, cus = 0;
-        if (hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0 ||
-            hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                &blocks_per_cu, reinterpret_cast<const void*>(&ssam3d_star_kernel<T, P, NW, R, BUDGET, NBUF, NT>), NW * kWave,
-                0) != hipSuccess || blocks_per_cu <= 0) {
-            (void)hipGetLastError();
-            cus = 256;
-            blocks_per_cu = 1;
-        }
-        planes = balanced_planes(LD, (long)g.strips_x * g.tiles_y, cus * blocks_per_cu, LD, 4 * R);
+        static const int fit = device_blocks(reinterpret_cast<const void*>(&ssam3d_star_kernel<T, P, NW, R, BUDGET, NBUF, NT>), NW * kWave, 1);
+        planes = balanced_planes(LD, (long)g.strips_x * g.tiles_y, fit, LD, 4 * R);
         if (!pr.march_y) planes = staggered_planes(planes, LD, slice);
     }
     if (planes > LD) planes = LD;

@@ -222,18 +222,8 @@ hipError_t launch3d_star2(const Problem3D& pr, const Tuning& tu, Geometry* geo, 
     int planes = tu.planes_per_wave;
     if (planes <= 0) {
         // the longest z-chunks that still give every compute unit its share of blocks (each re-reads four planes)
-        int blocks_per_cu = 0, dev = 0, cus = 0;
-        if (hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0 ||
-            hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                &blocks_per_cu, reinterpret_cast<const void*>(&ssam3d_star2_kernel<T, P, NW, NBUF, NT>), NW * kWave, 0) !=
-                hipSuccess ||
-            blocks_per_cu <= 0) {
-            (void)hipGetLastError();
-            cus = 256;
-            blocks_per_cu = 1;
-        }
-        planes = balanced_planes(pr.D, (long)g.strips_x * g.tiles_y, cus * blocks_per_cu, pr.D, 8);
+        static const int fit = device_blocks(reinterpret_cast<const void*>(&ssam3d_star2_kernel<T, P, NW, NBUF, NT>), NW * kWave, 1);
+        planes = balanced_planes(pr.D, (long)g.strips_x * g.tiles_y, fit, pr.D, 8);
         planes = staggered_planes(planes, pr.D, slice);
     }
     if (planes > pr.D) planes = pr.D;
