@@ -638,8 +638,10 @@ int ssam_stencil_iterate(void* d_a, void* d_b, int W, int H, int D, const void* 
     if (steps < 0) return SSAM_ERR_SHAPE;
     void* src = d_a;
     void* dst = d_b;
+    const bool cached = steps > 1 && 2 * (size_t)W * H * D * (dtype == SSAM_F32 ? 4 : 8) <= (size_t)192 << 20;   // of 256 MiB
     for (int t = 0; t < steps;) {
         Problem3D p{src, dst, W, H, D, h_coef, rx, ry, rz, boundary, dtype, (hipStream_t)hip_stream};
+        p.reread = cached;
         int rc = SSAM_OK;
         if (const int fused = run_fused(p, steps - t, nullptr, false, nullptr, &rc)) {
             if (rc) return rc;

@@ -53,6 +53,7 @@ struct Problem3D {
     hipStream_t stream;
     bool march_y = false;  // march along y with the register strip along z (instances see ry, rz exchanged)
     bool dense = false;    // filter semantics: every element of the box is a tap, zeros included
+    bool reread = false;   // the next launch reads this one's output, and both grids fit the last-level cache
 };
 
 // Tile geometry of one launch (all host arithmetic; also reported by ssam_describe).
@@ -149,6 +150,8 @@ inline int wave_slots(const void* kernel)
     }
     return cus * blocks_per_cu * 4;
 }
+
+constexpr int kCUs = 256;   // compute units of the device
 
 // Blocks of `threads` threads of `kernel` the device holds at once; `fallback` blocks per compute unit of 256 without a
 // device.  Launchers ask once per kernel: the three queries took longer than planning and launching a small grid.

@@ -31,8 +31,8 @@
 //     column of their row, which no plain load delivers, so blocks at the left or right edge of the
 //     grid replace those pieces when they READ the staged plane: one more broadcast read of the
 //     row's edge piece, only in those blocks.
-// Requirements (the launcher falls back to ssam3d_lds_kernel otherwise): W a multiple of V and
-// both base pointers 16-byte aligned.
+// Rows that are not whole 16-byte pieces, and buffers aligned to the element only, take the STAGED form of the kernel; planes
+// beyond 4 GiB take the launcher's fallback.
 #pragma once
 #include "ssam_kernel3d_lds.h"
 
@@ -167,7 +167,22 @@ __device__ __forceinline__ int younger_requests(int t, int nt, bool full_rows, i
     return younger;
 }
 
-template <typename T, int P, int NW, int R, int BUDGET, int NBUF, int NT>
+// The forms of the kernel.  kStagedCached stores without the streaming hint: rows at any offset end in part of a cache line,
+// and a sweep whose input the last one has just written finds it in the last-level cache only if it was left there
+// (201x203x199 fp64, clamp, four sweeps ping-pong: 3x3x3 box 144 us streaming, 124-130 plain; star r2 141, 118.  Out of the cache
+// the hint is right: 413x300x301 star r2 566 us against 608, one 201x203x199 sweep on cold buffers 25 against 35.)
+enum : int { kRing = 0, kStaged = 1, kStagedCached = 2 };
+
+// STAGED: for grids whose rows are not whole 16-byte pieces (or whose buffers are aligned to the element only).  A plane
+// travels through registers, where its pieces are put right -- shifted into place at the end of a row, blanked or repeated
+// outside the grid -- and the staged plane holds what the march reads, so that it has no edge cases; two buffers, the next
+// plane's loads in flight during a step.  Before, such grids went to the one-wave kernels, whose lanes beyond the halo store
+// nothing and which read every row element by element at the end of a row (zero padding, us a sweep, then -> now, 201x203x199 |
+// 413x300x301: star r1 fp32 36 -> 17 | 132 -> 73, fp64 42 -> 25 | 160 -> 137; star r4 fp32 41 -> 34 | 136 -> 110; 3x3x3 box
+// fp64 42 -> 29 | 159 -> 135; 5x5x5 fp64 135 -> 81 | 461 -> 308; 7x7x7 fp64, which had the direct kernel only, 3200 -> 335 |
+// 12770 -> 1360).  The large fp64 ones move their bytes at 4.3 TB/s; the small ones wait: one plane ahead is all that the
+// registers hold, and the waves of two or three blocks share a unit.
+template <typename T, int P, int NW, int R, int BUDGET, int NBUF, int NT, int FORM>
 __global__ __launch_bounds__(NW* kWave) __attribute__((amdgpu_waves_per_eu(2))) void ssam3d_star_kernel(
     const Args3D<T, SliceMask<R, R, R, BUDGET, 0>::kNW> a)
 {
@@ -181,10 +196,11 @@ __global__ __launch_bounds__(NW* kWave) __attribute__((amdgpu_waves_per_eu(2))) 
     constexpr int NTHR = NW * kWave;
     typedef PlaneFetch<T, NW * P + 2 * R, HC, NTHR> Fetch;   // the block stages NW*P + 2R rows per plane
     constexpr int RS = Fetch::RS, NCH = Fetch::NCH, SLOTS = Fetch::SLOTS;
-    constexpr bool NT_STORE = (NT & kStreamStores) != 0;
+    constexpr bool STAGED = FORM != kRing;
+    constexpr bool NT_STORE = FORM != kStagedCached && (NT & kStreamStores) != 0;
     static_assert((PF - 1) * NCH + PF * P <= 30, "request count beyond what the wait encodes");
 
-    __shared__ vec_t stage[NBUF][SLOTS];
+    __shared__ vec_t stage[STAGED ? 2 : NBUF][SLOTS];
 
     const int tid = threadIdx.x;
     const int lane = tid & (kWave - 1);
@@ -213,7 +229,7 @@ __global__ __launch_bounds__(NW* kWave) __attribute__((amdgpu_waves_per_eu(2))) 
     const bool inside_xy = x0 - HC * V >= 0 && x0 + (kWave + HC) * V <= W && yb0 - R >= 0 && yb0 + NW * P + R <= H;
 
     Fetch fetch;
-    fetch.plan(tid, x0, yb0 - R, W, H, rowst);
+    if constexpr (!STAGED) fetch.plan(tid, x0, yb0 - R, W, H, rowst);
 
     T acc[NZ][P][V];
 #pragma unroll
@@ -230,10 +246,10 @@ __global__ __launch_bounds__(NW* kWave) __attribute__((amdgpu_waves_per_eu(2))) 
 
     // Clamp rule at the left / right edge of the grid (block-uniform): the halo pieces, and the pieces of lanes
     // beyond the last column, are the row's edge column repeated.
-    const bool clamp_l = clamp && x0 == 0;                  // the left halo pieces lie outside the grid
-    const bool clamp_r = clamp && x0 + kWave * V > W;       // so do the pieces of the lanes from column W on
+    const bool clamp_l = !STAGED && clamp && x0 == 0;                  // the left halo pieces lie outside the grid
+    const bool clamp_r = !STAGED && clamp && x0 + kWave * V > W;       // so do the pieces of the lanes from column W on
     // right halo pieces 1 .. right_in lie inside the grid, the others outside
-    const int right_in = clamp ? min(max((W - x0 - kWave * V) / V, 0), HC) : HC;
+    const int right_in = clamp && !STAGED ? min(max((W - x0 - kWave * V) / V, 0), HC) : HC;
     const int last_piece = (wave * P) * RS + HC + (W - x0) / V - 1;   // the piece that ends in column W-1 (when one of the above is outside)
     const bool beyond = xc >= W;
     // row `k` of the wave's window in staged plane `st`: the lane's own piece, and halo piece h (1 = nearest).
@@ -440,10 +456,86 @@ __global__ __launch_bounds__(NW* kWave) __attribute__((amdgpu_waves_per_eu(2))) 
             T* po = a.out + (size_t)zo * plane + (size_t)y0 * rowst + xc;
 #pragma unroll
             for (int p = 0; p < P; ++p)
-                if (y0 + p < H) store_vec<T, V, NT_STORE>(po + (size_t)p * rowst, acc[0][p]);
+                if (y0 + p < H) {
+                    T* const q = po + (size_t)p * rowst;
+                    if constexpr (!STAGED) {
+                        store_vec<T, V, NT_STORE>(q, acc[0][p]);
+                    } else if (xc + V <= W) {
+                        store_vec_elem<T, V, NT_STORE>(q, acc[0][p]);
+                    } else {
+#pragma unroll
+                        for (int j = 0; j < V; ++j)
+                            if (xc + j < W) q[j] = acc[0][p][j];
+                    }
+                }
         }
     };
 
+    if constexpr (STAGED) {
+        // the thread's pieces, the same in every plane: where each is read (moved into the row), how far it was moved, and
+        // which of its elements lie inside the grid
+        unsigned from[NCH], moved = 0, keep = 0;
+        static_assert(NCH * V <= 32 && NCH <= 8, "one mask word");
+#pragma unroll
+        for (int i = 0; i < NCH; ++i) {
+            const int f = min(i * NTHR + tid, Fetch::TOTAL - 1);
+            const int row = f / RS, y = yb0 - R + row, x = x0 + (f - row * RS - HC) * V;
+            const int xx = min(max(x, 0), W - V), yy = min(max(y, 0), H - 1);
+            from[i] = (unsigned)((size_t)yy * rowst + xx);       // below 2^31 elements
+            moved |= (x < 0 ? 8u : (unsigned)min(x - xx, V)) << (4 * i);
+#pragma unroll
+            for (int j = 0; j < V; ++j) keep |= (clamp || (y >= 0 && y < H && x >= 0 && x + j < W) ? 1u : 0u) << (i * V + j);
+        }
+        T raw[NCH][V];
+        auto load = [&](int t) __attribute__((always_inline)) {
+            const T* pz = in + (size_t)min(max(z0 - R + t, 0), D - 1) * plane;
+#pragma unroll
+            for (int i = 0; i < NCH; ++i) load_vec_elem<T, V, false>(pz + from[i], raw[i]);
+        };
+        auto put = [&](int t, vec_t* buf) __attribute__((always_inline)) {
+            const int z = z0 - R + t;
+            const bool plane_in = clamp || (z >= 0 && z < D);            // block-uniform
+            if (!inside_xy) {
+                // the selections are made anew in every step: kept, they would take all scalar registers
+                asm volatile("" : "+v"(moved), "+v"(keep));
+#pragma unroll
+                for (int i = 0; i < NCH; ++i) {
+                    const unsigned m = (moved >> (4 * i)) & 15u;
+                    const T first = raw[i][0];
+                    shift_columns(raw[i], (int)(m & 7u));
+#pragma unroll
+                    for (int j = 0; j < V; ++j) {
+                        const T v = m & 8u ? first : raw[i][j];
+                        raw[i][j] = keep_if(v, (keep >> (i * V + j)) & 1u ? ~0u : 0u);
+                    }
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < NCH; ++i) {
+                vec_t v;
+#pragma unroll
+                for (int j = 0; j < V; ++j) v[j] = plane_in ? raw[i][j] : T(0);
+                buf[i * NTHR + tid] = v;
+            }
+        };
+        load(0);
+        put(0, stage[0]);
+        if (nt > 1) load(1);
+        for (int t = 0; t < nt; t += 2) {
+            static_for<2>([&](auto half) __attribute__((always_inline)) {
+                constexpr int b = decltype(half)::value;
+                const int u = t + b;
+                if (u < nt) {
+                    // plane u is staged, and every wave has left plane u - 1, whose buffer takes plane u + 1
+                    __syncthreads();
+                    if (u + 1 < nt) put(u + 1, stage[b ^ 1]);
+                    if (u + 2 < nt) load(u + 2);
+                    step(std::false_type{}, stage[b], z0 - R + u);
+                }
+            });
+        }
+        return;
+    } else {
     // ---- planes straight into LDS, PF steps ahead --------------------------------------------
     auto request = [&](int z, int b) __attribute__((always_inline)) { fetch.request(in, plane, z, D, clamp, inside_xy, stage[b], wave); };
     // a wave that stores all P rows issues P stores per step once output planes complete (step 2R on)
@@ -472,6 +564,7 @@ __global__ __launch_bounds__(NW* kWave) __attribute__((amdgpu_waves_per_eu(2))) 
     };
     if (clamp_l || clamp_r || right_in < HC) march(std::true_type{});   // block-uniform
     else march(std::false_type{});
+    }
 }
 
 // All blocks of these kernels march through their z-chunks in step, so at any moment the device reads one plane and
@@ -487,6 +580,26 @@ inline int staggered_planes(int planes, int depth, size_t plane_bytes)
     return ceil_div(depth, longer) == ceil_div(depth, planes) ? longer : planes;
 }
 
+// Planes per z-chunk of a grid that gives a compute unit only a few blocks: the busiest unit's plane-steps are what a launch
+// takes, the ones it repeats for the planes above a chunk included.  (Halving the chunks until every unit had a block, and never
+// below 4R planes, cost more: 96^3 star fp32 r1 8.5 -> 6.0 us, r2 19.6 -> 8.8, r4 31.4 -> 16.2; 200^3 r1 16.4 -> 12.8, where the
+// halving ended in 1.4 blocks per unit.)  `most`: the staged form's chunks end at 8R planes, beyond which blocks drift apart and
+// no longer find their neighbours' rows in the caches (413x300x301 fp64 star r1 137 us with 8 planes, 142 with 16, 153 with 23).
+// From four blocks per unit on, the ring's chunks stay as long as they were.
+inline int shared_planes(int depth, long tiles_xy, int R, int most)
+{
+    int best = 1;
+    long best_cost = -1;
+    const long least = (tiles_xy + kCUs - 1) / kCUs;
+    for (long blocks = least; blocks < least + 8; ++blocks) {       // on the busiest unit
+        const int chunks = (int)min(blocks * kCUs / tiles_xy, (long)depth);
+        const int planes = min(ceil_div(depth, chunks), most);
+        const long cost = (tiles_xy * ceil_div(depth, planes) + kCUs - 1) / kCUs * (planes + 2 * R + 1);
+        if (best_cost < 0 || cost < best_cost) best = planes, best_cost = cost;
+    }
+    return best;
+}
+
 // Fallback of a shape that has no other compiled instance: the dispatcher then takes the direct kernel.
 inline hipError_t launch3d_unavailable(const Problem3D&, const Tuning&, Geometry*, bool) { return hipErrorNotSupported; }
 
@@ -497,8 +610,22 @@ hipError_t launch3d_star(const Problem3D& pr, const Tuning& tu, Geometry* geo, b
 {
     constexpr int V = Piece16<T>::V;
     const size_t slice = (size_t)(pr.march_y ? pr.D : pr.H) * (pr.march_y ? (size_t)pr.W * pr.H : (size_t)pr.W) * sizeof(T);
-    if (pr.W % V != 0 || slice > 0xffffffffull || (!dry_run && !pointers_aligned(pr.in, pr.out, 16)))
-        return FALLBACK(pr, tu, geo, dry_run);
+    const bool staged = pr.W % V != 0 || (!dry_run && !pointers_aligned(pr.in, pr.out, 16));
+    if (pr.W < V || slice > 0xffffffffull) return FALLBACK(pr, tu, geo, dry_run);
+    const int LH = pr.march_y ? pr.D : pr.H, LD = pr.march_y ? pr.H : pr.D;   // strip / march extents
+    // Where the staged form leaves most of a block idle, the one-wave kernels stay: grids of fewer rows than a block's waves own
+    // at two each, and, at radius 1 in fp64, rows of a few elements (7x99x120: star 7.3 us against 7.7 staged, faces and edges
+    // 8.6 against 8.9; 33 wide 7.4 against 6.1).
+    if constexpr (FALLBACK != static_cast<Launch3DFn>(&launch3d_unavailable)) {
+        if (staged && (LH < NW * 2 || (R == 1 && sizeof(T) == 8 && pr.W < 16))) return FALLBACK(pr, tu, geo, dry_run);
+    }
+    // Two rows per wave instead of four: twice the blocks on a grid that has fewer than one per unit (96^3 fp32 star r1 6.6 us
+    // with four, 6.0 with two; r2 11.1, 8.7), and the staged form's registers let two blocks share a unit (413x300x301 fp32 star
+    // r2 88 us, 77; fp64 3x3x3 143, 133).
+    if constexpr (P == 4) {
+        if (staged || (long)ceil_div(pr.W, kWave * V) * ceil_div(LH, NW * P) * ceil_div(LD, 4 * R) < kCUs)
+            return launch3d_star<T, 2, NW, R, BUDGET, NBUF, NT, FALLBACK>(pr, tu, geo, dry_run);
+    }
     Geometry g;
     g.V = V;
     g.P = P;
@@ -506,16 +633,20 @@ hipError_t launch3d_star(const Problem3D& pr, const Tuning& tu, Geometry* geo, b
     g.valid_lanes = kWave;
     g.strips_x = ceil_div(pr.W, kWave * V);
     g.rows_per_wave = P;
-    const int LH = pr.march_y ? pr.D : pr.H, LD = pr.march_y ? pr.H : pr.D;   // strip / march extents
     g.tiles_y = ceil_div(LH, NW * P);
     int planes = tu.planes_per_wave;
     if (planes <= 0) {
         // The longest z-chunks that still give every compute unit its share of blocks: each chunk
         // re-reads 2R planes, and one round of equally long blocks finishes together (512^3, radius 4:
         // fp32 202 -> 195 us from 64 to 128 planes, fp64 406 -> 364 us from 64 to 256).
-        static const int fit = device_blocks(reinterpret_cast<const void*>(&ssam3d_star_kernel<T, P, NW, R, BUDGET, NBUF, NT>), NW * kWave, 1);
-        planes = balanced_planes(LD, (long)g.strips_x * g.tiles_y, fit, LD, 4 * R);
-        if (!pr.march_y) planes = staggered_planes(planes, LD, slice);
+        const long xy = (long)g.strips_x * g.tiles_y;
+        if (staged || xy * ceil_div(LD, 4 * R) < 4L * kCUs) {
+            planes = shared_planes(LD, xy, R, staged ? 8 * R : LD);
+        } else {
+            static const int fit = device_blocks(reinterpret_cast<const void*>(&ssam3d_star_kernel<T, P, NW, R, BUDGET, NBUF, NT, kRing>), NW * kWave, 1);
+            planes = balanced_planes(LD, xy, fit, LD, 4 * R);
+            if (!pr.march_y) planes = staggered_planes(planes, LD, slice);
+        }
     }
     if (planes > LD) planes = LD;
     g.planes_per_wave = planes;
@@ -529,7 +660,12 @@ hipError_t launch3d_star(const Problem3D& pr, const Tuning& tu, Geometry* geo, b
 
     Args3D<T, SliceMask<R, R, R, BUDGET, 0>::kNW> a;
     fill_args3d<T, V, R, R, R, BUDGET>(pr, g, &a);
-    hipLaunchKernelGGL((ssam3d_star_kernel<T, P, NW, R, BUDGET, NBUF, NT>), dim3(g.blocks), dim3(NW * kWave), 0, pr.stream, a);
+    if (staged && pr.reread)
+        hipLaunchKernelGGL((ssam3d_star_kernel<T, P, NW, R, BUDGET, NBUF, NT, kStagedCached>), dim3(g.blocks), dim3(NW * kWave), 0, pr.stream, a);
+    else if (staged)
+        hipLaunchKernelGGL((ssam3d_star_kernel<T, P, NW, R, BUDGET, NBUF, NT, kStaged>), dim3(g.blocks), dim3(NW * kWave), 0, pr.stream, a);
+    else
+        hipLaunchKernelGGL((ssam3d_star_kernel<T, P, NW, R, BUDGET, NBUF, NT, kRing>), dim3(g.blocks), dim3(NW * kWave), 0, pr.stream, a);
     return hipGetLastError();
 }
 

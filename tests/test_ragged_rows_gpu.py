@@ -65,3 +65,34 @@ def test_views_that_start_off_a_vector_boundary(ssam):
             filt = wl.seeded_filter(M, M, 1121, dtype)
             print(f"view {np.dtype(dtype).name} {M}x{M}", flush=True)
             assert_parity(ssam.ssam_conv2d(a, filt, "clamp").cpu().numpy(), oracle.conv2d(img, filt, "clamp"), filt, 1.0, "view")
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("W", [2, 3, 4, 5, 7, 127, 129, 131, 255, 257, 262])
+def test_widths_3d(ssam, dtype, W):
+    """3D: a strip is 64 vectors wide, and the staged plane is put right before it is read."""
+    for D, H in ((1, 1), (3, 9), (9, 37)):
+        fld = wl.uniform_field((D, H, W), -1.0, 1.0, 1130 + W, dtype)
+        buf = torch.zeros(fld.size + 1, dtype=torch.from_numpy(fld).dtype, device="cuda")
+        for first in (0, 1):                               # aligned to 16 bytes, and to the element only
+            a = buf[first:first + fld.size].view(fld.shape)
+            a.copy_(torch.from_numpy(fld))
+            for mask in (wl.mask_star(1, 1, 1), wl.mask_star(4, 4, 4), wl.mask_box(1, 1, 1), wl.mask_box(3, 3, 3)):
+                coef = wl.seeded_coefficients(mask, 1131, dtype)
+                for boundary in ("zero", "clamp"):
+                    print(f"ragged 3d {np.dtype(dtype).name} {D}x{H}x{W}+{first} {coef.shape} {boundary}", flush=True)
+                    got = ssam.ssam_stencil3d(a, coef, boundary).cpu().numpy()
+                    assert_parity(got, oracle.stencil(fld, coef, boundary), coef, 1.0, f"{D}x{H}x{W}+{first}")
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("shape", [(20, 41, 263), (5, 16, 63), (33, 34, 130)])
+def test_sweeps_3d(ssam, dtype, shape):
+    fld = wl.uniform_field(shape, -1.0, 1.0, 1140, dtype)
+    for mask in (wl.mask_star(2, 2, 2), wl.mask_box(1, 1, 1)):
+        coef = wl.seeded_coefficients(mask, 1141, dtype)
+        for boundary in ("zero", "clamp"):
+            print(f"sweeps 3d {np.dtype(dtype).name} {shape} {coef.shape} {boundary}", flush=True)
+            a = torch.from_numpy(fld).cuda()
+            res = ssam.ssam_stencil_iterate(a, torch.empty_like(a), coef, 5, boundary).cpu().numpy()
+            assert_parity(res, oracle.iterate(fld, coef, 5, boundary), coef, 1.0, f"iterate {shape}")
