@@ -472,7 +472,7 @@ def bench_config(ssam, wl, torch, args) -> int:
     if dom["bound"] == "hbm":
         roof = {"bound": "hbm", "achieved": dom["hbm_GBps"], "peak": HBM_PEAK_GBPS, "unit": "GB/s", "frac": dom["hbm_frac"]}
     else:
-        roof = {"bound": dom["bound"], "achieved": dom["alu_TFLOPs"], "peak": ALU_PEAK_TFLOPS[tag], "unit": "TFLOP/s", "frac": dom["alu_frac"]}
+        roof = {"bound": dom["bound"], "achieved": dom["alu_TFLOPs"], "peak": arithmetic_peak(dom["kernel"], tag), "unit": "TFLOP/s", "frac": dom["alu_frac"]}
     roof.update({"traffic": dom["traffic"], "kernel": dom["kernel"], "case": dom["case"]})
     out = {
         "metric": "GStencil/s", "value": total_pts / (wall / steps) / 1e9, "unit": "GStencil/s",

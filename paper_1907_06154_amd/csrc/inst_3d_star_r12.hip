@@ -1,5 +1,5 @@
 // Compiled instances: 3D stars of radius 1 (7-point) and 2 (13-point) on the block-cooperative star
-// kernel.  Fallbacks (rows that are not a multiple of 16 bytes): the one-wave-per-tile instances of
+// kernel.  Fallbacks (grids of a few rows or columns whose rows are not a multiple of 16 bytes): the one-wave-per-tile instances of
 // the same shapes, registered as variant 4 beside the other radius-1 / radius-2 shapes.
 // Default: four rows per wave, eight waves per block (7-point fp64 on 512^3: 351 us against 375 us
 // with two rows per wave, which stays as variant 10).

@@ -1,7 +1,7 @@
 // Compiled instances: 25-point star of radius 4 (largest register pressure: nine output planes
 // are in flight per lane).  Default: the block-cooperative star kernel (ssam_kernel3d_star.h),
 // two rows per wave, eight waves per block.  Variant 2: the earlier block-cooperative kernel with
-// halo lanes (also the fallback for rows that are not a multiple of 16 bytes); variant 1: the
+// halo lanes (also the fallback on grids of few rows whose width is not whole 16-byte pieces); variant 1: the
 // one-wave-per-tile kernel (single plane buffer for fp64: with two buffers the register allocator
 // spills); variant 10: four rows per wave (fp32; fp64 spills there).
 #include "ssam_kernel3d_star.h"
