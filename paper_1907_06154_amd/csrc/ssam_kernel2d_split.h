@@ -378,7 +378,9 @@ __global__ __launch_bounds__(NW* kWave) __attribute__((amdgpu_waves_per_eu(2))) 
             for (int s = 0; s < 3; ++s)
 #pragma unroll
                 for (int n = 0; n < NX; ++n) {
-                    const u32x2 p = before[s][n], q = *(const lds_u32x2*)(stage + slot + s * pitch * 32 + n * 128 + NG * 16);
+                    // one patch band: the band before is outside the outputs' reach, and what it holds need not be finite
+                    const u32x2 p = NB > 1 ? before[s][n] : u32x2{0u, 0u};
+                    const u32x2 q = *(const lds_u32x2*)(stage + slot + s * pitch * 32 + n * 128 + NG * 16);
                     const u32x4 v{p[0], p[1], q[0], q[1]};
                     b[s][n] = __builtin_bit_cast(bf16x8, v);
                     before[s][n] = q;

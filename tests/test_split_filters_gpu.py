@@ -92,6 +92,37 @@ def test_values_the_split_does_not_carry(ssam, M):
         assert np.array_equal(got, clean * np.float32(scale)), scale
 
 
+def assert_footprint(got, want, filt, value, what):
+    """Non-finite results exactly where the oracle has them; everything else to the rounding of the filter's sum,
+    outputs that read `value` itself to that of `value` times a weight."""
+    assert np.array_equal(np.isnan(got), np.isnan(want)) and np.array_equal(np.isinf(got), np.isinf(want)), what
+    fine = np.isfinite(want)
+    tol = filt.size * 2.0 ** -24 * np.abs(filt).sum() * np.where(np.abs(want) > 1e3, abs(value), 1.0) if np.isfinite(value) else \
+        np.full(want.shape, filt.size * 2.0 ** -24 * np.abs(filt).sum())
+    assert np.all(np.abs(got[fine].astype(np.float64) - want[fine]) <= tol[fine]), what
+
+
+@pytest.mark.parametrize("M,anchor", [(8, None), (14, None), (16, (0, 0)), (17, None), (25, (24, 0)), (32, None), (9, (0, 0)), (15, (14, 0))])
+def test_one_row_filters_and_the_band_above(ssam, M, anchor):
+    """Filters of one row whose last columns form a tail piece (two bands to a piece): a value above an output that
+    its filter does not read stays out of it, whatever it is (2.1e31 is infinite once it is scaled)."""
+    filt = wl.seeded_filter(M, 1, 945 + M, np.float32)
+    img = wl.uniform_field((130, 300), -1.0, 1.0, 946, np.float32)
+    if anchor is None:
+        assert "split3mx" in name_of(ssam, img, filt, "zero")
+    ssam.ssam_set_tuning("rows_per_wave", 24)       # several bands to a wave
+    try:
+        for value in (np.inf, np.nan, 2.1e31, -3e38):
+            for y, x in ((70, 150), (0, 0), (129, 299), (67, 191)):
+                dirty = img.copy()
+                dirty[y, x] = value
+                print(f"split {M}x1 value {value} at {y},{x}", flush=True)
+                with np.errstate(invalid="ignore", over="ignore"):
+                    assert_footprint(run(ssam, dirty, filt, "zero", anchor), oracle.conv2d(dirty, filt, "zero", anchor), filt, value, (y, x))
+    finally:
+        ssam.ssam_set_tuning("rows_per_wave", -1)
+
+
 def test_filters_of_any_scale(ssam):
     img = wl.uniform_field((140, 300), -1.0, 1.0, 951, np.float32)
     filt = wl.seeded_filter(10, 10, 952, np.float32)
