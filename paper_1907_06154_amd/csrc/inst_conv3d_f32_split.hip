@@ -127,14 +127,15 @@ hipError_t launch3d_split(const float* in, float* out, int W, int H, int D, cons
     if (hipError_t e = allow_lds(kernel, ((kp - 1) * 3 + part.bands - 1) * 4 + (groups - 1) * 2 + (tail ? 1 : 0))) return e;
     for (int k0 = 0; k0 < K; k0 += kp)
         for (int n0 = 0; n0 < N; n0 += np) {
-            // a last part of fewer rows or planes is filled up with zeros
-            a.N = np;
+            // A last part may have fewer rows or planes.  The matrix operand is zero there; the plain path has to know, or an
+            // infinity would reach outputs that do not read it.
+            a.N = N - n0 < np ? N - n0 : np;
+            a.K = K - k0 < kp ? K - k0 : kp;
             a.ay = ay - n0;
             a.az = az - k0;
-            for (int k = 0; k < kp; ++k)
-                for (int n = 0; n < np; ++n)
-                    for (int m = 0; m < M; ++m)
-                        a.w[(k * np + n) * M + m] = k0 + k < K && n0 + n < N ? w[((long)(k0 + k) * N + n0 + n) * M + m] : 0.0f;
+            for (int k = 0; k < a.K; ++k)
+                for (int n = 0; n < a.N; ++n)
+                    for (int m = 0; m < M; ++m) a.w[(k * a.N + n) * M + m] = w[((long)(k0 + k) * N + n0 + n) * M + m];
             hipLaunchKernelGGL(kernel, dim3(g.blocks), dim3(kSplit3dWaves * kWave), part.lds, stream, a);
             if (hipError_t e = hipGetLastError()) return e;
             a.accumulate = 1;

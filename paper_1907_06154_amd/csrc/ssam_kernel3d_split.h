@@ -21,7 +21,7 @@ struct ArgsSplit3D {
     const float* in;
     float* out;
     int W, H, D;
-    int M, N, ax, ay, az;
+    int M, N, K, ax, ay, az;   // the part's own extents: K planes of N rows, at most what the instance has room for
     int boundary;
     int strips_x, tiles_y;
     long tiles;
@@ -64,7 +64,7 @@ __global__ __launch_bounds__(kSplit3dWaves* kWave) __attribute__((amdgpu_waves_p
     lds_char* const stage_base = (lds_char*)lds_raw + (size_t)K * PIECES * 3 * kWave * 16;
     {
         lds_float* const wl = (lds_float*)stage_base;
-        for (int i = tid; i < K * M * N; i += NW * kWave) wl[i] = wts[i] * a.w_scale;
+        for (int i = tid; i < a.K * M * N; i += NW * kWave) wl[i] = wts[i] * a.w_scale;
         __syncthreads();
         for (int f = wave; f < K * PIECES; f += NW) {
             const int k = f / PIECES, p = f - k * PIECES;
@@ -87,7 +87,7 @@ __global__ __launch_bounds__(kSplit3dWaves* kWave) __attribute__((amdgpu_waves_p
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     const int mm = m0[q] + e;
-                    const bool in = n[q] >= 0 && n[q] < N && mm >= 0 && mm < M;
+                    const bool in = k < a.K && n[q] >= 0 && n[q] < N && mm >= 0 && mm < M;
                     const float x = wl[in ? (k * N + n[q]) * M + mm : 0];
                     v[e] = in ? x : 0.0f;
                 }
@@ -192,7 +192,7 @@ __global__ __launch_bounds__(kSplit3dWaves* kWave) __attribute__((amdgpu_waves_p
             if (x < W) {
                 for (int y = y0; y < min(y0 + 4 * TB, H); ++y) {
                     float s = 0.0f;
-                    for (int k = 0; k < K; ++k) {
+                    for (int k = 0; k < a.K; ++k) {
                         const int z = z0 - a.az + o + k;
                         const float* pz = in + (size_t)min(max(z, 0), D - 1) * plane;
                         for (int n = 0; n < N; ++n) {

@@ -228,3 +228,20 @@ def test_volume_values_the_split_does_not_carry(ssam):
             assert np.all(np.abs(got[big].astype(np.float64) - want[big]) <= 125 * 2.0 ** -24 * 1e30)
     for scale in (2.0 ** -100, 2.0 ** 60):
         assert np.array_equal(run3(ssam, vol * np.float32(scale), filt, "clamp"), clean * np.float32(scale))
+
+
+@pytest.mark.parametrize("M,N,K", [(9, 9, 9), (10, 5, 5), (5, 11, 5), (13, 11, 5), (3, 10, 15)])
+def test_volume_footprint_of_filters_in_parts(ssam, M, N, K):
+    """Filters cut into parts of which the last has fewer rows or planes than the others: infinities and NaN stay inside
+    the filter's own extents."""
+    filt = np.random.default_rng(1000 + M).uniform(-1.0, 1.0, (K, N, M)).astype(np.float32)
+    vol = wl.uniform_field((40, 70, 90), -1.0, 1.0, 1001, np.float32)
+    assert "split3mx" in ssam.ssam_describe("conv3d", vol.shape, filt, "zero")
+    for anchor in (None, (0, 0, 0), (M - 1, N - 1, K - 1)):
+        for value in (np.inf, np.nan):
+            for at in ((20, 35, 45), (0, 0, 0), (39, 69, 89)):
+                dirty = vol.copy()
+                dirty[at] = value
+                print(f"split volume {M}x{N}x{K} anchor {anchor} value {value} at {at}", flush=True)
+                with np.errstate(invalid="ignore"):
+                    assert_footprint(run3(ssam, dirty, filt, "zero", anchor), oracle.conv3d(dirty, filt, "zero", anchor), filt, value, at)
