@@ -1,6 +1,5 @@
 // The dense fp32 3D filters on the bf16 matrix cores (ssam_kernel3d_split.h): instances, tile plan, launch.
 #include <atomic>
-#include <cmath>
 
 #include "ssam_kernel3d_split.h"
 
@@ -50,15 +49,9 @@ hipError_t launch3d_split(const float* in, float* out, int W, int H, int D, cons
                           int az, int boundary, hipStream_t stream, const Tuning& tu, Geometry* geo, bool dry_run)
 {
     if (W < 4 || (long)W * H > 0x7fffffffL) return hipErrorNotSupported;
-    // as in two dimensions: the filter has to stay clear of the ends of the exponent range
-    float top = 0.0f;
-    for (long i = 0; i < (long)M * N * K; ++i) {
-        if (!std::isfinite(w[i])) return hipErrorNotSupported;
-        top = std::fmax(top, std::fabs(w[i]));
-    }
-    if (top < 0x1p-90f || top > 0x1p90f) return hipErrorNotSupported;
     int ew;
-    std::frexp(top, &ew);
+    const long taps = split_taps(w, (long)M * N * K, &ew);
+    if (2 * taps < 5L * K) return hipErrorNotSupported;      // see ssam_kernel3d_split.h: fewer round worse than fp32 multiply-adds
 
     const int rest = (M + 3) % 8;
     const bool tail = M > 5 && rest >= 1 && rest <= 4;

@@ -4,9 +4,11 @@
 // end at 157 TFLOP/s: 605 us on 8192^2, where memory would allow 90.  The bf16 matrix instructions are sixteen times as
 // fast.  They are used here without giving up precision:
 //   - Every fp32 value is the exact sum of three bf16 values, x = h + m + l (8 + 8 + 8 bits).  Of the nine partial products
-//     of x and a weight, six are formed (l*m, m*l and l*l are below 2^-26 of the product) and summed in fp32; the leading
-//     products h*h have an accumulator of their own, so that the small ones do not round it.  Error against 64-bit sums,
-//     2-norm, 8192^2: 9x9 4.6e-8 (fp32 matrix instructions: 1.6e-7), 20x20 1.0e-7 (2.7e-7).
+//     of x and a weight, six are formed (l*m, m*l and l*l together reach 2^-24 of the product, 2^-26.5 in the quadratic mean)
+//     and summed in fp32; the leading products h*h have an accumulator of their own, so that the small ones do not round it.
+//     Error against 64-bit sums, 2-norm, uniform random filters on pictures in [0, 1) and [-1, 1): 9x9 4.6 .. 5.3e-8 (fp32
+//     matrix instructions: 1.4 .. 1.6e-7), 20x20 1.0 .. 2.0e-7 (3.0 .. 3.8e-7); from three taps on no filter was further off
+//     than fp32 multiply-adds in the mean (launch2d_split leaves one and two to those).
 //   - Inputs are scaled by 2^24 and weights to [1, 2), so that no part becomes subnormal; a value that is not finite or is
 //     2^76 and more (found while the row is split) sends the outputs in its reach to plain fp32 multiply-adds.
 //   - The matrix operand that holds the filter is the Toeplitz matrix of a 4x4 block of outputs: 16 outputs by the (N + 3)
@@ -428,7 +430,11 @@ __global__ __launch_bounds__(NW* kWave) __attribute__((amdgpu_waves_per_eu(2))) 
     else march(No{});
 }
 
-// Launches one filter of at most kSplitMaxTaps taps and 21 rows; hipErrorNotSupported: not for this kernel.
+// The number of taps of w[0 .. count) that are not zero, and the largest one's binary exponent; 0 for a filter the split does
+// not carry.
+long split_taps(const float* w, long count, int* exponent);
+
+// Launches one filter, in parts of at most 21 rows; hipErrorNotSupported: not for this kernel.
 hipError_t launch2d_split(const Problem2D& pr, const Tuning& tu, Geometry* geo, bool dry_run);
 
 }  // namespace ssam

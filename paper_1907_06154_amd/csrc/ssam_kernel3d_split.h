@@ -8,7 +8,10 @@
 // flight stay in registers and move one slot per step.  All staged pieces of a group of eight columns are held in registers,
 // so a piece of the filter's table is read once per TB bands.  The products of one filter plane and column group form one
 // chain of matrix instructions that starts from zero and is added to the plane's sum on the vector unit: a sum is rounded
-// once per chain and not once per instruction, without a second set of accumulators.
+// once per chain and not once per instruction, without a second set of accumulators.  Every plane costs that addition, so a
+// filter of fewer than 2.5 taps per plane is left to the fp32 kernels, which round once per tap (ratio of the errors, split to
+// fp32, 60 Mpoint: 1x1xK 1.25 .. 1.4, 2x1xK 0.94 .. 1.08, 1x2xK 0.94 .. 1.06, 1x3xK 0.8 .. 0.9; 5x5x5 with 9 taps that are not
+// zero 1.05, with 16 0.80).
 #pragma once
 #include "ssam_kernel2d_split.h"
 
@@ -292,10 +295,15 @@ __global__ __launch_bounds__(kSplit3dWaves* kWave) __attribute__((amdgpu_waves_p
                     v4f c[TB];
 #pragma unroll
                     for (int n = 0; n < TB; ++n) c[n] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+                    // The small products of all pieces come first, then the leading ones: a sum is rounded NP times at its own
+                    // size and not after each of the 6 NP instructions, whose rounding is coarser than the vector unit's (error
+                    // against 64 bits: 5x5x5 8.4e-8 -> 6.2e-8; 1x9x1, one column of a piece in use, 1.7 -> 0.66 of what fp32
+                    // multiply-adds leave.  Time of 5x5x5 on 512^3: 396 -> 398 us).
+                    const lds_u32x4* const first = table + (k * PIECES + (TAILG ? NG * NB : g * NB)) * 3 * kWave + lane;
                     static_for<NP>([&](auto pp) __attribute__((always_inline)) {
                         constexpr int p = decltype(pp)::value;
                         constexpr int pb = !TAILG ? p : (2 * p + 1 < NB ? 2 * p + 1 : NB - 1);
-                        const lds_u32x4* const tp = table + ((k * PIECES + (TAILG ? NG * NB : g * NB) + p) * 3) * kWave + lane;
+                        const lds_u32x4* const tp = first + p * 3 * kWave;
                         const bf16x8 ah = __builtin_bit_cast(bf16x8, (u32x4)tp[0]);
                         const bf16x8 am = __builtin_bit_cast(bf16x8, (u32x4)tp[kWave]);
                         const bf16x8 al = __builtin_bit_cast(bf16x8, (u32x4)tp[2 * kWave]);
@@ -309,6 +317,11 @@ __global__ __launch_bounds__(kSplit3dWaves* kWave) __attribute__((amdgpu_waves_p
                         for (int n = 0; n < TB; ++n) c[n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, b[1][n + pb], c[n], 0, 0, 0);
 #pragma unroll
                         for (int n = 0; n < TB; ++n) c[n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(am, b[0][n + pb], c[n], 0, 0, 0);
+                    });
+                    static_for<NP>([&](auto pp) __attribute__((always_inline)) {
+                        constexpr int p = decltype(pp)::value;
+                        constexpr int pb = !TAILG ? p : (2 * p + 1 < NB ? 2 * p + 1 : NB - 1);
+                        const bf16x8 ah = __builtin_bit_cast(bf16x8, (u32x4)first[p * 3 * kWave]);
 #pragma unroll
                         for (int n = 0; n < TB; ++n) c[n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, b[0][n + pb], c[n], 0, 0, 0);
                     });

@@ -1,0 +1,36 @@
+"""Which kernel takes a dense filter: the rules on sizes and values (planning only, no GPU)."""
+import numpy as np
+import pytest
+
+import paper_1907_06154_amd as ssam
+
+
+def route(kind, shape, filt, boundary="zero"):
+    return ssam.ssam_describe(kind, shape, filt, boundary).split()[0]
+
+
+def with_taps(shape, count):
+    f = np.zeros(int(np.prod(shape)), dtype=np.float32)
+    f[np.linspace(0, f.size - 1, count).astype(int)] = 0.5
+    return f.reshape(shape)
+
+
+@pytest.mark.parametrize("size", [9, 20, 25])
+def test_filters_of_one_or_two_taps_keep_the_fp32_kernels(size):
+    for taps, split in ((1, False), (2, False), (3, True), (9, True)):
+        assert ("split3mx" in route("conv2d", (1000, 1000), with_taps((size, size), taps))) == split, taps
+
+
+@pytest.mark.parametrize("M,N,K,split", [(1, 1, 9, False), (1, 1, 17, False), (2, 1, 5, False), (1, 2, 9, False), (1, 3, 5, True),
+                                         (3, 1, 9, True), (5, 1, 1, True), (1, 9, 1, True), (5, 5, 5, True)])
+def test_volume_filters_of_few_taps_per_plane_keep_the_fp32_kernels(M, N, K, split):
+    f = np.full((K, N, M), 0.25, dtype=np.float32)
+    assert ("split3mx" in route("conv3d", (300, 300, 300), f)) == split
+
+
+@pytest.mark.parametrize("size", [5, 7, 9])
+def test_sparse_volume_filters(size):
+    shape = (size,) * 3
+    for taps in (1, 2, 2 * size):
+        assert "split3mx" not in route("conv3d", (200, 200, 200), with_taps(shape, taps)), taps
+    assert "split3mx" in route("conv3d", (200, 200, 200), with_taps(shape, 3 * size))

@@ -245,3 +245,56 @@ def test_volume_footprint_of_filters_in_parts(ssam, M, N, K):
                 print(f"split volume {M}x{N}x{K} anchor {anchor} value {value} at {at}", flush=True)
                 with np.errstate(invalid="ignore"):
                     assert_footprint(run3(ssam, dirty, filt, "zero", anchor), oracle.conv3d(dirty, filt, "zero", anchor), filt, value, at)
+
+
+def sums64(x, filt):
+    """The filter in 64 bits on the GPU, clamp rule, centre anchor, a tap at a time."""
+    pad = []
+    for n in reversed(filt.shape):
+        pad += [n // 2, n - 1 - n // 2]
+    xp = torch.nn.functional.pad(x.double()[None, None], pad, mode="replicate")[0, 0]
+    out = torch.zeros(x.shape, dtype=torch.float64, device="cuda")
+    for at in np.argwhere(filt != 0):
+        out.add_(xp[tuple(slice(int(o), int(o) + n) for o, n in zip(at, x.shape))], alpha=float(filt[tuple(at)]))
+    return out
+
+
+@pytest.mark.parametrize("M,N,K", [(1, 1, 9), (2, 1, 5), (1, 2, 6), (1, 3, 5), (1, 4, 3), (1, 5, 1), (1, 9, 1), (2, 9, 1), (3, 1, 5),
+                                   (4, 1, 1), (5, 5, 5), (9, 1, 2)])
+def test_thin_volume_filters_are_no_further_off_than_fp32_multiply_adds(ssam, M, N, K):
+    """2-norm of the error against 64 bits, in the quadratic mean over four filters, against that of the direct kernel.
+    The two differ in the order and number of their roundings only; over four filters the mean scatters by a tenth."""
+    vol = torch.rand((150, 290, 300), device="cuda", generator=torch.Generator("cuda").manual_seed(11))
+    ratios = []
+    for k in range(4):
+        filt = np.random.default_rng(1100 + k).uniform(-1.0, 1.0, (K, N, M)).astype(np.float32)
+        x = vol if k % 2 == 0 else vol * 2 - 1
+        want = sums64(x, filt)
+        err = [float((ssam.ssam_conv3d(x, filt, "clamp").double() - want).norm())]
+        ssam.ssam_set_tuning("force_generic", 1)
+        try:
+            err.append(float((ssam.ssam_conv3d(x, filt, "clamp").double() - want).norm()))
+        finally:
+            ssam.ssam_set_tuning("force_generic", -1)
+        ratios.append(err[0] / err[1])
+    assert np.sqrt(np.mean(np.square(ratios))) <= 1.1, ratios
+
+
+@pytest.mark.parametrize("M,taps", [(9, 1), (20, 1), (25, 2), (13, 3)])
+def test_filters_of_few_taps_are_no_further_off_than_fp32_multiply_adds(ssam, M, taps):
+    img = torch.rand((700, 900), device="cuda", generator=torch.Generator("cuda").manual_seed(12))
+    ratios = []
+    for k in range(6):
+        rng = np.random.default_rng(1110 + k)
+        filt = np.zeros(M * M, dtype=np.float32)
+        filt[rng.choice(M * M, taps, replace=False)] = rng.uniform(-1.0, 1.0, taps)
+        filt = filt.reshape(M, M)
+        want = sums64(img, filt)
+        err = [float((ssam.ssam_conv2d(img, filt, "clamp").double() - want).norm())]
+        ssam.ssam_set_tuning("force_generic", 1)
+        try:
+            err.append(float((ssam.ssam_conv2d(img, filt, "clamp").double() - want).norm()))
+        finally:
+            ssam.ssam_set_tuning("force_generic", -1)
+        ratios.append(err[0] / err[1])
+    assert np.sqrt(np.mean(np.square(ratios))) <= (1.005 if taps <= 2 else 1.1), ratios
