@@ -41,10 +41,11 @@ hipError_t allow_lds(SplitKernel kernel, int index)
 }  // namespace
 
 // The scaled weights and inputs have to stay clear of the ends of the exponent range; what is infinite, NaN or beyond 2^90 in
-// the filter goes to the other kernels (the same in the data: to the plain path inside the kernel).
+// the filter goes to the other kernels (the same in the data: to the plain path inside the kernel), and so does a filter with a
+// tap so small beside its largest that parts of it would be subnormal.
 long split_taps(const float* w, long count, int* exponent)
 {
-    float top = 0.0f;
+    float top = 0.0f, least = INFINITY;
     long taps = 0;
     for (long i = 0; i < count; ++i) {
         const float a = std::fabs(w[i]);
@@ -52,8 +53,9 @@ long split_taps(const float* w, long count, int* exponent)
         if (a == 0.0f) continue;
         ++taps;
         top = std::fmax(top, a);
+        least = std::fmin(least, a);
     }
-    if (top < 0x1p-90f) return 0;
+    if (top < 0x1p-90f || std::ldexp(least, 100) < top) return 0;
     std::frexp(top, exponent);      // top = f 2^exponent, f in [1/2, 1)
     return taps;
 }

@@ -34,3 +34,12 @@ def test_sparse_volume_filters(size):
     for taps in (1, 2, 2 * size):
         assert "split3mx" not in route("conv3d", (200, 200, 200), with_taps(shape, taps)), taps
     assert "split3mx" in route("conv3d", (200, 200, 200), with_taps(shape, 3 * size))
+
+
+def test_a_tap_far_below_the_largest():
+    """A weight whose low parts would be subnormal once the largest is scaled to [1, 2)."""
+    for kind, shape, size in (("conv2d", (1000, 1000), (9, 9)), ("conv3d", (100, 100, 100), (5, 5, 5))):
+        f = np.full(size, 2.0 ** 40, dtype=np.float32)
+        for e, split in ((-59, True), (-61, False), (-80, False)):
+            f.flat[3] = 2.0 ** e
+            assert ("split3mx" in route(kind, shape, f)) == split, (kind, e)

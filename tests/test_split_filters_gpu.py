@@ -298,3 +298,13 @@ def test_filters_of_few_taps_are_no_further_off_than_fp32_multiply_adds(ssam, M,
             ssam.ssam_set_tuning("force_generic", -1)
         ratios.append(err[0] / err[1])
     assert np.sqrt(np.mean(np.square(ratios))) <= (1.005 if taps <= 2 else 1.1), ratios
+
+
+def test_a_tap_far_below_the_largest_keeps_its_bits(ssam):
+    """Where the large taps meet zeros, the output is one small product."""
+    img = np.zeros((300, 300), dtype=np.float32)
+    img[150, 150] = 1.2345678
+    filt = np.full((9, 9), 2.0 ** 40, dtype=np.float32)
+    filt[0, 0] = np.float32(1.7654321) * np.float32(2.0 ** -80)
+    got = run(ssam, img, filt, "zero")[154, 154]
+    assert abs(float(got) - float(img[150, 150]) * float(filt[0, 0])) <= 2.0 ** -23 * float(img[150, 150]) * float(filt[0, 0])
