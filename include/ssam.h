@@ -128,7 +128,10 @@ const char *ssam_status_string(int status);
 /* Planning query, host only (nothing is launched, no pointer is dereferenced except h_coef):
  * writes a NUL-terminated description of the kernel instance and tile geometry the
  * dispatcher would use -- e.g. "float_M3N3_b2_v4p8 V=4 P=8 halo_lanes=1+1 valid_lanes=61
- * strips_x=34 ..." -- into buf (at most buflen bytes).  kind 0 = ssam_conv2d with (a, b) =
+ * strips_x=34 ..." -- into buf (at most buflen bytes).  P is what the launch uses, also where it differs from
+ * the instance's (two rows per wave instead of four on small 3D grids); lds is the LDS a block asks for at
+ * launch; form=1 says that the launch takes the staged form of the block-cooperative 3D kernel named, or
+ * the register-tiled fp64 kernel where the name is "generic_direct".  kind 0 = ssam_conv2d with (a, b) =
  * (M, N) and the default anchor; kind 1 = ssam_stencil2d with (a, b) = (rx, ry); kind 2 =
  * ssam_stencil3d with (a, b, c) = (rx, ry, rz); kind 3 = the launch ssam_stencil_iterate uses
  * on a 2D grid with (a, b) = (rx, ry) while c sweeps remain (c <= 0: many); an instance named

@@ -94,6 +94,7 @@ hipError_t launch3d_split(const float* in, float* out, int W, int H, int D, cons
     g.xcd_remap = tu.xcd_remap < 0 ? 1 : (tu.xcd_remap ? 1 : 0);
     const long blocks = (g.tiles + kSplit3dWaves - 1) / kSplit3dWaves;
     g.blocks = blocks > kMaxBlocks ? -1 : (g.xcd_remap ? ceil_div((int)blocks, kXcds) * kXcds : (int)blocks);
+    g.lds = (int)part.lds;
     if (geo) *geo = g;
     if (!launchable(g)) return hipErrorNotSupported;
     if (dry_run) return hipSuccess;

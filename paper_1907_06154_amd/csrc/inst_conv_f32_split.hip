@@ -116,15 +116,16 @@ hipError_t launch2d_split(const Problem2D& pr, const Tuning& tu, Geometry* geo, 
     g.rows_per_wave = rows;
     g.tiles_y = ceil_div(pr.H, rows);
     plan_blocks(&g, tu.xcd_remap);
-    if (geo) *geo = g;
-    if (!launchable(g)) return hipErrorInvalidConfiguration;
-    if (dry_run) return hipSuccess;
-
     const int quads = 16 * nx + 2 * groups - (tail ? 0 : 1);
     const int pitch = ceil_div(quads, 8) * 8;     // 8-byte words per staged row; no bank conflict was counted at 24 .. 56
     size_t stage = (size_t)kSplitWaves * 12 * pitch * 8;
     if (stage < (size_t)kSplitMaxTaps * 4) stage = kSplitMaxTaps * 4;
     const size_t lds = (size_t)pieces * 3 * kWave * 16 + stage;
+    g.lds = (int)lds;
+    if (geo) *geo = g;
+    if (!launchable(g)) return hipErrorInvalidConfiguration;
+    if (dry_run) return hipSuccess;
+
     const SplitKernel kernel = nx == 1 ? (tail ? split_kernel<1, true>(bands) : split_kernel<1, false>(bands))
                              : nx == 2 ? (tail ? split_kernel<2, true>(bands) : split_kernel<2, false>(bands))
                                        : (tail ? split_kernel<3, true>(bands) : split_kernel<3, false>(bands));

@@ -4,7 +4,7 @@
 namespace ssam {
 
 hipError_t launch_dense(const double* in, double* out, int W, int H, int D, const double* w, int M, int N, int K, int ax, int ay,
-                        int az, int boundary, hipStream_t stream, const Tuning& tu, Geometry* geo, bool dry_run)
+                        int az, int boundary, hipStream_t stream, Geometry* geo, bool dry_run)
 {
     // parts of a filter: whole rows of one or more planes, at most kDenseTaps values; output planes two by two in 3D
     const int kmax = kDenseTaps / (M * N) > 0 ? kDenseTaps / (M * N) : 1;
@@ -21,6 +21,7 @@ hipError_t launch_dense(const double* in, double* out, int W, int H, int D, cons
     const int pitch = ((4 << lane_cols) + M + 8) & ~1;      // a lane's last window ends up to four columns past the tile
     const int tiles_y = ceil_div(H, nw * wave_rows);
     const long tiles = (long)tiles_x * tiles_y * tiles_z;
+    const size_t lds = ((size_t)(nw * wave_rows + np - 1) * pitch + 8) * sizeof(double);
     Geometry g;
     g.V = 4;
     g.P = 4;
@@ -29,11 +30,15 @@ hipError_t launch_dense(const double* in, double* out, int W, int H, int D, cons
     g.tiles_z = tiles_z;
     g.tiles = tiles;
     g.xcd_remap = 1;
+    g.lds = (int)lds;
+    g.form = 1;
+    g.valid_lanes = kWave;
+    g.rows_per_wave = wave_rows;
+    g.planes_per_wave = tz;
     g.blocks = tiles > kMaxBlocks ? -1 : ceil_div((int)tiles, kXcds) * kXcds;
     if (geo) *geo = g;
     if (!launchable(g)) return hipErrorNotSupported;
     if (dry_run) return hipSuccess;
-    (void)tu;
 
     DenseArgs a;
     a.in = in;
@@ -50,7 +55,6 @@ hipError_t launch_dense(const double* in, double* out, int W, int H, int D, cons
     a.tiles = (int)tiles;
     a.blocks = g.blocks;
     a.xcd_remap = g.xcd_remap;
-    const size_t lds = ((size_t)(nw * wave_rows + np - 1) * pitch + 8) * sizeof(double);
     for (int k0 = 0; k0 < K; k0 += kp)
         for (int n0 = 0; n0 < N; n0 += np) {
             a.K = K - k0 < kp ? K - k0 : kp;

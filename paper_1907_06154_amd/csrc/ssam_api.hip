@@ -160,25 +160,25 @@ hipError_t launch_generic(const T* in, T* out, int W, int H, int D, const T* c, 
 hipError_t launch_direct(const void* in, void* out, int W, int H, int D, const void* c, int M, int N, int K, int ax, int ay, int az,
                          int boundary, bool skip_zero, int dtype, hipStream_t stream, const Tuning& tu, Geometry* geo, bool dry)
 {
+    if (dtype == SSAM_F64) {
+        const double* w = static_cast<const double*>(c);
+        bool dense = tu.force_generic <= 0 && (long)M * N * K >= 9;
+        for (long i = 0; dense && skip_zero && i < (long)M * N * K; ++i) dense = w[i] != 0.0;
+        if (dense) {
+            const hipError_t e = launch_dense((const double*)in, (double*)out, W, H, D, w, M, N, K, ax, ay, az, boundary, stream, geo, dry);
+            if (e != hipErrorNotSupported) return e;
+        }
+    }
     if (geo) {
         *geo = Geometry();
         geo->blocks = ceil_div(W, 64) * ceil_div(H, 4) * D;
     }
-    if (dtype == SSAM_F32) {
-        if (dry) return hipSuccess;
+    if (dry) return hipSuccess;
+    if (dtype == SSAM_F32)
         return launch_generic<float>((const float*)in, (float*)out, W, H, D, (const float*)c, M, N, K, ax, ay, az, boundary, skip_zero,
                                      stream);
-    }
-    const double* w = static_cast<const double*>(c);
-    bool dense = tu.force_generic <= 0 && (long)M * N * K >= 9;
-    for (long i = 0; dense && skip_zero && i < (long)M * N * K; ++i) dense = w[i] != 0.0;
-    if (dense) {
-        const hipError_t e = launch_dense((const double*)in, (double*)out, W, H, D, w, M, N, K, ax, ay, az, boundary, stream, tu,
-                                          nullptr, dry);
-        if (e != hipErrorNotSupported) return e;
-    }
-    if (dry) return hipSuccess;
-    return launch_generic<double>((const double*)in, (double*)out, W, H, D, w, M, N, K, ax, ay, az, boundary, skip_zero, stream);
+    return launch_generic<double>((const double*)in, (double*)out, W, H, D, (const double*)c, M, N, K, ax, ay, az, boundary, skip_zero,
+                                  stream);
 }
 
 // ---- plain copy (measurement aid) ---------------------------------------------------------
@@ -583,9 +583,9 @@ int describe(int rc, const std::string& name, const Geometry& g, char* buf, int 
     if (buf && buflen > 0) {
         snprintf(buf, (size_t)buflen,
                  "%s V=%d P=%d halo_lanes=%d+%d valid_lanes=%d strips_x=%d tiles_y=%d tiles_z=%d rows_per_wave=%d "
-                 "planes_per_wave=%d tiles=%ld blocks=%d xcd_remap=%d",
+                 "planes_per_wave=%d tiles=%ld blocks=%d xcd_remap=%d lds=%d form=%d",
                  name.c_str(), g.V, g.P, g.halo_left, g.halo_right, g.valid_lanes, g.strips_x, g.tiles_y, g.tiles_z,
-                 g.rows_per_wave, g.planes_per_wave, g.tiles, g.blocks, g.xcd_remap);
+                 g.rows_per_wave, g.planes_per_wave, g.tiles, g.blocks, g.xcd_remap, g.lds, g.form);
     }
     return rc;
 }

@@ -69,6 +69,8 @@ struct Geometry {
     long tiles = 0;            // waves with work
     int blocks = 0;            // launched blocks (padded to a multiple of 8 when remapped)
     int xcd_remap = 0;
+    int lds = 0;               // bytes of LDS a block asks for at launch (dynamic)
+    int form = 0;              // 1: the staged form of a block-cooperative 3D kernel; the register-tiled kernel instead of the direct one
 };
 
 typedef hipError_t (*Launch2DFn)(const Problem2D&, const Tuning&, Geometry*, bool dry_run);

@@ -627,6 +627,7 @@ hipError_t launch3d_star(const Problem3D& pr, const Tuning& tu, Geometry* geo, b
             return launch3d_star<T, 2, NW, R, BUDGET, NBUF, NT, FALLBACK>(pr, tu, geo, dry_run);
     }
     Geometry g;
+    g.form = staged ? 1 : 0;
     g.V = V;
     g.P = P;
     g.halo_left = g.halo_right = 0;

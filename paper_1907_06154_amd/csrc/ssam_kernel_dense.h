@@ -159,6 +159,6 @@ __global__ __launch_bounds__(NW* kWave) void dense_kernel(const DenseArgs a)
 
 // Filter w[K][N][M] anchored at (ax, ay, az), in as many launches as the launch arguments need.
 hipError_t launch_dense(const double* in, double* out, int W, int H, int D, const double* w, int M, int N, int K, int ax, int ay,
-                        int az, int boundary, hipStream_t stream, const Tuning& tu, Geometry* geo, bool dry_run);
+                        int az, int boundary, hipStream_t stream, Geometry* geo, bool dry_run);
 
 }  // namespace ssam

@@ -43,3 +43,27 @@ def test_a_tap_far_below_the_largest():
         for e, split in ((-59, True), (-61, False), (-80, False)):
             f.flat[3] = 2.0 ** e
             assert ("split3mx" in route(kind, shape, f)) == split, (kind, e)
+
+
+def plan(kind, shape, filt, boundary="zero"):
+    name, *fields = ssam.ssam_describe(kind, shape, filt, boundary).split()
+    return name, {k: v for k, v in (f.split("=") for f in fields)}
+
+
+def test_the_description_is_of_the_launch_that_is_made():
+    """Kernels that go by another's name: the register-tiled fp64 kernel instead of the direct one, the staged and the
+    two-row forms of the block-cooperative 3D kernel."""
+    for shape, filt in (((1500, 1600), np.ones((12, 12))), ((1500, 1600), np.ones((32, 32)))):
+        name, g = plan("conv2d", shape, filt)
+        assert name == "generic_direct" and g["form"] == "1" and int(g["lds"]) > 0
+        assert int(g["strips_x"]) * int(g["tiles_y"]) * int(g["tiles_z"]) == int(g["tiles"]) <= int(g["blocks"]) < int(g["tiles"]) + 8
+        assert int(g["strips_x"]) * 64 >= 1600 and int(g["tiles_y"]) * 64 >= 1500
+    name, g = plan("conv2d", (1500, 1600), np.ones((12, 12), dtype=np.float32))
+    assert "split3mx" in name and g["form"] == "0" and int(g["lds"]) > 0
+    star = np.zeros((3, 3, 3))
+    star[1, 1, :] = star[1, :, 1] = star[:, 1, 1] = 1.0
+    for W, form in ((200, "0"), (201, "1")):
+        name, g = plan("stencil3d", (200, 200, W), star)
+        assert "p4w8star_ring3" in name and g["form"] == form, (W, g)
+    assert plan("stencil3d", (512, 512, 512), star)[1]["P"] == "4"
+    assert plan("stencil3d", (40, 40, 40), star)[1]["P"] == "2"
