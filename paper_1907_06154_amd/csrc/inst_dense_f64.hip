@@ -9,19 +9,21 @@ hipError_t launch_dense(const double* in, double* out, int W, int H, int D, cons
     // parts of a filter: whole rows of one or more planes, at most kDenseTaps values; output planes two by two in 3D
     const int kmax = kDenseTaps / (M * N) > 0 ? kDenseTaps / (M * N) : 1;
     const int kp = ceil_div(K, ceil_div(K, kmax < K ? kmax : K));                      // as even as possible
-    const int nmax = kDenseTaps / (M * kp) < N ? kDenseTaps / (M * kp) : N;            // (M * kp: below 32)
+    const int nmax = kDenseTaps / (M * kp) < N ? kDenseTaps / (M * kp) : N;            // M N kp <= kDenseTaps, or kp is 1
     const int np = ceil_div(N, ceil_div(N, nmax));
     const int tz = K > 1 && D > 1 ? 2 : 1;
-    // Waves stacked in a block: four share the halo rows; fewer where the grid would leave compute units idle.
+    // Waves stacked in a block: four share the halo rows; fewer where the grid would leave compute units idle, or where eight
+    // lanes side by side (32 rows per wave) and a large filter would need more than the 64 KB of LDS a launch may ask for.
     const int lane_cols = W <= 40 || (W % 64 > 0 && W % 64 <= 32 && W < 200) ? 3 : 4;
     const int wave_rows = 4 * (kWave >> lane_cols);
     const int tiles_x = ceil_div(W, 4 << lane_cols), tiles_z = ceil_div(D, tz);
-    int nw = 4;
-    while (nw > 1 && (long)tiles_x * ceil_div(H, nw * wave_rows) * tiles_z * nw < 2048) nw /= 2;
     const int pitch = ((4 << lane_cols) + M + 8) & ~1;      // a lane's last window ends up to four columns past the tile
+    auto lds_of = [&](int waves) { return ((size_t)(waves * wave_rows + np - 1) * pitch + 8) * sizeof(double); };
+    int nw = 4;
+    while (nw > 1 && ((long)tiles_x * ceil_div(H, nw * wave_rows) * tiles_z * nw < 2048 || lds_of(nw) > (64u << 10))) nw /= 2;
     const int tiles_y = ceil_div(H, nw * wave_rows);
     const long tiles = (long)tiles_x * tiles_y * tiles_z;
-    const size_t lds = ((size_t)(nw * wave_rows + np - 1) * pitch + 8) * sizeof(double);
+    const size_t lds = lds_of(nw);
     Geometry g;
     g.V = 4;
     g.P = 4;

@@ -66,6 +66,16 @@ def test_volumes(ssam, M, N, K, boundary):
         check(got, plain, oracle.conv3d(vol, filt, boundary, anchor), filt, (M, N, K, boundary, vol.shape))
 
 
+@pytest.mark.parametrize("H,W,M,N", [(13200, 160, 20, 20), (65536, 32, 21, 21), (65536, 40, 32, 14), (13200, 160, 12, 12)])
+def test_tall_narrow_pictures(ssam, H, W, M, N):
+    """Blocks of up to four waves of 32 rows: the largest staged tiles."""
+    filt = wl.seeded_filter(M, N, 1045, np.float64)
+    d = torch.from_numpy(wl.uniform_field((H, W), -1.0, 1.0, 1046, np.float64)).cuda()
+    print(f"dense f64 {M}x{N} {H}x{W}", flush=True)
+    got, plain = both(ssam, lambda: ssam.ssam_conv2d(d, filt, "clamp"))
+    check(got, plain, plain, filt, (M, N, H, W))
+
+
 def test_infinities_and_nan_reach_their_footprint_only(ssam):
     filt = wl.seeded_filter(13, 14, 1040, np.float64)
     img = wl.uniform_field((90, 140), -1.0, 1.0, 1041, np.float64)

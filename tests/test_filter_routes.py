@@ -67,3 +67,11 @@ def test_the_description_is_of_the_launch_that_is_made():
         assert "p4w8star_ring3" in name and g["form"] == form, (W, g)
     assert plan("stencil3d", (512, 512, 512), star)[1]["P"] == "4"
     assert plan("stencil3d", (40, 40, 40), star)[1]["P"] == "2"
+
+
+@pytest.mark.parametrize("shape", [(13200, 160), (65536, 40), (65536, 32), (22000, 90), (40000, 64)])
+def test_fp64_filters_on_tall_narrow_pictures_fit_the_lds_of_a_block(shape):
+    """Eight lanes side by side make a wave 32 rows tall; four of them and a large filter's halo pass 64 KB."""
+    for M, N in ((20, 20), (21, 21), (25, 25), (32, 14), (32, 32), (12, 12)):
+        name, g = plan("conv2d", shape, np.ones((N, M)))
+        assert g["form"] == "1" and 0 < int(g["lds"]) <= 64 << 10, (shape, M, N, g)
