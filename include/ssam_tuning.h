@@ -17,7 +17,8 @@ extern "C" {
 
 /* Tuning override for experiments and benchmarks (not needed for correct use): sets a named
  * integer launch parameter for subsequent calls, process-wide.  Names: "rows_per_wave",
- * "valid_lanes", "planes_per_wave", "xcd_remap", "force_generic", "variant" (an alternative
+ * "valid_lanes", "planes_per_wave", "xcd_remap", "force_generic" (1 = the direct one-point-per-thread kernel
+ * for every shape, 2 = the same but the register-tiled kernel for fp64 boxes without zeros), "variant" (an alternative
  * compiled instance of the same shape, where one exists; e.g. 5 = the vector-unit instance of a dense
  * fp32 filter whose default instance evaluates its products on the matrix cores, 0 = its instance on the
  * fp32 matrix instructions where the default is the one on the bf16 ones), "march_axis" (3D: 0 = march along z,

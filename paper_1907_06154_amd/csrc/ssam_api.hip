@@ -155,14 +155,32 @@ hipError_t launch_generic(const T* in, T* out, int W, int H, int D, const T* c, 
     return hipSuccess;
 }
 
-// What no compiled shape takes.  fp64 boxes without a zero (or whose zeros are taps) run on the register-tiled kernel; sparse
-// tap lists and fp32 on the one-point-per-thread kernel.
+// Whether an fp64 box without zeros goes to the register-tiled kernel instead of the one-point-per-thread one.  That kernel
+// issues its multiply-adds up to ten times as fast but needs work to fill the machine with: a lane makes 4 x 4 outputs, in 3D
+// of two planes, and a block goes through the filter's planes one after the other, a barrier each.  Ratio of the times,
+// register-tiled to direct, from 2100 pairs of shape and grid:
+//   one filter plane: 0.05 .. 0.95 from 800000 points on; 512^2: 16x16 0.5, 12x12 0.64, 12x4 0.88, 4x12 1.02, 16x1 1.4, 1x16
+//   1.8; 700^2: 12x3 0.77, 2x16 1.07, 1x32 1.2; 64^2 .. 360^2 alike: 24x24 0.6, 16x9 0.76, 9x16 0.9, 16x4 1.0, 3x12 1.6
+//   several: 64^3 1.4 (13x9x3) .. 10 (1x1x13); 72^3 9x9x3 0.82, 9x5x3 1.03; 88^3 9x3x3 0.98; 96^3 7x3x3 1.0, 3x3x9 1.5; 128^3
+//   3x3x9 0.88, 9x1x3 1.0, 1x9x3 1.1, 2x2x9 1.5; 256^3 3x2x9 0.73, 5x1x9 0.87, 1x5x9 0.89, 2x2x9 1.04, 1x1x9 2.2
+bool dense_is_faster(long points, int M, int N, int K)
+{
+    const long plane = (long)M * N;      // taps of a filter plane
+    if (plane * K < 9) return false;
+    if (K == 1)
+        return points >= 800000 || (points >= 450000 && M >= 3) || (M >= 4 && points * plane >= 13000000) || (M >= 9 && plane >= 100);
+    if (points < 350000 || (M == 1 && points < 6000000)) return false;
+    return (plane >= 9 && points * plane >= 18500000) || (plane >= 5 && points * plane >= 70000000);
+}
+
+// What no compiled shape takes.  fp64 boxes without a zero (or whose zeros are taps) run on the register-tiled kernel where it
+// is the faster one; sparse tap lists and fp32 on the one-point-per-thread kernel.
 hipError_t launch_direct(const void* in, void* out, int W, int H, int D, const void* c, int M, int N, int K, int ax, int ay, int az,
                          int boundary, bool skip_zero, int dtype, hipStream_t stream, const Tuning& tu, Geometry* geo, bool dry)
 {
     if (dtype == SSAM_F64) {
         const double* w = static_cast<const double*>(c);
-        bool dense = tu.force_generic <= 0 && (long)M * N * K >= 9;
+        bool dense = tu.force_generic == 2 || (tu.force_generic <= 0 && dense_is_faster((long)W * H * D, M, N, K));
         for (long i = 0; dense && skip_zero && i < (long)M * N * K; ++i) dense = w[i] != 0.0;
         if (dense) {
             const hipError_t e = launch_dense((const double*)in, (double*)out, W, H, D, w, M, N, K, ax, ay, az, boundary, stream, geo, dry);
@@ -503,10 +521,11 @@ int run_conv3d(const void* in, void* out, int W, int H, int D, const void* f, in
     const long waste = tu.embed_waste > 0 ? tu.embed_waste : 8;
     bool cube = R >= 1 && R <= 3 && tu.force_generic <= 0 && tu.embed_waste != 0 &&
                 (long)(2 * R + 1) * (2 * R + 1) * (2 * R + 1) <= waste * M * N * K;
-    // fp64: the radius-3 cube costs 343 taps whatever it holds and is slow on small grids; the direct kernel is faster for fewer
-    // taps (5x6x4: 64^3 264 -> 80 us, 256^3 561 -> 447) and, for the full cube, on grids of up to a few million points (64^3
-    // 264 -> 150 us; 256^3 561 and 791)
-    if (dtype == SSAM_F64 && R == 3 && tu.variant < 0 && ((long)M * N * K < 200 || (long)W * H * D < (4L << 20))) cube = false;
+    // fp64: the radius-3 cube costs 343 taps whatever it holds and is slow on small grids; the kernels of launch_direct are
+    // faster for fewer taps (5x6x4 on 256^3: 561 -> 447 us) and, for the full cube, on grids of up to a few million points
+    // (64^3: 264 -> 84; 256^3: 561 and 791)
+    if (dtype == SSAM_F64 && R == 3 && tu.variant < 0 && ((long)M * N * K < 200 || (long)W * H * D < (4L << 20)))
+        cube = false;
     if (dtype == SSAM_F32 && split3d_is_faster(W, H, D, M, N, K, cube ? R : 0, tu)) {
         const hipError_t e = launch3d_split((const float*)in, (float*)out, W, H, D, (const float*)f, M, N, K, ax, ay, az, boundary,
                                             stream, tu, geo, dry);

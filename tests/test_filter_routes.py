@@ -75,3 +75,20 @@ def test_fp64_filters_on_tall_narrow_pictures_fit_the_lds_of_a_block(shape):
     for M, N in ((20, 20), (21, 21), (25, 25), (32, 14), (32, 32), (12, 12)):
         name, g = plan("conv2d", shape, np.ones((N, M)))
         assert g["form"] == "1" and 0 < int(g["lds"]) <= 64 << 10, (shape, M, N, g)
+
+
+@pytest.mark.parametrize("shape,size,tiled", [
+    ((512, 515), (16, 16), 1), ((512, 515), (1, 16), 0), ((512, 515), (16, 1), 0), ((256, 259), (24, 24), 1), ((256, 259), (12, 3), 0),
+    ((1024, 1027), (1, 12), 1), ((64, 64, 64), (3, 9, 13), 0), ((64, 64, 64), (9, 1, 1), 0), ((128, 128, 128), (9, 3, 3), 1),
+    ((128, 128, 128), (9, 2, 2), 0), ((256, 256, 256), (9, 1, 1), 0), ((256, 256, 256), (9, 1, 7), 1)])
+def test_fp64_filters_take_the_register_tiled_kernel_where_it_is_faster(shape, size, tiled):
+    """Filters of a few taps per plane and grids too small to fill the machine stay on the direct kernel."""
+    filt = np.ones(size)
+    name, g = plan("conv2d" if len(shape) == 2 else "conv3d", shape, filt)
+    assert name == "generic_direct" and int(g["form"]) == tiled
+    for force, form in ((1, 0), (2, 1)):
+        ssam.ssam_set_tuning("force_generic", force)
+        try:
+            assert int(plan("conv2d" if len(shape) == 2 else "conv3d", shape, filt)[1]["form"]) == form
+        finally:
+            ssam.ssam_set_tuning("force_generic", -1)
