@@ -524,7 +524,7 @@ int run_conv3d(const void* in, void* out, int W, int H, int D, const void* f, in
     // fp64: the radius-3 cube costs 343 taps whatever it holds and is slow on small grids; the kernels of launch_direct are
     // faster for fewer taps (5x6x4 on 256^3: 561 -> 447 us) and, for the full cube, on grids of up to a few million points
     // (64^3: 264 -> 84; 256^3: 561 and 791)
-    if (dtype == SSAM_F64 && R == 3 && tu.variant < 0 && ((long)M * N * K < 200 || (long)W * H * D < (4L << 20)))
+    if (dtype == SSAM_F64 && R == 3 && tu.variant < 0 && tu.embed_waste < 0 && ((long)M * N * K < 200 || (long)W * H * D < (4L << 20)))
         cube = false;
     if (dtype == SSAM_F32 && split3d_is_faster(W, H, D, M, N, K, cube ? R : 0, tu)) {
         const hipError_t e = launch3d_split((const float*)in, (float*)out, W, H, D, (const float*)f, M, N, K, ax, ay, az, boundary,

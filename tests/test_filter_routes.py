@@ -92,3 +92,13 @@ def test_fp64_filters_take_the_register_tiled_kernel_where_it_is_faster(shape, s
             assert int(plan("conv2d" if len(shape) == 2 else "conv3d", shape, filt)[1]["form"]) == form
         finally:
             ssam.ssam_set_tuning("force_generic", -1)
+
+
+def test_embed_waste_asks_for_the_cube():
+    filt = np.ones((4, 6, 5))
+    assert route("conv3d", (64, 64, 64), filt) == "generic_direct"
+    ssam.ssam_set_tuning("embed_waste", 4)
+    try:
+        assert route("conv3d", (64, 64, 64), filt).endswith("+embedded")
+    finally:
+        ssam.ssam_set_tuning("embed_waste", -1)
