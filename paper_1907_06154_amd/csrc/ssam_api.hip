@@ -268,14 +268,19 @@ const Instance2D* pick2d(const Problem2D& p, bool stencil_semantics, int want_va
 // 138-147 us for 6x6 .. 9x9), so the line lies where the other instances reach it: boxes up to 6x6 and the flat shapes with
 // instances of their own (3x11, 11x3, 1 x n) stay bandwidth-bound on the vector unit (104 us at 6x6); 7x7 takes 127 us
 // there and is only faster here on smaller pictures (1024^2: 11.2 -> 8.9 us, 4096^2: 36.7 and 39.4) and on rows that are
-// not whole 16-byte pieces (4003x3001: 44.3 -> 32.5); from 8x8 on (145 us, equal) it is faster everywhere.  Pictures of a
-// few tiles gain nothing, and a strip narrower than a wave's 64 columns would be mostly empty.
+// not whole 16-byte pieces (4003x3001: 44.3 -> 32.5); from 8x8 on (145 us, equal) it is faster on large pictures.  On small ones
+// the box instances with short tiles are faster (9x9 on 700^2 5.8 us against 8.5, on 1500^2 12.2 against 14.2) but three times as
+// far from 64-bit sums, so the line stays.  Pictures of a few tiles gain nothing, and a strip narrower than a wave's 64 columns
+// would be mostly empty.  Of a filter one or two columns wide a piece of eight is mostly zeros: beyond the boxes (more than 20
+// rows) the direct kernel keeps it on small pictures (1x32: 130^2 12 us against 16, 512^2 10.5 and 15.5, 700^2 14.9 and 18.6;
+// 2x24: 256^2 12 and 21, 512^2 equal).
 bool split_is_faster(const Problem2D& p, const Instance2D* inst, const Instance2D* box, const Tuning& tu)
 {
     const long points = (long)p.W * p.H;
     if (p.dtype != SSAM_F32 || tu.force_generic > 0 || tu.variant >= 0 || tu.embed_waste >= 0) return false;
     if (points < 16384 || p.W < 64) return false;
     if (inst && (inst->budget != 2 || inst->M < 7 || inst->N < 7)) return false;
+    if (!inst && !box && (p.M == 1 ? points < 1000000 : p.M == 2 && points < 150000)) return false;
     const int edge = inst ? inst->M : box ? box->M : SSAM_MAX_FILTER;
     if (edge == 7) return p.W % 4 != 0 || points < (4L << 20);
     return edge > 7;

@@ -102,3 +102,11 @@ def test_embed_waste_asks_for_the_cube():
         assert route("conv3d", (64, 64, 64), filt).endswith("+embedded")
     finally:
         ssam.ssam_set_tuning("embed_waste", -1)
+
+
+@pytest.mark.parametrize("M,N,H,W,split", [(1, 32, 512, 512, False), (1, 22, 130, 130, False), (1, 32, 1100, 1100, True), (2, 24, 256, 256, False),
+                                           (2, 24, 512, 512, True), (3, 24, 256, 256, True), (32, 1, 512, 512, True), (1, 20, 512, 512, True)])
+def test_tall_thin_fp32_filters_on_small_pictures(M, N, H, W, split):
+    """One or two columns and more than 20 rows: the direct kernel, which is faster there."""
+    name = route("conv2d", (H, W), np.ones((N, M), dtype=np.float32))
+    assert ("split3mx" in name) == split and (split or name == "generic_direct"), name
