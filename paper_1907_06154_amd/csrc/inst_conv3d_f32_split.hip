@@ -79,6 +79,7 @@ hipError_t launch3d_split(const float* in, float* out, int W, int H, int D, cons
         }
     }
     if (planes > D) planes = D;
+    if (planes > kSplitMaxBands) planes = kSplitMaxBands;
     Geometry g;
     g.V = 4;
     g.P = 4 * part.tb;

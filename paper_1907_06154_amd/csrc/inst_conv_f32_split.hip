@@ -112,6 +112,7 @@ hipError_t launch2d_split(const Problem2D& pr, const Tuning& tu, Geometry* geo, 
     g.valid_lanes = 16 * nx;
     g.strips_x = ceil_div(pr.W, 64 * nx);
     if (rows > ceil_div(pr.H, 4) * 4) rows = ceil_div(pr.H, 4) * 4;
+    if (rows > 4 * kSplitMaxBands) rows = 4 * kSplitMaxBands;
     while ((long)g.strips_x * ceil_div(pr.H, rows) > 4 * kMaxBlocks) rows *= 2;
     g.rows_per_wave = rows;
     g.tiles_y = ceil_div(pr.H, rows);

@@ -37,6 +37,7 @@ typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));   // element-aligned 16-byte access
+typedef float f32x3u __attribute__((ext_vector_type(3), aligned(4)));
 
 constexpr int kSplitMaxTaps = 672;          // taps of one launch (a 32-wide filter of 21 rows)
 constexpr float kSplitScaleIn = 0x1p24f;    // inputs are multiplied by this
@@ -82,6 +83,129 @@ __device__ __forceinline__ void split3(const float (&f)[4], u32x2& h, u32x2& m, 
     }
 }
 
+
+// ---- values the split does not carry: plain multiply-adds -----------------------------------------------------------------
+// A wave notes the bands (planes) of outputs that such a value reaches and stores nothing there; the block makes them after the
+// march, when the accumulators' registers are free: band o is bit o / 64 of lane o % 64's word.
+// Made by the wave itself within the march, a load per four multiply-adds, they were most of the time as soon as one value was
+// not finite.  4096^2 / 256^3, us: no NaN | 17 of them | one value in 10^4 | all:
+//   9x9    before 43 | 196 | 679 | 989      now 43 | 57 | 100 | 218      (fp32 matrix instructions: 49 .. 53 whatever the values)
+//   20x20  before 93 | 1378 | 3669 | 4074   now 93 | 127 | 430 | 694     (220 .. 245)
+//   5x5x5  before 61 | 1326 | 2557 | 2872   now 60 | 127 | 328 | 392     (vector unit: 102)
+constexpr int kSplitMaxBands = 64 * 32;
+__device__ __forceinline__ void note_band(unsigned& redo, int lane, int o) { redo |= (lane == (o & 63) ? 1u : 0u) << (o >> 6); }
+__device__ __forceinline__ bool band_noted(unsigned redo, int o)
+{
+    return ((unsigned)__builtin_amdgcn_readlane((int)redo, o & 63) >> (o >> 6)) & 1u;
+}
+
+// f holds the four columns from clamp(x, 0, W - 4) on, |d| columns away from x; makes element e column clamp(x + e, 0, W - 1).
+__device__ __forceinline__ void move_columns(float (&f)[4], int d)
+{
+    const float f0 = f[0], f3 = f[3];
+    const bool r2 = d >= 2, r1 = d >= 3 || d == 1, l2 = d <= -2, l1 = d <= -3 || d == -1;
+    f[0] = r2 ? f[2] : f[0]; f[1] = r2 ? f3 : f[1]; f[2] = r2 ? f3 : f[2];
+    f[0] = r1 ? f[1] : f[0]; f[1] = r1 ? f[2] : f[1]; f[2] = r1 ? f3 : f[2];
+    f[3] = l2 ? f[1] : f[3]; f[2] = l2 ? f0 : f[2]; f[1] = l2 ? f0 : f[1];
+    f[3] = l1 ? f[2] : f[3]; f[2] = l1 ? f[1] : f[2]; f[1] = l1 ? f0 : f[1];
+}
+
+// s[b][e] = the sum over `planes` x `rows` filter rows of M taps at columns col[b] + e, b < B: B independent rows, or parts of
+// one.  plane_at(k) is the (wave-uniform) start of filter plane k's input plane, row_at(k, r, b, keep) the offset in it of filter
+// row (k, r)'s input row, both moved into the grid; it clears keep where the row counts as zeros.  Eight taps are a step: three
+// pieces of four columns and eight weights, requested a step ahead.  INSIDE: rows, planes and columns col[b] .. col[b] +
+// plain_reach(M) - 1 lie inside the grid for every lane.
+constexpr int plain_reach(int M) { return (M + 7) / 8 * 8 + 4; }
+template <int B, bool INSIDE, class PlaneAt, class RowAt>
+__device__ __forceinline__ void plain_sums(int planes, int rows, const PlaneAt& plane_at, const RowAt& row_at, const int (&col)[B], int W,
+                                           bool clamp, const ConstPtr<float> w, int M, float (&s)[B][4])
+{
+    const int lane = threadIdx.x & (kWave - 1);
+    float win[2][B][12], wm[2];              // wm: lane i's is the step's weight i % 8 (scalar loads return in any order: a wait
+    unsigned keep[2][B];                     // for one step's would be a wait for the next one's)
+    int k = 0, r = 0, m = 0;                 // the step that is requested next; the last one again after the last
+    auto request = [&](auto buf) __attribute__((always_inline)) {
+        constexpr int H = decltype(buf)::value;
+        const float* const pk = plane_at(k);
+#pragma unroll
+        for (int b = 0; b < B; ++b) {
+            keep[H][b] = ~0u;
+            const int row = row_at(k, r, b, keep[H][b]);
+#pragma unroll
+            for (int q = 0; q < 3; ++q) {
+                const int x = col[b] + m + 4 * q;
+                if (INSIDE && q == 2) {      // column 11 has no use, and the compiler gives its register away while the load runs
+                    const f32x3u v = *reinterpret_cast<const f32x3u*>(pk + (row + x));
+#pragma unroll
+                    for (int e = 0; e < 3; ++e) win[H][b][4 * q + e] = v[e];
+                } else {
+                    const f32x4u v = *reinterpret_cast<const f32x4u*>(pk + (row + (INSIDE ? x : min(max(x, 0), W - 4))));
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) win[H][b][4 * q + e] = v[e];
+                }
+            }
+        }
+        wm[H] = w[(k * rows + r) * M + min(m + (lane & 7), M - 1)];
+        const bool row_end = m + 8 >= M, plane_end = row_end && r + 1 >= rows, end = plane_end && k + 1 >= planes;
+        m = end ? m : row_end ? 0 : m + 8;
+        r = end ? r : plane_end ? 0 : row_end ? r + 1 : r;
+        k = end || !plane_end ? k : k + 1;
+    };
+    auto take = [&](auto buf, int m0) __attribute__((always_inline)) {
+        constexpr int H = decltype(buf)::value;
+        if constexpr (!INSIDE) {
+#pragma unroll
+            for (int b = 0; b < B; ++b)
+#pragma unroll
+                for (int q = 0; q < 3; ++q) {
+                    const int x = col[b] + m0 + 4 * q;
+                    if (!__any(x < 0 || x + 4 > W || keep[H][b] != ~0u)) continue;     // most pieces of an edge strip lie inside
+                    float f[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) f[e] = win[H][b][4 * q + e];
+                    move_columns(f, x - min(max(x, 0), W - 4));
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        win[H][b][4 * q + e] = keep_if(f[e], (clamp || (x + e >= 0 && x + e < W)) ? keep[H][b] : 0u);
+                }
+        }
+        auto tap = [&](int i) __attribute__((always_inline)) {
+            const float wi = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, wm[H]), i));
+#pragma unroll
+            for (int b = 0; b < B; ++b)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) s[b][e] = fma_t(win[H][b][i + e], wi, s[b][e]);
+        };
+        if (m0 + 8 <= M) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) tap(i);
+        } else {
+#pragma unroll
+            for (int i = 0; i < 7; ++i)
+                if (m0 + i < M) tap(i);      // taps beyond the row are not multiplied: what lies there need not be finite
+        }
+    };
+#pragma unroll
+    for (int b = 0; b < B; ++b)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) s[b][e] = 0.0f;
+    typedef std::integral_constant<int, 0> Even;
+    typedef std::integral_constant<int, 1> Odd;
+    const int per_row = (M + 7) / 8, steps = planes * rows * per_row;
+    int m0 = 0;
+    auto next = [&]() __attribute__((always_inline)) { m0 = m0 + 8 < M ? m0 + 8 : 0; };
+    request(Even{});
+    int i = 0;
+    for (; i + 1 < steps; i += 2) {
+        request(Odd{});
+        take(Even{}, m0);
+        next();
+        request(Even{});
+        take(Odd{}, m0);
+        next();
+    }
+    if (i < steps) take(Even{}, m0);
+}
 
 // Fences the LDS traffic of one wave: what its lanes wrote before is what its lanes read after (the
 // hardware keeps a wave's LDS accesses in order; this keeps the compiler from exchanging them).
@@ -210,58 +334,32 @@ __global__ __launch_bounds__(NW* kWave) __attribute__((amdgpu_waves_per_eu(2))) 
         for (int n = 0; n < NX; ++n) before[s][n] = u32x2{0u, 0u};
 
     unsigned bad = 0;      // bit k: the band staged k steps ago holds a value the split does not carry
+    unsigned redo = 0;     // output bands such a value reaches
+
+    // Four outputs from column x on, row y of a tile that ends before row yend.
+    auto store_quad = [&](auto inside_tag, int x, int y, int yend, v4f v) __attribute__((always_inline)) {
+        constexpr bool INSIDE = decltype(inside_tag)::value;
+        if (y >= yend) return;
+        float* const rowp = a.out + (size_t)y * W;
+        if (INSIDE || x + 4 <= W) {
+            f32x4u* const p = reinterpret_cast<f32x4u*>(rowp + x);
+            if (a.accumulate) v += (v4f)*p;
+            __builtin_nontemporal_store((f32x4u)v, p);
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (x + e < W) rowp[x + e] = a.accumulate ? rowp[x + e] + v[e] : v[e];
+        }
+    };
 
     // Stores output band o, which the step before has completed.  touched: `bad` as it was after that step.
     auto store_band = [&](auto inside_tag, int o, unsigned touched) __attribute__((always_inline)) {
-        constexpr bool INSIDE = decltype(inside_tag)::value;
         if ((touched & ((1u << NB) - 1)) == 0) {
-            const int y = y0 + 4 * o + kg;
-            float* rowp = a.out + (size_t)y * W;
-            if (y < y1) {
 #pragma unroll
-                for (int n = 0; n < NX; ++n) {
-                    const int x = x0 + 64 * n + 4 * j;
-                    v4f v = (acc[NB - 1][n] + low[NB - 1][n]) * a.out_scale;
-                    if (INSIDE || x + 4 <= W) {
-                        f32x4u* const p = reinterpret_cast<f32x4u*>(rowp + x);
-                        if (a.accumulate) v += (v4f)*p;
-                        __builtin_nontemporal_store((f32x4u)v, p);
-                    } else {
-#pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            if (x + e < W) rowp[x + e] = a.accumulate ? rowp[x + e] + v[e] : v[e];
-                    }
-                }
-            }
+            for (int n = 0; n < NX; ++n)
+                store_quad(inside_tag, x0 + 64 * n + 4 * j, y0 + 4 * o + kg, y1, (acc[NB - 1][n] + low[NB - 1][n]) * a.out_scale);
         } else {
-            // plain multiply-adds: an input in reach is not finite, or too large to be split
-            for (int n = 0; n < NX; ++n) {
-                const int x = x0 + 64 * n + lane;
-                if (x >= W) continue;
-                float s[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-                for (int k = 0; k < N + 3; ++k) {
-                    const int y = y0 + 4 * o + k - a.ay;
-                    const bool row_in = y >= 0 && y < H;
-                    const float* rowp = in + (size_t)min(max(y, 0), H - 1) * W;
-                    for (int m = 0; m < M; ++m) {
-                        const int xx = x + m - a.ax;
-                        const float f = rowp[min(max(xx, 0), W - 1)];
-                        const float v = (clamp || (row_in && xx >= 0 && xx < W)) ? f : 0.0f;
-#pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            if (k >= e && k - e < N) s[e] = fma_t(v, wts[(k - e) * M + m], s[e]);
-                    }
-                }
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const int y = y0 + 4 * o + e;
-                    if (y < y1) {
-                        float* const p = a.out + (size_t)y * W + x;
-                        *p = a.accumulate ? *p + s[e] : s[e];
-                    }
-                }
-            }
-            __builtin_amdgcn_s_waitcnt(0);   // nothing of this branch is left for the waits of the march to allow for
+            note_band(redo, lane, o);
         }
     };
 
@@ -285,14 +383,7 @@ __global__ __launch_bounds__(NW* kWave) __attribute__((amdgpu_waves_per_eu(2))) 
                     // column clamp(x + e)
                     const int x = xe + 4 * (16 * i + j);
                     const int d = x - min(max(x, 0), W - 4);
-                    const float f0 = f[0], f3 = f[3];
-                    {
-                        const bool r2 = d >= 2, r1 = d >= 3 || d == 1, l2 = d <= -2, l1 = d <= -3 || d == -1;
-                        f[0] = r2 ? f[2] : f[0]; f[1] = r2 ? f3 : f[1]; f[2] = r2 ? f3 : f[2];
-                        f[0] = r1 ? f[1] : f[0]; f[1] = r1 ? f[2] : f[1]; f[2] = r1 ? f3 : f[2];
-                        f[3] = l2 ? f[1] : f[3]; f[2] = l2 ? f0 : f[2]; f[1] = l2 ? f0 : f[1];
-                        f[3] = l1 ? f[2] : f[3]; f[2] = l1 ? f[1] : f[2]; f[1] = l1 ? f0 : f[1];
-                    }
+                    move_columns(f, d);
 #pragma unroll
                     for (int e = 0; e < 4; ++e)
                         f[e] = keep_if(f[e], keep & ((clamp || (x + e >= 0 && x + e < W)) ? ~0u : 0u)) * kSplitScaleIn;
@@ -428,6 +519,41 @@ __global__ __launch_bounds__(NW* kWave) __attribute__((amdgpu_waves_per_eu(2))) 
     };
     if (inside_x) march(Yes{});
     else march(No{});
+
+    // ---- the bands that were left out, of all the block's waves, one by one to each of them: a single value would otherwise
+    // keep one wave busy long after the others (every band of the filter's reach, a load's latency per step)
+    typedef __attribute__((address_space(3))) unsigned lds_unsigned;
+    ((lds_unsigned*)stage)[lane] = redo;
+    __syncthreads();
+    const int waves = (int)min((long)NW, a.tiles - (long)lb * NW);
+    int turn = 0;
+    for (int v = 0; v < waves; ++v) {
+        const unsigned noted = *((lds_unsigned*)((__attribute__((address_space(3))) char*)stage_raw + (size_t)v * 12 * pitch * 8) + lane);
+        if (!__any(noted != 0u)) continue;
+        const long vt = (long)lb * NW + v;
+        const int vx = (int)(vt % a.strips_x) * (64 * NX), vy = (int)(vt / a.strips_x) * a.rows, vend = min(vy + a.rows, H);
+        int col[NX];
+#pragma unroll
+        for (int n = 0; n < NX; ++n) col[n] = vx - a.ax + 64 * n + 4 * j;
+        const bool inside_cols = vx - a.ax >= 0 && vx - a.ax + 64 * NX - 4 + plain_reach(M) <= W;
+        for (int o = 0; vy + 4 * o < vend; ++o) {
+            if (!band_noted(noted, o) || turn++ % waves != wave) continue;
+            const int ys = vy - a.ay + 4 * o;            // first input row of the band
+            const bool inside = inside_cols && ys >= 0 && ys + 4 + N - 1 <= H;
+            auto plane_at = [&](int) __attribute__((always_inline)) { return in; };
+            auto row_at = [&](int, int r, int, unsigned& keep) __attribute__((always_inline)) {
+                const int y = ys + kg + r;
+                if (!clamp && (y < 0 || y >= H)) keep = 0u;
+                return min(max(y, 0), H - 1) * W;
+            };
+            float s[NX][4];
+            if (inside) plain_sums<NX, true>(1, N, plane_at, row_at, col, W, clamp, wts, M, s);
+            else plain_sums<NX, false>(1, N, plane_at, row_at, col, W, clamp, wts, M, s);
+#pragma unroll
+            for (int n = 0; n < NX; ++n)
+                store_quad(No{}, vx + 64 * n + 4 * j, vy + 4 * o + kg, vend, v4f{s[n][0], s[n][1], s[n][2], s[n][3]});
+        }
+    }
 }
 
 // The number of taps of w[0 .. count) that are not zero, and the largest one's binary exponent; 0 for a filter the split does

@@ -165,55 +165,32 @@ __global__ __launch_bounds__(kSplit3dWaves* kWave) __attribute__((amdgpu_waves_p
 #pragma unroll
         for (int b = 0; b < TB; ++b) acc[k][b] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
     unsigned bad = 0;         // bit s: the plane staged s steps ago holds a value the split does not carry
+    unsigned redo = 0;        // output planes such a value reaches
     float raw[RND][4];
+
+    // Four outputs from column x on.
+    auto store_quad = [&](auto inside_tag, int x, int y, int z, v4f v) __attribute__((always_inline)) {
+        constexpr bool INSIDE = decltype(inside_tag)::value;
+        if (y >= H) return;
+        float* const p0 = a.out + (size_t)z * plane + (size_t)y * W + x;
+        if (INSIDE || x + 4 <= W) {
+            f32x4u* const p = reinterpret_cast<f32x4u*>(p0);
+            if (a.accumulate) v += (v4f)*p;
+            __builtin_nontemporal_store((f32x4u)v, p);
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (x + e < W) p0[e] = a.accumulate ? p0[e] + v[e] : v[e];
+        }
+    };
 
     // Stores output plane o, which the step before has completed.  touched: `bad` as it was after that step.
     auto store_plane = [&](auto inside_tag, int o, unsigned touched) __attribute__((always_inline)) {
-        constexpr bool INSIDE = decltype(inside_tag)::value;
-        float* const po = a.out + (size_t)(z0 + o) * plane;
         if ((touched & ((1u << K) - 1)) == 0) {
 #pragma unroll
-            for (int n = 0; n < TB; ++n) {
-                const int y = y0 + 4 * n + kg, x = x0 + 4 * j;
-                float* const p0 = po + (size_t)y * W + x;
-                v4f v = acc[K - 1][n] * a.out_scale;
-                if (y < H) {
-                    if (INSIDE || x + 4 <= W) {
-                        f32x4u* const p = reinterpret_cast<f32x4u*>(p0);
-                        if (a.accumulate) v += (v4f)*p;
-                        __builtin_nontemporal_store((f32x4u)v, p);
-                    } else {
-#pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            if (x + e < W) p0[e] = a.accumulate ? p0[e] + v[e] : v[e];
-                    }
-                }
-            }
+            for (int n = 0; n < TB; ++n) store_quad(inside_tag, x0 + 4 * j, y0 + 4 * n + kg, z0 + o, acc[K - 1][n] * a.out_scale);
         } else {
-            // plain multiply-adds: an input in reach is not finite, or too large to be split
-            const int x = x0 + lane;
-            if (x < W) {
-                for (int y = y0; y < min(y0 + 4 * TB, H); ++y) {
-                    float s = 0.0f;
-                    for (int k = 0; k < a.K; ++k) {
-                        const int z = z0 - a.az + o + k;
-                        const float* pz = in + (size_t)min(max(z, 0), D - 1) * plane;
-                        for (int n = 0; n < N; ++n) {
-                            const int yy = y + n - a.ay;
-                            const bool row_in = z >= 0 && z < D && yy >= 0 && yy < H;
-                            const float* rowp = pz + (size_t)min(max(yy, 0), H - 1) * W;
-                            for (int m = 0; m < M; ++m) {
-                                const int xx = x + m - a.ax;
-                                const float f = rowp[min(max(xx, 0), W - 1)];
-                                s = fma_t((clamp || (row_in && xx >= 0 && xx < W)) ? f : 0.0f, wts[(k * N + n) * M + m], s);
-                            }
-                        }
-                    }
-                    float* const p = po + (size_t)y * W + x;
-                    *p = a.accumulate ? *p + s : s;
-                }
-            }
-            __builtin_amdgcn_s_waitcnt(0);   // nothing of this branch is left for the waits of the march to allow for
+            note_band(redo, lane, o);
         }
     };
 
@@ -357,6 +334,41 @@ __global__ __launch_bounds__(kSplit3dWaves* kWave) __attribute__((amdgpu_waves_p
     };
     if (inside) march(Yes{});
     else march(No{});
+
+    // ---- the planes that were left out, of all the block's waves, one by one to each of them, as in two dimensions
+    typedef __attribute__((address_space(3))) unsigned lds_unsigned;
+    ((lds_unsigned*)stage)[lane] = redo;
+    __syncthreads();
+    const int waves = (int)min((long)NW, a.tiles - (long)lb * NW);
+    int turn = 0;
+    for (int v = 0; v < waves; ++v) {
+        const unsigned noted = *((lds_unsigned*)(stage_base + (size_t)v * (3 * total * 8)) + lane);
+        if (!__any(noted != 0u)) continue;
+        const long vt = (long)lb * NW + v;
+        const int vx = (int)(vt % a.strips_x) * 64, vy = (int)((vt / a.strips_x) % a.tiles_y) * (4 * TB);
+        const int vz = (int)(vt / ((long)a.strips_x * a.tiles_y)) * a.planes, vend = min(vz + a.planes, D);
+        const int ys = vy - a.ay;
+        int col[TB];
+#pragma unroll
+        for (int n = 0; n < TB; ++n) col[n] = vx - a.ax + 4 * j;
+        const bool inside_xy = vx - a.ax >= 0 && vx - a.ax + 60 + plain_reach(M) <= W && ys >= 0 && ys + 4 * TB + N - 1 <= H;
+        for (int o = 0; vz + o < vend; ++o) {
+            if (!band_noted(noted, o) || turn++ % waves != wave) continue;
+            const int zs = vz - a.az + o;                // first input plane of the output plane
+            auto plane_at = [&](int k) __attribute__((always_inline)) { return in + (size_t)min(max(zs + k, 0), D - 1) * plane; };
+            auto row_at = [&](int k, int r, int n, unsigned& keep) __attribute__((always_inline)) {
+                const int z = zs + k, y = ys + 4 * n + kg + r;
+                if (!clamp && (z < 0 || z >= D || y < 0 || y >= H)) keep = 0u;
+                return min(max(y, 0), H - 1) * W;
+            };
+            float s[TB][4];
+            if (inside_xy && zs >= 0 && zs + a.K <= D) plain_sums<TB, true>(a.K, N, plane_at, row_at, col, W, clamp, wts, M, s);
+            else plain_sums<TB, false>(a.K, N, plane_at, row_at, col, W, clamp, wts, M, s);
+#pragma unroll
+            for (int n = 0; n < TB; ++n)
+                store_quad(No{}, vx + 4 * j, vy + 4 * n + kg, vz + o, v4f{s[n][0], s[n][1], s[n][2], s[n][3]});
+        }
+    }
 }
 
 typedef void (*Split3dKernel)(const ArgsSplit3D);

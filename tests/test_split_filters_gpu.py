@@ -308,3 +308,31 @@ def test_a_tap_far_below_the_largest_keeps_its_bits(ssam):
     filt[0, 0] = np.float32(1.7654321) * np.float32(2.0 ** -80)
     got = run(ssam, img, filt, "zero")[154, 154]
     assert abs(float(got) - float(img[150, 150]) * float(filt[0, 0])) <= 2.0 ** -23 * float(img[150, 150]) * float(filt[0, 0])
+
+
+@pytest.mark.parametrize("shape", [(9, 9), (20, 20), (25, 25), (1, 14), (5, 5, 5), (9, 9, 9), (5, 11, 10)])
+@pytest.mark.parametrize("boundary", ["clamp", "zero"])
+def test_many_values_the_split_does_not_carry(ssam, shape, boundary):
+    """A picture with a hole of NaN, and single infinities and large values beside it: bands that a block's waves share out
+    among themselves, inside the grid and at its edges, in filters of one part and of several."""
+    filt = np.random.default_rng(1200 + len(shape)).uniform(-1.0, 1.0, shape).astype(np.float32)
+    three = len(shape) == 3
+    size = (50, 61, 190) if three else (203, 521)
+    field = wl.uniform_field(size, -1.0, 1.0, 1201, np.float32)
+    field[..., 20:35, 60:95] = np.nan
+    rng = np.random.default_rng(1202)
+    for value in (np.inf, -np.inf, 1e31):
+        at = tuple(rng.integers(0, n, 6) for n in size)
+        field[at] = value
+    kind = "conv3d" if three else "conv2d"
+    assert "split3mx" in ssam.ssam_describe(kind, size, filt, boundary)
+    with np.errstate(invalid="ignore", over="ignore"):
+        want = (oracle.conv3d if three else oracle.conv2d)(field, filt, boundary)
+    for knob, value in (("rows_per_wave", -1), ("planes_per_wave" if three else "rows_per_wave", 24)):
+        ssam.ssam_set_tuning(knob, value)
+        try:
+            print(f"split {shape} {boundary} {knob} {value}", flush=True)
+            got = (run3 if three else run)(ssam, field, filt, boundary)
+        finally:
+            ssam.ssam_set_tuning(knob, -1)
+        assert_footprint(got, want, filt, 1e31, (shape, boundary, knob, value))
