@@ -11,7 +11,8 @@ typedef void (*SplitKernel)(const ArgsSplit2D, int);
 constexpr int kSplitWaves = 4;
 
 // Three strips of 64 columns per wave only up to four patch bands: with five and six the sums of three strips no longer
-// fit 256 registers (15x15 on 8192^2: 337 us spilling, 247 us with two strips; 20x20: 329 and 319).
+// fit 256 registers (15x15 on 8192^2: 337 us spilling, 247 us with two strips; 20x20: 329 and 319).  Four bands and a tail
+// piece spill seven registers with three strips and are still the fastest (9x13 on 8192^2 146 us, two strips 154).
 template <int NX, bool TAIL>
 SplitKernel split_kernel(int bands)
 {
@@ -83,9 +84,12 @@ hipError_t launch2d_split(const Problem2D& pr, const Tuning& tu, Geometry* geo, 
     // matrix and vector instructions add up (they were not seen to overlap): a step of four output rows issues 96 cycles
     // of matrix instructions per table piece and 64 columns, staging four input rows about 60 + 46 (nx + 1) vector
     // instructions, the bands - 1 steps above a tile included, and every workgroup builds the table once.  Four waves per
-    // SIMD, which one strip and a small table leave room for, hide more than two (9x9 on 8192^2: 143 us with one strip,
-    // 150 with three; with larger filters the table's traffic decides, 20x20: 358 with one strip, 319 with two).  A partly
-    // filled last round costs what its fullest SIMD does.
+    // SIMD, which one strip and a small table leave room for, hide more than two.  A partly filled last round costs what its
+    // fullest SIMD does.  Tiles of more than 512 rows save nothing more; pictures that would want taller ones (20x20 from
+    // 20000^2 on) are shared out in more rounds of 512.
+    // Measured with one, two, three strips (us): 9x9 on 8192^2 135, 135, 129 (chosen: three), 4003x3001 31.9, 33.8, 30.7
+    // (three), 2048^2 13.8, 14.3, 16.4 (two), 1024^2 9.8, 8.1, 9.6 (two); 9x13 on 8192^2 178, 154, 146 (three); 20x20 358, 319
+    // (two).  Over 100 pairs of filter and picture the choice was at most 16 % from the best, 2 % in the mean.
     int nx = 1, rows = 512;
     double best = 1e30;
     for (int cand = 1; cand <= (bands <= 4 ? 3 : 2); ++cand) {
@@ -94,7 +98,7 @@ hipError_t launch2d_split(const Problem2D& pr, const Tuning& tu, Geometry* geo, 
         for (int k = 0; k <= 3; ++k) {     // rows that give every SIMD one wave, then one, two, three fills of waves
             const long want = 1024L * (k == 0 ? 1 : k * per_simd) / strips;
             int r = ceil_div(ceil_div(pr.H, want < 1 ? 1 : (int)want), 4) * 4;
-            if (r > 512) continue;
+            if (r > 512) r = 512;
             if (tu.rows_per_wave > 0) r = ceil_div(tu.rows_per_wave, 4) * 4;
             const double busy = r / 4 * pieces * 96.0 * cand * (cand == 1 ? 1.1 : 1.0) +
                                 (r / 4 + bands - 1) * 4.0 * (60 + 46 * (cand + 1)) + 150.0 * pieces + 1500.0;

@@ -110,3 +110,16 @@ def test_tall_thin_fp32_filters_on_small_pictures(M, N, H, W, split):
     """One or two columns and more than 20 rows: the direct kernel, which is faster there."""
     name = route("conv2d", (H, W), np.ones((N, M), dtype=np.float32))
     assert ("split3mx" in name) == split and (split or name == "generic_direct"), name
+
+
+def test_large_pictures_keep_the_wide_strips():
+    """Tiles are at most 512 rows; a picture that would want taller ones keeps the strip width of the next smaller."""
+    filt = np.ones((20, 20), dtype=np.float32)
+    for n in (8192, 16384, 20000, 24000, 32768):
+        _, g = plan("conv2d", (n, n), filt, "clamp")
+        assert g["valid_lanes"] == "32" and int(g["rows_per_wave"]) <= 512, (n, g)
+    ssam.ssam_set_tuning("rows_per_wave", 64)
+    try:
+        assert plan("conv2d", (24000, 24000), filt)[1]["rows_per_wave"] == "64"
+    finally:
+        ssam.ssam_set_tuning("rows_per_wave", -1)
