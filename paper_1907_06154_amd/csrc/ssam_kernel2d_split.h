@@ -356,8 +356,12 @@ __global__ __launch_bounds__(NW* kWave) __attribute__((amdgpu_waves_per_eu(2))) 
     auto store_band = [&](auto inside_tag, int o, unsigned touched) __attribute__((always_inline)) {
         if ((touched & ((1u << NB) - 1)) == 0) {
 #pragma unroll
-            for (int n = 0; n < NX; ++n)
+            for (int n = 0; n < NX; ++n) {
+                // The additions read the last matrix instructions' results from another basic block, which the compiler has been
+                // seen to do without the wait states this needs (see the three-dimensional kernel); eight are enough for these.
+                asm volatile("s_nop 7" : "+v"(acc[NB - 1][n]), "+v"(low[NB - 1][n]));
                 store_quad(inside_tag, x0 + 64 * n + 4 * j, y0 + 4 * o + kg, y1, (acc[NB - 1][n] + low[NB - 1][n]) * a.out_scale);
+            }
         } else {
             note_band(redo, lane, o);
         }
