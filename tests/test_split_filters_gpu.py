@@ -170,6 +170,7 @@ def run3(ssam, vol, filt, boundary, anchor=None):
                                    (17, 17, 2), (9, 9, 9), (5, 1, 1), (1, 6, 1), (4, 13, 2), (8, 8, 16)])
 @pytest.mark.parametrize("boundary", ["clamp", "zero"])
 def test_volumes(ssam, M, N, K, boundary):
+    """Small grids, on whatever kernel they take: many of them stay on the direct one."""
     rng = np.random.default_rng(970 + M + 20 * N + 400 * K)
     filt = rng.uniform(-1.0, 1.0, (K, N, M)).astype(np.float32)
     for i, (D, H, W) in enumerate([(40, 41, 64), (17, 70, 67), (9, 60, 131), (70, 33, 36), (1, 40, 1700)]):
@@ -179,6 +180,25 @@ def test_volumes(ssam, M, N, K, boundary):
         print(f"split {M}x{N}x{K} {boundary} {vol.shape} anchor {anchor} {name}", flush=True)
         err = normalised_error(run3(ssam, vol, filt, boundary, anchor), oracle.conv3d(vol, filt, boundary, anchor), filt, 1.0)
         assert err <= TOL3, (M, N, K, boundary, vol.shape, err)
+
+
+@pytest.mark.parametrize("M,N,K", [
+    (1, 6, 1), (5, 1, 1), (2, 9, 6), (3, 2, 7), (4, 4, 4), (4, 13, 2), (5, 5, 5),                      # one group of eight columns
+    (6, 5, 3), (6, 13, 2), (7, 7, 7), (8, 8, 16), (9, 2, 8), (9, 9, 9),                                # ... and a tail piece
+    (10, 4, 4), (10, 10, 1), (11, 5, 3), (12, 9, 2), (12, 2, 9), (13, 1, 6), (13, 12, 5),              # two groups
+    (14, 3, 5), (14, 11, 6), (15, 6, 4), (16, 9, 3), (16, 5, 1), (17, 1, 8), (17, 17, 2), (17, 17, 17)])   # ... and a tail piece
+def test_volumes_on_the_split_kernel(ssam, M, N, K):
+    """Every kind of instance, filters of one part and of several (more than 7 planes, 4 with two groups; more than 9 rows), on
+    grids large enough that the filter goes to the split kernel wherever it is anchored."""
+    filt = np.random.default_rng(975 + M + 20 * N + 400 * K).uniform(-1.0, 1.0, (K, N, M)).astype(np.float32)
+    H, W = 67, 131
+    vol = wl.uniform_field((max(11, int(5.1e7 / filt.size / (H * W)) + 1), H, W), -1.0, 1.0, 976, np.float32)
+    for i, anchor in enumerate([None, (0, 0, 0), (M - 1, N - 1, K - 1), (M - 1, 0, K // 2)]):
+        boundary = ("clamp", "zero")[(i + M) % 2]
+        assert "split3mx" in ssam.ssam_describe("conv3d", vol.shape, filt, boundary)
+        print(f"split {M}x{N}x{K} {boundary} {vol.shape} anchor {anchor}", flush=True)
+        err = normalised_error(run3(ssam, vol, filt, boundary, anchor), oracle.conv3d(vol, filt, boundary, anchor), filt, 1.0)
+        assert err <= TOL3 + 2 * 2.0 ** -24, (M, N, K, boundary, anchor, err)      # 17x17x17: ten parts
 
 
 @pytest.mark.parametrize("planes", [1, 3, 5, 16])
