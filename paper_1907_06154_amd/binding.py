@@ -109,11 +109,14 @@ def _device_tensor(t, name: str):
 
 def _stream_ptr(stream) -> int:
     """The stream's handle; without one, the calling thread's current stream on its current device (asked for
-    by handle: building a torch.cuda.Stream object takes a microsecond)."""
+    by handle: building a torch.cuda.Stream object takes a microsecond; that way is not part of torch's interface)."""
     if stream is not None:
         return stream.cuda_stream
     import torch
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    handle = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if handle is None:
+        return torch.cuda.current_stream().cuda_stream
+    return handle(torch.cuda.current_device())
 
 
 def _host_coef(coef, code: int) -> np.ndarray:

@@ -27,3 +27,12 @@ def test_refusals_and_statuses():
     assert m.stencil3d(16, 16, 4, 4, 4, np.ones((3, 3, 3)), 1, 1, 0) == 5
     assert m.iterate(16, 1 << 20, 4, 4, 1, f32, 1, 0, -1, 0)[0] == 3
     assert m.scan(16, 1 << 20, -1, 0, 0, 0, 0) == 2
+
+
+def test_current_stream_without_the_private_query(monkeypatch):
+    import types
+    import torch
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=1234))
+    assert b._stream_ptr(None) == 1234
+    assert b._stream_ptr(types.SimpleNamespace(cuda_stream=77)) == 77
