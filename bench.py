@@ -143,7 +143,7 @@ def time_groups(timer, enqueue_group, launches_per_group: int, min_seconds: floa
 
 
 def arithmetic_peak(kname, tag):
-    return SPLIT_PEAK_TFLOPS if kname.endswith("split3mx") else ALU_PEAK_TFLOPS[tag]
+    return SPLIT_PEAK_TFLOPS if kname.split("+")[0].endswith("split3mx") else ALU_PEAK_TFLOPS[tag]
 
 
 def kernel_entry(case, kname, launch_ms, launches, traffic, extra=None):

@@ -60,3 +60,12 @@ def test_every_workload_of_the_generators_can_be_named_on_the_command_line():
             assert c.kind in ("conv2d", "conv3d", "stencil2d", "stencil3d"), c.name
             assert c.coef.ndim == (2 if c.kind == "conv2d" else 3), c.name
             assert len(c.shape) == (2 if c.kind in ("conv2d", "stencil2d") else 3), c.name
+
+
+def test_split_kernels_are_priced_against_the_bf16_peak():
+    """... also where the filter runs in a larger box ("...+embedded"), as the bound beside it says."""
+    import bench
+    for name in ("float_M20N20_b2_v4p4split3mx", "float_r222_b3_split3mx", "float_r222_b3_split3mx+embedded"):
+        assert bench.arithmetic_peak(name, "f32") == bench.SPLIT_PEAK_TFLOPS
+    for name in ("float_M9N9_b2_v4p4f1nt2mx", "float_M7N7_b2_v4p4f1nt2mx+embedded"):
+        assert bench.arithmetic_peak(name, "f32") == bench.ALU_PEAK_TFLOPS["f32"]
