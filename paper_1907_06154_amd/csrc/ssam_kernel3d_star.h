@@ -618,6 +618,18 @@ hipError_t launch3d_star(const Problem3D& pr, const Tuning& tu, Geometry* geo, b
     // 8.6 against 8.9; 33 wide 7.4 against 6.1).
     if constexpr (FALLBACK != static_cast<Launch3DFn>(&launch3d_unavailable)) {
         if (staged && (LH < NW * 2 || (R == 1 && sizeof(T) == 8 && pr.W < 16))) return FALLBACK(pr, tu, geo, dry_run);
+    } else {
+        // The radius-3 box pays for its 343 taps whatever it holds, 72 us (fp64 82) on the smallest grid; without a fallback the
+        // direct kernel takes over, whose time goes with taps and rows of 64 columns: 127 taps on 3x4x33 24 us against 70 staged, on
+        // 40x40x33 33 and 73, 100x100x33 90 and 110, 100x100x65 167 and 112; 175 taps on 40x40x129 72 and 84, 40x40x301 104 and 90;
+        // 343 taps (two launches there) on 3x4x257 61 and 71, 12x12x33 equal, 40x40x5 110 and 74.
+        if (staged) {
+            const T* const c = static_cast<const T*>(pr.c);
+            long taps = 0;
+            for (int i = 0; i < (2 * R + 1) * (2 * R + 1) * (2 * R + 1); ++i) taps += pr.dense || c[i] != T(0);
+            const double work = (double)taps * ceil_div(pr.W, kWave) * kWave * pr.H * pr.D;
+            if (work < (taps > 298 ? 2.5e6 : 8.5e7)) return FALLBACK(pr, tu, geo, dry_run);
+        }
     }
     // Two rows per wave instead of four: twice the blocks on a grid that has fewer than one per unit (96^3 fp32 star r1 6.6 us
     // with four, 6.0 with two; r2 11.1, 8.7), and the staged form's registers let two blocks share a unit (413x300x301 fp32 star

@@ -123,3 +123,20 @@ def test_large_pictures_keep_the_wide_strips():
         assert plan("conv2d", (24000, 24000), filt)[1]["rows_per_wave"] == "64"
     finally:
         ssam.ssam_set_tuning("rows_per_wave", -1)
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+def test_radius_3_stencils_on_small_ragged_grids(dtype):
+    """Faces and edges (127 taps) and boxes inside the radius-3 box: the direct kernel until there is work for the box."""
+    off = np.abs(np.indices((7, 7, 7)) - 3)
+    edges = ((off != 0).sum(axis=0) <= 2).astype(dtype)
+    box = np.ones((7, 5, 5), dtype=dtype)
+    for shape, ring in (((11, 5, 11), False), ((101, 5, 41), False), ((40, 40, 33), False), ((200, 200, 301), True)):
+        for coef in (edges, box):
+            name = route("stencil3d", shape, coef)
+            if ring:
+                assert "ring" in name or "split3mx" in name, (shape, name)
+            else:                                                      # (a box of 175 taps goes to the split kernel from W = 32 on)
+                assert name == "generic_direct" or (coef is box and "split3mx" in name), (shape, name)
+    assert "ring" in route("stencil3d", (40, 40, 9), np.ones((7, 7, 7), dtype=dtype))
+    assert "ring" in route("stencil3d", (11, 5, 12), edges)            # whole 16-byte pieces: the unstaged form, as ever
