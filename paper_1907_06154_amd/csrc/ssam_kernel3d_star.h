@@ -618,6 +618,10 @@ hipError_t launch3d_star(const Problem3D& pr, const Tuning& tu, Geometry* geo, b
     // 8.6 against 8.9; 33 wide 7.4 against 6.1).
     if constexpr (FALLBACK != static_cast<Launch3DFn>(&launch3d_unavailable)) {
         if (staged && (LH < NW * 2 || (R == 1 && sizeof(T) == 8 && pr.W < 16))) return FALLBACK(pr, tu, geo, dry_run);
+        // ... and on grids of a few planes, where a barrier for each of the 2R planes around them is most of the time (1x124x9,
+        // 2x200x9, 3x17x9, 5x300x9, us: star r4 fp32 12.4, 13.3, 13.7, 18 there and 16.6, 16.7, 16.6, 18 staged, fp64 1.13, 1.06, 1.0 and
+        // 0.86 times; 5x5x5 fp32 1.25, 1.05, 0.94, 0.70 times, star r2 fp32 1.13, 1.03, 0.98, 0.76; fp64 staged faster from one plane on)
+        if (staged && LD < R - (sizeof(T) == 8 ? 1 : 0)) return FALLBACK(pr, tu, geo, dry_run);
     } else {
         // The radius-3 box pays for its 343 taps whatever it holds, 72 us (fp64 82) on the smallest grid; without a fallback the
         // direct kernel takes over, whose time goes with taps and rows of 64 columns: 127 taps on 3x4x33 24 us against 70 staged, on

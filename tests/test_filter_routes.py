@@ -140,3 +140,14 @@ def test_radius_3_stencils_on_small_ragged_grids(dtype):
                 assert name == "generic_direct" or (coef is box and "split3mx" in name), (shape, name)
     assert "ring" in route("stencil3d", (40, 40, 9), np.ones((7, 7, 7), dtype=dtype))
     assert "ring" in route("stencil3d", (11, 5, 12), edges)            # whole 16-byte pieces: the unstaged form, as ever
+
+
+@pytest.mark.parametrize("dtype,r,planes", [(np.float32, 4, 4), (np.float64, 4, 3), (np.float32, 2, 2), (np.float64, 2, 1), (np.float32, 1, 1)])
+def test_stars_on_a_few_planes_of_ragged_rows(dtype, r, planes):
+    """The staged form from `planes` planes on; below, the kernels with halo lanes."""
+    coef = np.zeros((2 * r + 1,) * 3, dtype=dtype)
+    coef[r, r, :] = coef[r, :, r] = coef[:, r, r] = 1.0
+    for D in range(1, 6):
+        _, g = plan("stencil3d", (D, 40, 131), coef)
+        assert (g["form"] == "1") == (D >= planes), (D, g)
+        assert (g["halo_lanes"] == "0+0") == (D >= planes), (D, g)
