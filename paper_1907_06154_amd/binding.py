@@ -113,10 +113,10 @@ def _stream_ptr(stream) -> int:
     if stream is not None:
         return stream.cuda_stream
     import torch
-    handle = getattr(torch._C, "_cuda_getCurrentRawStream", None)
-    if handle is None:
+    try:
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    except AttributeError:
         return torch.cuda.current_stream().cuda_stream
-    return handle(torch.cuda.current_device())
 
 
 def _host_coef(coef, code: int) -> np.ndarray:

@@ -32,6 +32,7 @@ import os
 import re
 import subprocess
 import sys
+from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
@@ -48,7 +49,7 @@ def short(name: str) -> str:
 def ours(kernel: str) -> bool:
     """A compute kernel of the library (not its plain copy kernel, not one of torch's)."""
     k = short(kernel)
-    return k.startswith(("ssam2d", "ssam3d", "scan_", "generic_kernel"))
+    return k.startswith(("ssam2d", "ssam3d", "scan_", "generic_kernel", "dense_kernel"))
 
 
 def is_copy(kernel: str) -> bool:
@@ -153,19 +154,20 @@ def sweeps_of(kernel: str) -> int:
 
 def sq(dirs, out_md: str) -> None:
     """VALU utilisation per kernel from one pass of 8 SQ counters per directory."""
-    ctrs = "SQ_WAVE_CYCLES SQ_BUSY_CYCLES SQ_INSTS_MFMA SQ_ACTIVE_INST_VALU SQ_ACTIVE_INST_LDS SQ_INSTS_VALU SQ_INSTS_LDS SQ_WAIT_ANY"
+    ctrs = "SQ_WAVE_CYCLES SQ_BUSY_CYCLES SQ_INSTS_MFMA SQ_ACTIVE_INST_VALU SQ_VALU_MFMA_BUSY_CYCLES SQ_INSTS_VALU SQ_INSTS_LDS SQ_WAIT_ANY"
     out = ["# VALU utilisation of the benchmark kernels (rocprofv3 SQ counters)\n",
            "One MI355X, one counter pass per configuration (8 SQ counters):\n",
-           f"    rocprofv3 --pmc {ctrs} --kernel-trace --output-format csv -d <dir> -o c -- python3 bench.py --workload config<N> "
+           f"    rocprofv3 --pmc {ctrs} --kernel-trace --output-format csv -d <dir> -o c -- python3 bench.py --workload <workload> "
            "--no-cpu-baseline --steps 1 --warmup 0\n",
            "Per dispatch, mean over the dispatches of a kernel.  `VALU instr / point / sweep` = SQ_INSTS_VALU x 64 lanes / (grid "
            "points x sweeps of the launch): what one output costs in lane-instructions, halo lanes and warm-up rows included.  "
            "`VALU busy` = (SQ_ACTIVE_INST_VALU + SQ_INSTS_MFMA) x 4 cycles / (1024 SIMDs x dispatch duration x 2.4 GHz): the "
            "fraction of all VALU issue slots of the chip the kernel used.  `MFMA share` = SQ_INSTS_MFMA / SQ_INSTS_VALU.  "
+           "`matrix busy` = SQ_VALU_MFMA_BUSY_CYCLES / (1024 SIMDs x dispatch duration x 2.4 GHz).  "
            "`waiting` = SQ_WAIT_ANY / SQ_WAVE_CYCLES: share of wave-cycles spent waiting on any counter (memory, LDS).  "
            "Durations are those of the counter run (serialised dispatches), a few per cent above the timed runs.\n",
-           "| run | kernel | dispatches | duration us | sweeps | VALU instr / point / sweep | VALU busy | MFMA share | "
-           "LDS instr / VALU instr | waiting |\n|---|---|---|---|---|---|---|---|---|---|"]
+           "| run | kernel | dispatches | duration us | sweeps | VALU instr / point / sweep | VALU busy | MFMA share | matrix busy | "
+           "LDS instr / VALU instr | waiting |\n|---|---|---|---|---|---|---|---|---|---|---|"]
     for d in dirs:
         bench = json.load(open(d.rstrip("/") + ".json"))
         pts = 1
@@ -182,7 +184,8 @@ def sq(dirs, out_md: str) -> None:
             out.append(f"| {os.path.basename(d.rstrip('/'))} | `{k}` | {len(rows)} | {us:.1f} | {sw} | "
                        f"{m['SQ_INSTS_VALU'] * 64 / pts / sw:.1f} | "
                        f"{(m['SQ_ACTIVE_INST_VALU'] + m['SQ_INSTS_MFMA']) * 4 / (1024 * us * 1e-6 * 2.4e9):.2f} | "
-                       f"{m['SQ_INSTS_MFMA'] / max(m['SQ_INSTS_VALU'], 1):.2f} | {m['SQ_INSTS_LDS'] / max(m['SQ_INSTS_VALU'], 1):.3f} | "
+                       f"{m['SQ_INSTS_MFMA'] / max(m['SQ_INSTS_VALU'], 1):.2f} | "
+                       f"{m['SQ_VALU_MFMA_BUSY_CYCLES'] / (1024 * us * 1e-6 * 2.4e9):.2f} | {m['SQ_INSTS_LDS'] / max(m['SQ_INSTS_VALU'], 1):.3f} | "
                        f"{m['SQ_WAIT_ANY'] / max(m['SQ_WAVE_CYCLES'], 1):.2f} |")
     open(out_md, "w").write("\n".join(out) + "\n")
     print("\n".join(out))
@@ -193,7 +196,7 @@ def lds(dirs, out_md: str) -> None:
     ctrs = "SQ_LDS_BANK_CONFLICT SQ_LDS_IDX_ACTIVE SQ_LDS_ADDR_CONFLICT SQ_INSTS_LDS SQ_ACTIVE_INST_LDS SQ_WAVE_CYCLES SQ_BUSY_CYCLES SQ_WAIT_INST_LDS"
     out = ["# LDS bank conflicts of the kernels that use LDS (rocprofv3 SQ counters)\n",
            "One MI355X, one counter pass per configuration:\n",
-           f"    rocprofv3 --pmc {ctrs} --kernel-trace --output-format csv -d <dir> -o c -- python3 bench.py --workload config<N> "
+           f"    rocprofv3 --pmc {ctrs} --kernel-trace --output-format csv -d <dir> -o c -- python3 bench.py --workload <workload> "
            "--no-cpu-baseline --steps 1 --warmup 0\n",
            "Per dispatch, mean over the dispatches of a kernel.  `conflict share` = SQ_LDS_BANK_CONFLICT / SQ_LDS_IDX_ACTIVE: "
            "cycles the LDS spent replaying bank conflicts over the cycles it was busy with indexed accesses.  `LDS busy` = "
@@ -222,9 +225,15 @@ def resources(out_md: str, only_default: bool = True) -> None:
     from . import build
     flags = [f for f in build.FLAGS if f not in ("-fPIC",)]
     rows = []
-    for src in sorted(glob.glob(os.path.join(build.CSRC, "*.hip"))):
-        res = subprocess.run(["hipcc", *flags, "--cuda-device-only", "-c", src, "-o", "/dev/null",
-                              "-Rpass-analysis=kernel-resource-usage"], capture_output=True, text=True)
+
+    def report(src):
+        return subprocess.run(["hipcc", *flags, "--cuda-device-only", "-c", src, "-o", "/dev/null",
+                               "-Rpass-analysis=kernel-resource-usage"], capture_output=True, text=True)
+
+    sources = sorted(glob.glob(os.path.join(build.CSRC, "*.hip")))
+    with ThreadPoolExecutor(max_workers=8) as pool:
+        reports = list(pool.map(report, sources))
+    for src, res in zip(sources, reports):
         if res.returncode != 0:
             raise SystemExit(res.stderr)
         cur = None
@@ -259,7 +268,7 @@ def resources(out_md: str, only_default: bool = True) -> None:
            "reserves a private segment (bytes per lane; scratch loads and stores in their code): "
            + (", ".join(f"`{r['kernel']}` ({r.get('ScratchSize')}; {r.get('scratch_instructions', '?')})" for r in spilled) or "none")
            + ".  A reserved segment without scratch instructions is never touched: its slots belonged to scalar-register "
-           "spills that ended up in vector-register lanes.\n",
+           "spills that ended up in vector-register lanes.  With scratch instructions, vector registers are spilled.\n",
            "| translation unit | kernel | VGPRs | AGPRs | SGPRs | LDS bytes / block | scratch bytes / lane | waves / SIMD |\n|---|---|---|---|---|---|---|---|"]
     for r in rows:
         out.append(f"| {r['file']} | `{r['kernel']}` | {r.get('VGPRs', '')} | {r.get('AGPRs', '')} | {r.get('TotalSGPRs', '')} | "
@@ -312,8 +321,9 @@ def sweep(default_json: str, vector_json: str, out_md: str) -> None:
            f"Whole-step throughput {a['value']:.1f} GStencil/s, {a['ms_per_step']:.2f} ms per step (variant 5: {v['value']:.1f}, "
            f"{v['ms_per_step']:.2f} ms); plain grid-stride copy on the same buffers {a['plain_copy_GBps']:.0f} GB/s.\n",
            "Fractions: algorithmic GB/s of 8 TB/s; TFLOP/s of 157.3 (the published fp32 vector peak, which assumes packed FMA and "
-           "equals the fp32 matrix peak; the non-packed vector rate reachable here is 78.6).\n",
-           "| case | kernel instance | launch us | GStencil/s | algorithmic GB/s | of 8 TB/s | TFLOP/s | of 157.3 | bound | "
+           "equals the fp32 matrix peak; the non-packed vector rate reachable here is 78.6), the `...split3mx` instances' of 419 (a "
+           "sixth of the dense bf16 matrix peak: six products per multiplication).\n",
+           "| case | kernel instance | launch us | GStencil/s | algorithmic GB/s | of 8 TB/s | TFLOP/s | of peak | bound | "
            "vector-unit instance | launch us | GStencil/s | of 78.6 TFLOP/s |\n|---|---|---|---|---|---|---|---|---|---|---|---|---|"]
     kv = {k["case"]: k for k in v["kernels"]}
     for k in a["kernels"]:

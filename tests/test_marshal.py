@@ -33,6 +33,7 @@ def test_current_stream_without_the_private_query(monkeypatch):
     import types
     import torch
     monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 0)
     monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=1234))
     assert b._stream_ptr(None) == 1234
     assert b._stream_ptr(types.SimpleNamespace(cuda_stream=77)) == 77
