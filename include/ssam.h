@@ -86,9 +86,10 @@ int ssam_stencil2d(const void *d_in, void *d_out, int W, int H,
  *     out[z][y][x] = sum  h_coef[((dz+rz)*(2ry+1) + (dy+ry))*(2rx+1) + (dx+rx)] * IN(x+dx, y+dy, z+dz)
  * with the same zero-means-no-tap rule; Above = dz -1, Below = dz +1.
  * Shapes with a compiled instance (or that fit zero-padded inside one: stars up to radius 4, boxes
- * up to radius 3) run on the register-cache kernels, larger boxes on kernels for dense filters; any
+ * up to radius 3; fp32 boxes of radius 2 and 3 on the kernel for dense filters) run on those; any
  * other, up to SSAM_MAX_RADIUS per axis, runs on a direct one-point-per-thread kernel (correct, not
- * fast) whose taps travel in the launch arguments, in as many launches on hip_stream as it needs. */
+ * fast; fp64 boxes without zeros on a register-tiled one where that is faster) whose taps travel in
+ * the launch arguments, in as many launches on hip_stream as it needs. */
 int ssam_stencil3d(const void *d_in, void *d_out, int W, int H, int D,
                    const void *h_coef, int rx, int ry, int rz,
                    int boundary, int dtype, void *hip_stream);
@@ -99,8 +100,10 @@ int ssam_stencil3d(const void *d_in, void *d_out, int W, int H, int D,
  * M, N, K are the filter's extents along x, y, z, each 1 .. SSAM_MAX_FILTER3D, even sizes included;
  * (ax, ay, az) is the filter element placed on the output point, -1 for the default M/2, N/2, K/2.
  * Every element of the filter is a tap (a zero multiplies, it is not skipped).  3x3x3 and what fits
- * in it run on the register-cache kernels; larger fp32 filters on the bf16 matrix cores, every value split into three parts
- * (as accurate as fp32 arithmetic), fp64 ones as the smallest cube that holds them or register-tiled.  d_in and d_out must not overlap. */
+ * in it run on the register-cache kernels; larger fp32 filters on the bf16 matrix cores, every value
+ * split into three parts (no further from 64-bit sums than fp32 multiply-adds, to which filters of fewer
+ * than 2.5 taps per plane are left); fp64 ones as the smallest cube that holds them, register-tiled, or
+ * one point per thread, whichever is faster.  d_in and d_out must not overlap. */
 int ssam_conv3d(const void *d_in, void *d_out, int W, int H, int D,
                 const void *h_filter, int M, int N, int K, int ax, int ay, int az,
                 int boundary, int dtype, void *hip_stream);
