@@ -626,13 +626,13 @@ hipError_t launch3d_star(const Problem3D& pr, const Tuning& tu, Geometry* geo, b
         // The radius-3 box pays for its 343 taps whatever it holds, 72 us (fp64 82) on the smallest grid; without a fallback the
         // direct kernel takes over, whose time goes with taps and rows of 64 columns: 127 taps on 3x4x33 24 us against 70 staged, on
         // 40x40x33 33 and 73, 100x100x33 90 and 110, 100x100x65 167 and 112; 175 taps on 40x40x129 72 and 84, 40x40x301 104 and 90;
-        // 343 taps (two launches there) on 3x4x257 61 and 71, 12x12x33 equal, 40x40x5 110 and 74.
+        // 343 taps (two launches there) on 3x4x257 61 and 71, 12x12x33 equal, fp64 26x15x3 75 and 86, 40x40x5 110 and 74.
         if (staged) {
             const T* const c = static_cast<const T*>(pr.c);
             long taps = 0;
             for (int i = 0; i < (2 * R + 1) * (2 * R + 1) * (2 * R + 1); ++i) taps += pr.dense || c[i] != T(0);
             const double work = (double)taps * ceil_div(pr.W, kWave) * kWave * pr.H * pr.D;
-            if (work < (taps > 298 ? 2.5e6 : 8.5e7)) return FALLBACK(pr, tu, geo, dry_run);
+            if (work < (taps > 298 ? 1.6e7 : 1.2e8)) return FALLBACK(pr, tu, geo, dry_run);
         }
     }
     // Two rows per wave instead of four: twice the blocks on a grid that has fewer than one per unit (96^3 fp32 star r1 6.6 us
