@@ -35,7 +35,8 @@ struct ArgsSplit3D {
     float w[kSplit3dTaps];
 };
 
-// bands of four output rows per wave: what the registers leave beside K output planes in flight
+// bands of four output rows per wave: what the registers leave beside K output planes in flight (three planes, three bands and two
+// column groups spill six to ten of them)
 constexpr int split3d_bands(int K, int NB) { return K <= 3 ? 4 : NB <= 2 ? (K <= 5 ? 4 : 3) : (K <= 5 ? 3 : 2); }
 
 template <int K, int NB, int NG, bool TAIL>
