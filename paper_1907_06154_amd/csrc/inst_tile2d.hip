@@ -1,0 +1,166 @@
+// Small 2D grids, many sweeps a launch (ssam_kernel2d_tile.h): tile plan and launch.
+#include <cmath>
+
+#include "ssam_kernel2d_tile.h"
+
+namespace ssam {
+template <> const Tile2DKernel* tile2d_kernels<float, true>(int);
+template <> const Tile2DKernel* tile2d_kernels<float, false>(int);
+template <> const Tile2DKernel* tile2d_kernels<double, true>(int);
+template <> const Tile2DKernel* tile2d_kernels<double, false>(int);
+
+namespace {
+
+// More than 64 KB of LDS per workgroup is asked for once per kernel and device.
+hipError_t allow_lds(const void* kernel, int index)
+{
+    static std::atomic<unsigned long long> done[kTile2DIndexes];   // by instance: bit per device
+    int dev = 0;
+    if (hipError_t e = hipGetDevice(&dev)) return e;
+    const unsigned long long bit = 1ull << (dev & 63);
+    if (done[index].load(std::memory_order_relaxed) & bit) return hipSuccess;
+    const hipError_t e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 160 << 10);
+    if (e == hipSuccess) done[index].fetch_or(bit, std::memory_order_relaxed);
+    return e;
+}
+
+struct TilePlan {
+    const Tile2DKernel* k = nullptr;
+    int waves = 0, sweeps = 0, tiles_x = 0, tiles_y = 0;
+};
+
+int tiles_along(int extent, int tile, int step) { return ceil_div(extent - tile, step) + 1; }
+
+// The plan of least expected time for all of max_sweeps sweeps.  The expectation is fitted to 3400 measured launches (256^2 ..
+// 4096^2, both types, stars of radius 1, 2, 4, 6, boxes of radius 1, 2, 4, one to sixteen sweeps; 12 % off in the quadratic mean, and
+// the plan it picks 1.5 % slower than the best in the mean, 22 % at worst).  A launch costs 3.4 us and never less than 5; a sweep
+// of a compute unit's blocks their instructions, four cycles each, or 0.16 us of latency, whichever dominates; a block's loads and
+// stores 0.033 us per wave and four-byte column.
+TilePlan plan_tiles(int W, int H, int R, bool star, int elem, const Tile2DKernel* list, int max_sweeps)
+{
+    TilePlan best;
+    double best_us = 1e30;
+    const int taps = star ? 4 * R + 1 : (2 * R + 1) * (2 * R + 1), pub = 2 * R < kTileRows ? 2 * R : kTileRows;
+    for (const Tile2DKernel* k = list; k->kernel; ++k) {
+        const int TW = kWave * k->V;
+        if (W < TW) continue;
+        const double work = kTileRows * k->V * taps + 0.7 * (star ? kTileRows : kTileRows + 2 * R) * 2 * R * (elem / 4) + 4;
+        for (int waves = kTileWaves; waves >= 4; waves -= 4) {
+            const int TH = waves * kTileRows;
+            if (H < TH) continue;
+            const int fit = min(2 * kTileWaves / waves, (160 << 10) / (2 * waves * pub * kWave * k->V * elem));   // blocks a unit holds at once
+            double last = 1e30;
+            for (int launches = 1; launches <= max_sweeps; ++launches) {
+                const int sweeps = ceil_div(max_sweeps, launches);
+                const int step_x = TW - 2 * sweeps * R, step_y = TH - 2 * sweeps * R;
+                if (step_x < 1 || step_y < 1) continue;
+                const int tx = tiles_along(W, TW, step_x), ty = tiles_along(H, TH, step_y);
+                if ((long)tx * ty > 1L << 20) continue;
+                const int share = ceil_div(tx * ty, kCUs);        // blocks of the busiest unit
+                const double issue = share * waves * work / 2200, latency = 0.16 * ceil_div(share, fit < 1 ? 1 : fit);
+                const double one = 3.4 + sweeps * std::sqrt(issue * issue + latency * latency) + 0.033 * share * waves * k->V * (elem / 4);
+                const double us = launches * (one > 5.0 ? one : 5.0);
+                if (us < best_us) {
+                    best_us = us;
+                    best.k = k;
+                    best.waves = waves;
+                    best.sweeps = sweeps;
+                    best.tiles_x = tx;
+                    best.tiles_y = ty;
+                }
+                if (us > 1.5 * last) break;
+                if (us < last) last = us;
+            }
+        }
+    }
+    return best;
+}
+
+// The largest grid, in points, that a shape's sweeps run on here instead of in the marching kernels (several sweeps a launch, or
+// one).  The halo costs more the wider the stencil, and the marching kernels' latency less the larger the grid.  Ratio of the
+// times, this kernel to those, over 2, 4, 10 and 20 sweeps and both boundary rules:
+//   radius 1: 0.17 .. 0.8 up to 2048^2, 4096^2 0.58 .. 0.92, 8192^2 1.25 (fp64 box)
+//   fp32: box r2 0.29 .. 0.92 up to 2048x1500, 2048^2 0.81 .. 1.19; star r2 0.27 .. 0.76 up to 1500x1300, 2048x1500 0.89 .. 1.1;
+//     star r3 0.18 .. 0.94 up to 2048^2, 4096^2 1.02 .. 1.1; star r4 0.3 .. 0.79 up to 1500x1300, 2048x1500 0.99 .. 1.18; star r6
+//     0.2 .. 0.62 up to 1500x1300, 2048x1500 1.03.  Boxes from radius 3 on: single sweeps on the split kernel, with less error.
+//   fp64: box r2 0.49 .. 0.75 up to 1023x1025, 1500x1300 0.9 .. 1.04; box r3, which has single sweeps only, 0.45 .. 0.89 up to
+//     2048^2; box r4 0.8 .. 0.95 up to 300x512, 512^2 1.01 .. 1.07; star r2 0.42 .. 0.88 up to 1023x1025, 1500x1300 0.84 .. 1.07;
+//     star r3 0.36 .. 0.86 up to 2048x1500, 2048^2 0.79 .. 1.07; star r4 0.38 .. 0.76 up to 1023x1025, 1500x1300 0.86 .. 0.98,
+//     2048^2 1.07; star r6 0.28 .. 0.93 up to 1023x1025, 1500x1300 1.2
+long most_points(bool f32, bool star, int R)
+{
+    if (R == 1) return 1L << 24;
+    if (f32) return star && R == 3 ? 1L << 22 : star ? 2000000 : 3200000;
+    if (star) return R == 3 ? 3100000 : 1100000;
+    return R == 2 ? 1100000 : R == 3 ? 1L << 22 : 160000;
+}
+
+template <typename T, class Mask>
+hipError_t launch_tile(const Problem2D& pr, const TilePlan& plan, size_t lds)
+{
+    ArgsTile2D<T, Mask::kNW> a;
+    a.in = static_cast<const T*>(pr.in);
+    a.out = static_cast<T*>(pr.out);
+    a.W = pr.W;
+    a.H = pr.H;
+    a.boundary = pr.boundary;
+    a.sweeps = plan.sweeps;
+    a.tiles_x = plan.tiles_x;
+    a.step_x = kWave * plan.k->V - 2 * plan.sweeps * Mask::kAX;
+    a.step_y = plan.waves * kTileRows - 2 * plan.sweeps * Mask::kAX;
+    const T* w = static_cast<const T*>(pr.w);
+    for (int n = 0; n < Mask::kN; ++n)
+        for (int m = 0; m < Mask::kM; ++m)
+            if (Mask::tap(n, m)) a.w[Mask::widx(n, m)] = w[n * Mask::kM + m];
+    void* args[] = {&a};
+    return hipLaunchKernel(plan.k->kernel, dim3(plan.tiles_x * plan.tiles_y), dim3(plan.waves * kWave), args, lds, pr.stream);
+}
+
+template <typename T, int BUDGET>
+hipError_t launch_tile(const Problem2D& pr, const TilePlan& plan, size_t lds)
+{
+    switch (pr.ax) {
+#define SSAM_R(R) case R: return launch_tile<T, TapMask<2 * R + 1, 2 * R + 1, R, R, BUDGET>>(pr, plan, lds);
+        SSAM_R(1) SSAM_R(2) SSAM_R(3) SSAM_R(4) SSAM_R(5) SSAM_R(6)
+#undef SSAM_R
+    }
+    return hipErrorNotSupported;
+}
+
+}  // namespace
+
+int launch2d_tile(const Problem2D& pr, bool star, int max_sweeps, Geometry* geo, bool dry_run, hipError_t* err)
+{
+    const bool f32 = pr.dtype == SSAM_F32;
+    if (pr.M != pr.N || pr.ax != pr.ay || pr.M != 2 * pr.ax + 1 || max_sweeps < 2) return 0;
+    const Tile2DKernel* list = star ? (f32 ? tile2d_kernels<float, true>(pr.ax) : tile2d_kernels<double, true>(pr.ax))
+                                    : (f32 ? tile2d_kernels<float, false>(pr.ax) : tile2d_kernels<double, false>(pr.ax));
+    if (!list || (long)pr.W * pr.H > most_points(f32, star, pr.ax)) return 0;
+    const int elem = f32 ? 4 : 8, R = pr.ax;
+    const TilePlan plan = plan_tiles(pr.W, pr.H, R, star, elem, list, max_sweeps);
+    if (!plan.k) return 0;
+    const size_t row = (size_t)kWave * plan.k->V * elem;
+    const size_t lds = (2 * plan.waves * (size_t)(2 * R < kTileRows ? 2 * R : kTileRows) + 1) * row;
+    if (geo) {
+        Geometry g;
+        g.V = plan.k->V;
+        g.P = kTileRows;
+        g.valid_lanes = kWave;
+        g.strips_x = plan.tiles_x;
+        g.tiles_y = plan.tiles_y;
+        g.rows_per_wave = kTileRows;
+        g.tiles = (long)plan.tiles_x * plan.tiles_y * plan.waves;
+        g.blocks = plan.tiles_x * plan.tiles_y;
+        g.lds = (int)lds;
+        *geo = g;
+    }
+    *err = hipSuccess;
+    if (dry_run) return plan.sweeps;
+    *err = allow_lds(plan.k->kernel, plan.k->index);
+    if (*err == hipSuccess)
+        *err = star ? (f32 ? launch_tile<float, 1>(pr, plan, lds) : launch_tile<double, 1>(pr, plan, lds))
+                    : (f32 ? launch_tile<float, 2>(pr, plan, lds) : launch_tile<double, 2>(pr, plan, lds));
+    return plan.sweeps;
+}
+
+}  // namespace ssam

@@ -9,6 +9,7 @@
 #include "ssam_device.h"
 #include "ssam_host.h"
 #include "ssam_kernel2d_split.h"
+#include "ssam_kernel2d_tile.h"
 #include "ssam_kernel3d_split.h"
 #include "ssam_kernel_dense.h"
 
@@ -369,7 +370,6 @@ int run_fused(const Problem3D& p, int max_sweeps, Geometry* geo, bool dry, std::
     const Tuning tu = current_tuning();
     if (tu.fuse_sweeps == 0 || tu.fuse_sweeps == 1 || tu.force_generic > 0) return 0;
     if (tu.fuse_sweeps > 1 && tu.fuse_sweeps < max_sweeps) max_sweeps = tu.fuse_sweeps;
-    if (max_sweeps > kMaxFusedSweeps) max_sweeps = kMaxFusedSweeps;
     const int v = tu.variant > 0 ? tu.variant : 0;
     const bool flat = p.D == 1 && p.rz == 0;
     if (!flat && tu.march_axis == 1) return 0;   // 3D: z march only
@@ -381,12 +381,25 @@ int run_fused(const Problem3D& p, int max_sweeps, Geometry* geo, bool dry, std::
     // the tightest tap shape any multi-sweep instance offers for this stencil: a deeper instance of a
     // wider shape (a box standing in for a star) is not taken over a shallower one of the exact shape
     int shape_budget = 0;
+    // small grids: the kernel that keeps whole tiles in registers (the tile overrides and variants are the marching kernels')
+    if (flat && p.rx == p.ry && tu.rows_per_wave <= 0 && tu.valid_lanes <= 0 && tu.variant < 0) {
+        const int budget = p.dtype == SSAM_F32 ? tap_budget<float>((const float*)p.c, q.M, q.N, 1, q.ax, q.ay, 0)
+                                               : tap_budget<double>((const double*)p.c, q.M, q.N, 1, q.ax, q.ay, 0);
+        hipError_t e = hipSuccess;
+        if (const int sweeps = launch2d_tile(q, budget <= 1, max_sweeps, geo, dry, &e)) {
+            if (name)
+                *name = std::string(p.dtype == SSAM_F32 ? "float" : "double") + "_R" + std::to_string(p.rx) + (budget <= 1 ? "_b1" : "_b2") +
+                        "_tile_fused" + std::to_string(sweeps);
+            *rc = status_of(e);
+            return sweeps;
+        }
+    }
     if (flat) {
         const Instance2D* tight = p.dtype == SSAM_F32 ? pick2d<float>(q, true, 0, 0, true) : pick2d<double>(q, true, 0, 0, true);
         if (!tight) return 0;
         shape_budget = tight->budget;
     }
-    for (int sweeps = max_sweeps; sweeps >= 2; --sweeps) {
+    for (int sweeps = max_sweeps < kMaxFusedSweeps ? max_sweeps : kMaxFusedSweeps; sweeps >= 2; --sweeps) {
         if (sweeps == 2 && small) break;
         hipError_t e;
         if (flat) {

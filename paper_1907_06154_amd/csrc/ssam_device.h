@@ -56,6 +56,33 @@ __device__ __forceinline__ double shift_down(double v)
     return __builtin_bit_cast(double, h);
 }
 
+// The same shifts with a value for the lane that has no source: `edge` there, else the value of the lane below / above (without
+// bound_ctrl such a lane's destination keeps what it held).
+__device__ __forceinline__ int shift_in_up(int v, int edge) { return __builtin_amdgcn_update_dpp(edge, v, 0x138, 0xf, 0xf, false); }
+__device__ __forceinline__ int shift_in_down(int v, int edge) { return __builtin_amdgcn_update_dpp(edge, v, 0x130, 0xf, 0xf, false); }
+__device__ __forceinline__ float shift_in_up(float v, float edge)
+{
+    return __builtin_bit_cast(float, shift_in_up(__builtin_bit_cast(int, v), __builtin_bit_cast(int, edge)));
+}
+__device__ __forceinline__ float shift_in_down(float v, float edge)
+{
+    return __builtin_bit_cast(float, shift_in_down(__builtin_bit_cast(int, v), __builtin_bit_cast(int, edge)));
+}
+__device__ __forceinline__ double shift_in_up(double v, double edge)
+{
+    Halves a = __builtin_bit_cast(Halves, v), e = __builtin_bit_cast(Halves, edge);
+    a.lo = shift_in_up(a.lo, e.lo);
+    a.hi = shift_in_up(a.hi, e.hi);
+    return __builtin_bit_cast(double, a);
+}
+__device__ __forceinline__ double shift_in_down(double v, double edge)
+{
+    Halves a = __builtin_bit_cast(Halves, v), e = __builtin_bit_cast(Halves, edge);
+    a.lo = shift_in_down(a.lo, e.lo);
+    a.hi = shift_in_down(a.hi, e.hi);
+    return __builtin_bit_cast(double, a);
+}
+
 __device__ __forceinline__ float fma_t(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 __device__ __forceinline__ double fma_t(double a, double b, double c) { return __builtin_fma(a, b, c); }
 
@@ -141,6 +168,7 @@ __device__ __forceinline__ void store_vec(T* __restrict__ p, const T (&src)[V])
 // so rows that are not whole vectors need no access by element (4003x3001 fp32, 5x5: 38.4 us by element, 24.3 like this).
 template <typename T, int V> struct ElemVecOf;
 template <> struct ElemVecOf<float, 4> { typedef float type __attribute__((ext_vector_type(4), aligned(4))); };
+template <> struct ElemVecOf<float, 2> { typedef float type __attribute__((ext_vector_type(2), aligned(4))); };
 template <> struct ElemVecOf<double, 2> { typedef double type __attribute__((ext_vector_type(2), aligned(8))); };
 
 template <typename T, int V, bool STREAM>

@@ -44,32 +44,6 @@ struct Piece16 {
     typedef typename VecOf<T, V>::type type;
 };
 
-// old where the lane has no source, else the value of the lane below / above (see the file header)
-__device__ __forceinline__ int shift_in_up(int v, int edge) { return __builtin_amdgcn_update_dpp(edge, v, 0x138, 0xf, 0xf, false); }
-__device__ __forceinline__ int shift_in_down(int v, int edge) { return __builtin_amdgcn_update_dpp(edge, v, 0x130, 0xf, 0xf, false); }
-__device__ __forceinline__ float shift_in_up(float v, float edge)
-{
-    return __builtin_bit_cast(float, shift_in_up(__builtin_bit_cast(int, v), __builtin_bit_cast(int, edge)));
-}
-__device__ __forceinline__ float shift_in_down(float v, float edge)
-{
-    return __builtin_bit_cast(float, shift_in_down(__builtin_bit_cast(int, v), __builtin_bit_cast(int, edge)));
-}
-__device__ __forceinline__ double shift_in_up(double v, double edge)
-{
-    Halves a = __builtin_bit_cast(Halves, v), e = __builtin_bit_cast(Halves, edge);
-    a.lo = shift_in_up(a.lo, e.lo);
-    a.hi = shift_in_up(a.hi, e.hi);
-    return __builtin_bit_cast(double, a);
-}
-__device__ __forceinline__ double shift_in_down(double v, double edge)
-{
-    Halves a = __builtin_bit_cast(Halves, v), e = __builtin_bit_cast(Halves, edge);
-    a.lo = shift_in_down(a.lo, e.lo);
-    a.hi = shift_in_down(a.hi, e.hi);
-    return __builtin_bit_cast(double, a);
-}
-
 // Waits until at most n of this wave's vector-memory requests are outstanding and every LDS
 // access of the wave is done, then joins the block's barrier.  One statement, so that nothing is
 // scheduled in between, and a compiler-level memory barrier.  (The fence of __syncthreads would

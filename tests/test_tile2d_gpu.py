@@ -1,0 +1,77 @@
+"""Small 2D grids, many sweeps a launch on tiles held in registers: grids of exactly one tile, one point more, and tiles moved back
+from the grid's end, in every vector width; buffers aligned to the element only; against the CPU oracle."""
+import re
+
+import numpy as np
+import pytest
+
+import oracle
+import workloads as wl
+from parity_util import assert_parity
+
+torch = pytest.importorskip("torch")
+
+SHAPES = [("star", 1), ("star", 2), ("star", 5), ("box", 1), ("box", 2), ("box", 4)]
+GRIDS = [(16, 64), (17, 65), (64, 128), (65, 129), (64, 256), (67, 257), (131, 449), (300, 190)]
+
+
+def coefficients(kind, r, dtype):
+    return wl.seeded_coefficients(wl.mask_box(r, r) if kind == "box" else wl.mask_star(r, r), 70 + r, dtype)[0]
+
+
+def test_plans():
+    """Which grids the kernel takes, and that the plans of the sweeps that remain add up."""
+    import paper_1907_06154_amd as ssam
+
+    def name(shape, coef, remaining):
+        return ssam.ssam_describe("iterate2d", shape, coef, "zero", remaining=remaining).split()[0]
+
+    star, box3 = coefficients("star", 1, np.float32), coefficients("box", 3, np.float32)
+    assert "_tile_" in name((300, 400), star, 10) and "_tile_" not in name((8192, 8192), star, 10)
+    assert "_tile_" not in name((300, 63), star, 10) and "_tile_" not in name((15, 300), star, 10)   # narrower than a wave, fewer rows than four waves
+    assert "_tile_" not in name((300, 400), box3, 10)        # single sweeps on the split kernel, with less error
+    for shape in GRIDS + [(1023, 1025), (2048, 64)]:
+        left = 23
+        while left:
+            done = int((re.search(r"_fused(\d+)$", name(shape, star, left)) or [0, 1])[1])
+            assert 1 <= done <= left
+            left -= done
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("kind,r", SHAPES)
+def test_matches_oracle(dtype, kind, r):
+    import paper_1907_06154_amd as ssam
+    coef = coefficients(kind, r, dtype)
+    for shape in GRIDS:
+        fld = wl.uniform_field(shape, -1.0, 1.0, 700 + shape[1], dtype)
+        n = fld.size
+        for boundary in ("zero", "clamp"):
+            for steps in (2, 3, 7, 20):
+                print(f"tile {np.dtype(dtype).name} {kind} r{r} {shape} {boundary} steps {steps}", flush=True)
+                buf = torch.full((2, n + 8), float("nan"), dtype=torch.from_numpy(fld).dtype, device="cuda")
+                a, b = buf[0][1:n + 1].view(shape), buf[1][3:n + 3].view(shape)     # not aligned to a vector
+                a.copy_(torch.from_numpy(fld))
+                got = ssam.ssam_stencil_iterate(a, b, coef, steps, boundary)
+                assert_parity(got.cpu().numpy(), oracle.iterate(fld, coef, steps, boundary), coef, 1.0,
+                              f"{kind} r{r} {shape} {boundary} steps {steps}")
+                guard = torch.cat([buf[0][:1], buf[0][n + 1:], buf[1][:3], buf[1][n + 3:]])
+                assert torch.isnan(guard).all()
+
+
+@pytest.mark.gpu
+def test_zero_padding_keeps_infinities_apart():
+    """An infinity reaches the points the sweeps carry it to and no others, at the grid's edge and beside a tile's rim."""
+    import paper_1907_06154_amd as ssam
+    coef = coefficients("star", 1, np.float32)
+    fld = np.zeros((140, 300), dtype=np.float32)
+    for y, x in ((0, 0), (70, 150), (139, 299)):
+        fld[y, x] = np.inf
+    a = torch.from_numpy(fld).cuda()
+    got = ssam.ssam_stencil_iterate(a, torch.empty_like(a), coef, 6, "zero").cpu().numpy()
+    ys, xs = np.mgrid[0:140, 0:300]
+    near = np.zeros(fld.shape, dtype=bool)
+    for y, x in ((0, 0), (70, 150), (139, 299)):
+        near |= np.abs(ys - y) + np.abs(xs - x) <= 6
+    assert np.array_equal(~np.isfinite(got), near) and not got[~near].any()
