@@ -157,8 +157,8 @@ int ssam_describe(int kind, int W, int H, int D, const void *h_coef, int a, int 
  * returns without waiting and without allocating; no memset is enqueued, so it can be captured.
  * Schedules, chosen by size:
  *   - one workgroup, one launch (up to 128 KiB; no workspace);
- *   - three launches (below 128 MiB, and always in place beyond 128 KiB): the array is cut into contiguous
- *     segments, one per wave; segment sums, their exclusive prefixes, the scan of every segment
+ *   - two launches (below 128 MiB, and always in place beyond 128 KiB): the array is cut into contiguous
+ *     segments, one per wave; segment sums, then the scan of every segment from the sums before it
  *     (2 reads + 1 write per element);
  *   - one pass (from 128 MiB, out of place, up to 2^30 fp32 / 2^29 fp64 elements): every wave
  *     keeps a segment in registers, publishes its sum in the workspace and combines the sums of

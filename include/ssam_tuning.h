@@ -26,7 +26,7 @@ extern "C" {
  * "embed_waste" (a 2D filter shape without a compiled instance runs inside the smallest compiled
  * square box that holds it, zero-padded; a value n >= 0 allows that only while the box has at most
  * n times its taps, 0 = never: such shapes then use the direct one-point-per-thread kernel),
- * "scan_segments" (ssam_scan, three-launch schedule: upper limit of segments, 1 .. 4096),
+ * "scan_segments" (ssam_scan, two-launch schedule: upper limit of segments, 1 .. 4096),
  * "scan_order" (0 = its last launch takes the segments first to last), "scan_chained" (0 = never
  * the one-pass schedule, 1 = for every out-of-place array it can hold; built-in: from 128 MiB),
  * "scan_spin_limit" (polls a waiting wave of the one-pass schedule makes before it gives up, at

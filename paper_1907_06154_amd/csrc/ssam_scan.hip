@@ -6,13 +6,15 @@
 //
 // Two schedules share the wave-level code.
 //
-// Three launches (any size, also in place).  The array is cut into at most kScanMaxSegments (4096)
+// Two launches (any size, also in place).  The array is cut into at most kScanMaxSegments (4096)
 // contiguous segments, one per wave:
 //   1. scan_reduce   -- every wave sums its segment                 (reads n elements)
-//   2. scan_offsets  -- one workgroup turns the segment sums into exclusive prefixes
-//   3. scan_segments -- every wave scans its segment, starting from its prefix
+//   2. scan_segments -- every block adds up the segment sums before its own (at most 32 KB, from the
+//                       L2, while its first elements arrive) and scans its segments from there
 //                                                                   (reads n, writes n elements)
-// No launch waits for another wave.
+// No launch waits for another wave.  What bounds arrays below some ten megabytes is the launches: with
+// a launch of one workgroup in between that made the prefixes of the sums, 1000003 doubles took 10.6 us
+// instead of 8.9, 443972 floats 10.7 instead of 7.2.  The sums are added in the order that launch had.
 //
 // One pass (large arrays, out of place): every wave keeps a segment of 32 wave-rounds (32 KiB)
 // in registers, publishes the segment's sum, obtains the sum of everything before it from what
@@ -55,9 +57,10 @@ namespace {
 
 constexpr int kScanMaxSegments = 4096;   // upper limit of waves per launch = doubles in the workspace
 constexpr int kScanRounds = 4;           // wave-rounds in flight per wave (loads issued together)
-constexpr long long kOneGroupBytes = 128 << 10;  // arrays up to this size: one workgroup, one launch (8 instead of 12.5 us)
-constexpr int kOffsetsThreads = 1024;    // the one workgroup of launch 2 ...
-constexpr int kOffsetsEach = kScanMaxSegments / kOffsetsThreads;   // ... and the sums one of its threads owns
+constexpr long long kOneGroupBytes = 128 << 10;  // arrays up to this size: one workgroup, one launch (5.4 us at the limit, two launches 7.3; at 190 KB 7.5 .. 9.5 and 7.3)
+constexpr int kGroupThreads = 1024;      // the one workgroup of scan_one_group
+constexpr int kSumRuns = 16;             // launch 2 adds up the segment sums in 16 runs of 64 lanes ...
+constexpr int kSumsEach = kScanMaxSegments / (kSumRuns * kWave);     // ... of at most so many sums
 
 // One-pass schedule.
 // Wave-rounds a wave holds in registers: with 16-byte accesses 32 KiB per segment for fp32 and
@@ -72,7 +75,7 @@ constexpr int chain_rounds(int dtype, bool aligned)
 }
 constexpr int kChainFan = 64;                                      // items summed per level = lanes
 constexpr long long kChainMaxSegments = 64LL * 64 * 64;            // three levels
-constexpr long long kChainMinBytes = 128LL << 20;                  // shorter arrays take the three launches (as fast or faster there)
+constexpr long long kChainMinBytes = 128LL << 20;                  // shorter arrays take the two launches (as fast or faster on arrays that the caches hold)
 constexpr int kChainSpinLimit = 1 << 16;                           // polls before a wave gives up
 using Word = unsigned long long;
 // Workspace of the one-pass schedule, in 8-byte words: ticket counter, flag, SP, G, A.  The ticket counter (one atomic per workgroup) and
@@ -121,7 +124,7 @@ template <class T> struct ScanVec { static constexpr int V = 16 / sizeof(T); };
 
 // Elements [i, i + V) of a, zeros past n.  ALIGNED: the base pointer is 16-byte aligned, so a
 // vector that lies wholly inside the array is one 16-byte access.  STREAM: non-temporal access --
-// the one-pass schedule, whose arrays are far larger than the caches, gains 6 % from it; the three
+// the one-pass schedule, whose arrays are far larger than the caches, gains 6 % from it; the two
 // launches keep plain accesses, their second read of a mid-sized array comes from the caches.
 template <class T, bool ALIGNED, bool STREAM = false>
 __device__ __forceinline__ void load_elems(const T* __restrict__ a, long long i, long long n, T (&v)[ScanVec<T>::V])
@@ -153,7 +156,7 @@ struct ScanPlan {
     long long rounds;    // wave-rounds in the array: ceil(n / (64 V))
     long long per_seg;   // wave-rounds per segment (a multiple of kScanRounds)
     int segments;        // ceil(rounds / per_seg), at most kScanMaxSegments
-    int reverse;         // launch 3 takes the segments last to first
+    int reverse;         // launch 2 takes the segments last to first
 };
 
 // Launch 1: sums[s] = sum of segment s.
@@ -188,46 +191,39 @@ __global__ __launch_bounds__(kBlock) void scan_reduce(const T* __restrict__ a, d
     if (lane == kWave - 1) sums[s] = acc;
 }
 
-// Launch 2: sums[s] <- sums[0] + ... + sums[s-1], in place, by one workgroup.  A thread owns up to
-// kOffsetsEach consecutive sums and fetches them all before it adds any.
-__global__ __launch_bounds__(kOffsetsThreads) void scan_offsets(double* __restrict__ sums, int segments)
+// The segment sums in runs of 64 x each: lane l of run u owns sums (64 u + l) each .. + each - 1.  Their total, and what
+// lies before the lane.
+__device__ __forceinline__ double run_of_sums(const double* __restrict__ sums, int segments, int each, int u, int lane, double (&x)[kSumsEach],
+                                              double& before)
 {
-    __shared__ double wave_total[kOffsetsThreads / kWave];
-    const int t = threadIdx.x, lane = t & (kWave - 1), w = t >> 6;
-    const int each = (segments + kOffsetsThreads - 1) / kOffsetsThreads;
-    const int i0 = t * each;
-    double x[kOffsetsEach];
+    const int i0 = (u * kWave + lane) * each;
 #pragma unroll
-    for (int k = 0; k < kOffsetsEach; ++k) x[k] = (k < each && i0 + k < segments) ? sums[i0 + k] : 0.0;
+    for (int k = 0; k < kSumsEach; ++k) x[k] = sums[k < each && i0 + k < segments ? i0 + k : 0];
     double mine = 0.0;
 #pragma unroll
-    for (int k = 0; k < kOffsetsEach; ++k) mine += x[k];
-    const double incl = wave_inclusive_scan(mine);
-    if (lane == kWave - 1) wave_total[w] = incl;
-    __syncthreads();
-    double run = shift_up(incl);   // total of the lanes below (0 in lane 0)
-    for (int k = 0; k < w; ++k) run += wave_total[k];
-#pragma unroll
-    for (int k = 0; k < kOffsetsEach; ++k) {
-        if (k < each && i0 + k < segments) sums[i0 + k] = run;
-        run += x[k];
+    for (int k = 0; k < kSumsEach; ++k) {
+        x[k] = k < each && i0 + k < segments ? x[k] : 0.0;
+        mine += x[k];
     }
+    const double incl = wave_inclusive_scan(mine);
+    before = shift_up(incl);
+    return read_lane(incl, kWave - 1);
 }
 
-// Launch 3: the scan proper.  offsets == nullptr: a single segment that starts from 0.
+// Launch 2: the scan proper.  sums == nullptr: a single segment that starts from 0.
 template <class T, bool ALIGNED>
-__global__ __launch_bounds__(kBlock) void scan_segments(const T* a, T* b, const double* __restrict__ offsets, ScanPlan pl)
+__global__ __launch_bounds__(kBlock) void scan_segments(const T* a, T* b, const double* __restrict__ sums, ScanPlan pl)
 {
     constexpr int V = ScanVec<T>::V;
-    const int lane = threadIdx.x & (kWave - 1);
-    long long s = (long long)blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6);
-    if (s >= pl.segments) return;
-    if (pl.reverse) s = pl.segments - 1 - s;
-    const long long r0 = s * pl.per_seg;
-    const long long r1 = r0 + pl.per_seg < pl.rounds ? r0 + pl.per_seg : pl.rounds;
-    double carry = offsets ? offsets[s] : 0.0;
-    for (long long r = r0; r < r1; r += kScanRounds) {
-        T v[kScanRounds][V];
+    __shared__ double run_total[kSumRuns];
+    const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const long long first = (long long)blockIdx.x * kWavesPerBlock + wave;
+    const long long s = pl.reverse ? pl.segments - 1 - first : first;
+    const bool active = s >= 0 && s < pl.segments;
+    const long long r0 = active ? s * pl.per_seg : 0;
+    const long long r1 = !active ? 0 : r0 + pl.per_seg < pl.rounds ? r0 + pl.per_seg : pl.rounds;
+    T v[kScanRounds][V];
+    auto load = [&](long long r) __attribute__((always_inline)) {
 #pragma unroll
         for (int k = 0; k < kScanRounds; ++k) {
             if (r + k < r1) load_elems<T, ALIGNED>(a, ((r + k) * kWave + lane) * V, pl.n, v[k]);
@@ -235,6 +231,34 @@ __global__ __launch_bounds__(kBlock) void scan_segments(const T* a, T* b, const 
 #pragma unroll
                 for (int j = 0; j < V; ++j) v[k][j] = T(0);
         }
+    };
+    load(r0);
+    double carry = 0.0;
+    if (sums) {
+        // Every sum before segment s, always added in the same order: the totals of the runs before its own, which the block's
+        // waves form in turn, what lies before it in its own run, and its lane's.
+        const int each = (pl.segments + kSumRuns * kWave - 1) / (kSumRuns * kWave);
+        const int own = active ? (int)s / each : 0, lane_s = own % kWave, u_s = own / kWave;
+        double x[kSumsEach], before;
+        run_of_sums(sums, pl.segments, each, u_s, lane, x, before);
+        carry = read_lane(before, lane_s);
+        double mine[kSumsEach];
+#pragma unroll
+        for (int k = 0; k < kSumsEach; ++k) mine[k] = read_lane(x[k], lane_s);
+        const long long last = pl.reverse ? pl.segments - 1 - (first - wave) : first - wave + kWavesPerBlock - 1;    // the block's highest segment
+        const int runs = (int)(last < pl.segments ? last : pl.segments - 1) / each / kWave;      // whole runs before it
+        for (int u = wave; u < runs; u += kWavesPerBlock) {
+            const double t = run_of_sums(sums, pl.segments, each, u, lane, x, before);
+            if (lane == 0) run_total[u] = t;
+        }
+        __syncthreads();
+        for (int u = 0; u < u_s; ++u) carry += run_total[u];
+#pragma unroll
+        for (int k = 0; k < kSumsEach; ++k)
+            if (k < (int)(s - (long long)own * each)) carry += mine[k];
+    }
+    for (long long r = r0; r < r1; r += kScanRounds) {
+        if (r != r0) load(r);
 #pragma unroll
         for (int k = 0; k < kScanRounds; ++k) {
             if (r + k < r1) {
@@ -409,16 +433,16 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2))) voi
 
 // The whole scan by ONE workgroup: 16 waves, each a contiguous piece of kScanRounds wave-rounds per
 // step, piece sums exchanged through LDS, one barrier per step; in place is fine.  Two uses:
-//  - short arrays (gave_up == nullptr): one launch instead of three, which is all that counts there;
+//  - short arrays (gave_up == nullptr): one launch instead of two, which is all that counts there;
 //  - the fallback of the one-pass schedule, enqueued behind every pass: it returns at once unless
 //    the word at gave_up is set.  It is slow (about 30 ms per GiB) and only runs after a wave has
 //    already waited for 2^16 polls.
 template <class T, bool ALIGNED>
-__global__ __launch_bounds__(kOffsetsThreads) void scan_one_group(const T* a, T* b, long long n, const Word* gave_up)
+__global__ __launch_bounds__(kGroupThreads) void scan_one_group(const T* a, T* b, long long n, const Word* gave_up)
 {
     if (gave_up && __hip_atomic_load(gave_up, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0) return;
     constexpr int V = ScanVec<T>::V;
-    constexpr int NWAVES = kOffsetsThreads / kWave;
+    constexpr int NWAVES = kGroupThreads / kWave;
     __shared__ double piece_total[2][NWAVES];
     const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x >> 6;
     const long long per_wave = (long long)kScanRounds * kWave * V, per_step = per_wave * NWAVES;
@@ -487,7 +511,7 @@ int segment_cap()
 }
 
 // Segments of the one-pass schedule with `rounds` wave-rounds each, or 0 if an array of this size
-// does not take it (the pointers can still rule it out: in place always takes the three launches).
+// does not take it (the pointers can still rule it out: in place always takes the two launches).
 // Whether it does is decided on the shorter segments, whatever the alignment.
 long long chained_segments(long long n, int dtype, int rounds)
 {
@@ -506,7 +530,7 @@ long long one_group_limit(int dtype)
     return v < 0 ? kOneGroupBytes / (dtype == SSAM_F32 ? 4 : 8) : v;
 }
 
-size_t three_launch_bytes(long long n, int dtype)
+size_t two_launch_bytes(long long n, int dtype)
 {
     if (n <= one_group_limit(dtype)) return 0;
     const ScanPlan pl = plan_scan(n, dtype, segment_cap());
@@ -519,13 +543,12 @@ size_t chained_bytes(long long segs)
 }
 
 template <class T, bool ALIGNED>
-void launch_three(const void* d_in, void* d_out, double* sums, const ScanPlan& pl, hipStream_t st)
+void launch_two(const void* d_in, void* d_out, double* sums, const ScanPlan& pl, hipStream_t st)
 {
     const unsigned blocks = (unsigned)((pl.segments + kWavesPerBlock - 1) / kWavesPerBlock);
     if (pl.segments > 1) {
         hipLaunchKernelGGL((scan_reduce<T, ALIGNED>), dim3(blocks), dim3(kBlock), 0, st,
                            static_cast<const T*>(d_in), sums, pl);
-        hipLaunchKernelGGL(scan_offsets, dim3(1), dim3(kOffsetsThreads), 0, st, sums, pl.segments);
     }
     hipLaunchKernelGGL((scan_segments<T, ALIGNED>), dim3(blocks), dim3(kBlock), 0, st,
                        static_cast<const T*>(d_in), static_cast<T*>(d_out),
@@ -536,12 +559,12 @@ template <class T, bool ALIGNED>
 int launch_scan(const void* d_in, void* d_out, void* d_work, long long n, int dtype, long long chain_segs, hipStream_t st)
 {
     if (!chain_segs && n <= one_group_limit(dtype)) {
-        hipLaunchKernelGGL((scan_one_group<T, ALIGNED>), dim3(1), dim3(kOffsetsThreads), 0, st,
+        hipLaunchKernelGGL((scan_one_group<T, ALIGNED>), dim3(1), dim3(kGroupThreads), 0, st,
                            static_cast<const T*>(d_in), static_cast<T*>(d_out), n, static_cast<const Word*>(nullptr));
         return hipGetLastError() == hipSuccess ? SSAM_OK : SSAM_ERR_HIP;
     }
     if (!chain_segs) {
-        launch_three<T, ALIGNED>(d_in, d_out, static_cast<double*>(d_work), plan_scan(n, dtype, segment_cap()), st);
+        launch_two<T, ALIGNED>(d_in, d_out, static_cast<double*>(d_work), plan_scan(n, dtype, segment_cap()), st);
         return hipGetLastError() == hipSuccess ? SSAM_OK : SSAM_ERR_HIP;
     }
     Word* ws = static_cast<Word*>(d_work);
@@ -556,7 +579,7 @@ int launch_scan(const void* d_in, void* d_out, void* d_work, long long n, int dt
     const unsigned blocks = (unsigned)((chain_segs + kWavesPerBlock - 1) / kWavesPerBlock);
     hipLaunchKernelGGL((scan_chained<T, ALIGNED>), dim3(blocks), dim3(kBlock), 0, st,
                        static_cast<const T*>(d_in), static_cast<T*>(d_out), ws, cp);
-    hipLaunchKernelGGL((scan_one_group<T, ALIGNED>), dim3(1), dim3(kOffsetsThreads), 0, st,
+    hipLaunchKernelGGL((scan_one_group<T, ALIGNED>), dim3(1), dim3(kGroupThreads), 0, st,
                        static_cast<const T*>(d_in), static_cast<T*>(d_out), n, ws + kWsGaveUp);
     return hipGetLastError() == hipSuccess ? SSAM_OK : SSAM_ERR_HIP;
 }
@@ -612,8 +635,8 @@ int ssam_scan_static(const void* d_in, void* d_out, long long n, int dtype, void
 size_t ssam_scan_workspace_bytes(long long n, int dtype)
 {
     if (n <= 0 || n > (1LL << 40) || (dtype != SSAM_F32 && dtype != SSAM_F64)) return 0;
-    const size_t three = ssam::three_launch_bytes(n, dtype), one = ssam::chained_bytes(ssam::chained_segments(n, dtype, ssam::kChainRoundsUnaligned));
-    return three > one ? three : one;
+    const size_t two = ssam::two_launch_bytes(n, dtype), one = ssam::chained_bytes(ssam::chained_segments(n, dtype, ssam::kChainRoundsUnaligned));
+    return two > one ? two : one;
 }
 
 int ssam_scan(const void* d_in, void* d_out, long long n, int dtype, void* d_work, size_t work_bytes, void* hip_stream)
@@ -630,7 +653,7 @@ int ssam_scan(const void* d_in, void* d_out, long long n, int dtype, void* d_wor
     if (pa != pb && pa < pb + bytes && pb < pa + bytes) return SSAM_ERR_ALIAS;   // in place is fine, a partial overlap is not
     const bool aligned = pa % 16 == 0 && pb % 16 == 0;
     const long long chain_segs = pa == pb ? 0 : chained_segments(n, dtype, chain_rounds(dtype, aligned));
-    const size_t need = chain_segs ? chained_bytes(chained_segments(n, dtype, kChainRoundsUnaligned)) : three_launch_bytes(n, dtype);
+    const size_t need = chain_segs ? chained_bytes(chained_segments(n, dtype, kChainRoundsUnaligned)) : two_launch_bytes(n, dtype);
     if (need) {
         if (!d_work) return SSAM_ERR_NULL;
         const uintptr_t pw = (uintptr_t)d_work;

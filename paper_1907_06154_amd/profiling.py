@@ -339,7 +339,7 @@ def scan_summary(prefix: str, out_md: str) -> None:
     """The scan: <prefix>/<tag>_{trace,fetch,write}/ (rocprofv3 output) and <prefix>/<tag>_trace.txt (what the traced
     bench.py --tune run printed), tag = f32, f64; both schedules of the 1 GiB arrays in every run."""
     out = ["# rocprofv3 summary: inclusive scan (ssam_scan), 1 GiB arrays: 2^28 fp32 and 2^27 fp64 elements, both schedules\n",
-           "Both schedules are timed by the same command (`scan_chained=0`: three launches, `scan_chained=1`: one pass, the "
+           "Both schedules are timed by the same command (`scan_chained=0`: two launches, `scan_chained=1`: one pass, the "
            "default at this size), followed by the plain copy kernel on the same arrays.\n"]
     traffic = load_traffic()
     for tag, n, tname in (("f32", 1 << 28, "float"), ("f64", 1 << 27, "double")):
