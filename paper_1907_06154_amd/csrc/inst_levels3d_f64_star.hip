@@ -1,0 +1,6 @@
+// Several sweeps of a radius-1 3D stencil a launch (ssam_kernel3d_levels.h): fp64, 7-point star.
+#include "ssam_kernel3d_levels.h"
+
+namespace ssam {
+SSAM_LEVELS_KERNELS(double, 1)
+}  // namespace ssam

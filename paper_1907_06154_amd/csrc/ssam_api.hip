@@ -10,6 +10,7 @@
 #include "ssam_host.h"
 #include "ssam_kernel2d_split.h"
 #include "ssam_kernel2d_tile.h"
+#include "ssam_kernel3d_levels.h"
 #include "ssam_kernel3d_split.h"
 #include "ssam_kernel_dense.h"
 
@@ -390,6 +391,16 @@ int run_fused(const Problem3D& p, int max_sweeps, Geometry* geo, bool dry, std::
             if (name)
                 *name = std::string(p.dtype == SSAM_F32 ? "float" : "double") + "_R" + std::to_string(p.rx) + (budget <= 1 ? "_b1" : "_b2") +
                         "_tile_fused" + std::to_string(sweeps);
+            *rc = status_of(e);
+            return sweeps;
+        }
+    }
+    if (!flat && p.rx == 1 && p.ry == 1 && p.rz == 1 && tu.planes_per_wave <= 0 && tu.valid_lanes <= 0 && tu.variant < 0) {     // sweeps as levels of one march (the overrides are the other kernels')
+        const int budget = p.dtype == SSAM_F32 ? tap_budget<float>((const float*)p.c, 3, 3, 3, 1, 1, 1) : tap_budget<double>((const double*)p.c, 3, 3, 3, 1, 1, 1);
+        hipError_t e = hipSuccess;
+        if (const int sweeps = launch3d_levels(p, budget, max_sweeps, geo, dry, &e)) {
+            if (name)
+                *name = std::string(p.dtype == SSAM_F32 ? "float" : "double") + "_r111_b" + std::to_string(budget < 1 ? 1 : budget) + "_levels_fused" + std::to_string(sweeps);
             *rc = status_of(e);
             return sweeps;
         }
@@ -780,7 +791,7 @@ int ssam_describe(int kind, int W, int H, int D, const void* h_coef, int a, int 
         if (run_fused(p, c > 0 ? c : kMaxFusedSweeps, &g, true, &name, &rc)) return describe(rc, name, g, buf, buflen);
         return describe(run3d(p, &g, true, &name), name, g, buf, buflen);
     }
-    if (kind == 4) {   // the launch ssam_stencil_iterate uses on a 3D grid while two or more sweeps remain
+    if (kind == 4) {   // the launch ssam_stencil_iterate uses on a 3D grid while two sweeps remain
         if (!h_coef) return SSAM_ERR_NULL;
         if (int e = check_enums(boundary, dtype)) return e;
         if (int e = check_dims(W, H, D)) return e;
@@ -788,7 +799,7 @@ int ssam_describe(int kind, int W, int H, int D, const void* h_coef, int a, int 
             return SSAM_ERR_SHAPE;
         Problem3D p{nullptr, out, W, H, D, h_coef, a, b, c, boundary, dtype, nullptr};
         int rc = SSAM_OK;
-        if (run_fused(p, kMaxFusedSweeps, &g, true, &name, &rc)) return describe(rc, name, g, buf, buflen);
+        if (run_fused(p, 2, &g, true, &name, &rc)) return describe(rc, name, g, buf, buflen);
         return describe(run3d(p, &g, true, &name), name, g, buf, buflen);
     }
     if (kind == 5) {   // ssam_conv3d with (a, b, c) = (M, N, K) and the default anchor

@@ -1,0 +1,83 @@
+"""Sweeps as levels of one march along z: grids of exactly one tile, one row or column more, and tiles moved back from the grid's
+end, in every vector width; few planes, many; buffers aligned to the element only; against the CPU oracle."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads as wl
+from parity_util import assert_parity
+
+torch = pytest.importorskip("torch")
+
+# (D, H, W), all of more than 2^18 points
+GRIDS = [(257, 16, 64), (251, 17, 65), (65, 32, 128), (34, 61, 129), (33, 64, 130), (11, 100, 257), (5, 230, 300), (2, 400, 400),
+         (1, 600, 500), (70, 90, 96)]
+MASKS = {"star": wl.mask_star(1, 1, 1), "faces_edges": wl.mask_faces_edges(), "box": wl.mask_box(1, 1, 1)}
+
+
+def plan(ssam, shape, coef, boundary):
+    return ssam.ssam_describe("iterate3d", shape, coef, boundary).split()[0]
+
+
+def test_plans():
+    import paper_1907_06154_amd as ssam
+    for kind, mask in MASKS.items():
+        for dtype in (np.float32, np.float64):
+            coef = wl.seeded_coefficients(mask, 90, dtype)
+            assert "_levels_" in plan(ssam, (64, 64, 128), coef, "clamp")
+            assert "_levels_" not in plan(ssam, (64, 64, 64), coef, "zero")       # 2^18 points
+            assert "_levels_" not in plan(ssam, (300, 15, 128), coef, "zero")     # fewer rows than four waves'
+            assert "_levels_" not in plan(ssam, (128, 128, 63), coef, "zero")     # narrower than a wave
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("kind", list(MASKS))
+def test_matches_oracle(dtype, kind):
+    import paper_1907_06154_amd as ssam
+    coef = wl.seeded_coefficients(MASKS[kind], 91, dtype)
+    for shape in GRIDS:
+        fld = wl.uniform_field(shape, -1.0, 1.0, 900 + shape[2], dtype)
+        n = fld.size
+        for boundary in ("zero", "clamp"):
+            for steps, skew in ((2, 0), (3, 1), (4, 0), (7, 1)):
+                print(f"levels {np.dtype(dtype).name} {kind} {shape} {boundary} steps {steps}", flush=True)
+                buf = torch.full((2, n + 8), float("nan"), dtype=torch.from_numpy(fld).dtype, device="cuda")
+                a, b = buf[0][skew:n + skew].view(shape), buf[1][3 * skew:n + 3 * skew].view(shape)
+                a.copy_(torch.from_numpy(fld))
+                got = ssam.ssam_stencil_iterate(a, b, coef, steps, boundary)
+                assert_parity(got.cpu().numpy(), oracle.iterate(fld, coef, steps, boundary), coef, 1.0,
+                              f"{kind} {shape} {boundary} steps {steps}")
+                guard = torch.cat([buf[0][:skew], buf[0][n + skew:], buf[1][:3 * skew], buf[1][n + 3 * skew:]])
+                assert torch.isnan(guard).all()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+def test_every_tile_width_with_its_halo(dtype):
+    """Three sweeps on grids whose last tiles end one column after the others: each width's tiles with the least overlap."""
+    import paper_1907_06154_amd as ssam
+    coef = wl.seeded_coefficients(MASKS["star"], 92, dtype)
+    for shape in ((200, 150, 300), (60, 70, 361), (48, 130, 241), (90, 59, 177)):
+        fld = wl.uniform_field(shape, -1.0, 1.0, 93, dtype)
+        a = torch.from_numpy(fld).cuda()
+        got = ssam.ssam_stencil_iterate(a, torch.empty_like(a), coef, 3, "zero").cpu().numpy()
+        assert_parity(got, oracle.iterate(fld, coef, 3, "zero"), coef, 1.0, f"{shape}")
+
+
+@pytest.mark.gpu
+def test_zero_padding_keeps_infinities_apart():
+    """An infinity reaches the points the sweeps carry it to and no others: at the grid's corners and beside a tile's rim."""
+    import paper_1907_06154_amd as ssam
+    coef = wl.seeded_coefficients(MASKS["star"], 94, np.float32)
+    shape = (40, 70, 140)
+    at = ((0, 0, 0), (39, 69, 139), (20, 30, 62), (0, 35, 124))
+    fld = np.zeros(shape, dtype=np.float32)
+    grid = np.indices(shape)
+    near = np.zeros(shape, dtype=bool)
+    for p in at:
+        fld[p] = np.inf
+        near |= sum(np.abs(g - c) for g, c in zip(grid, p)) <= 5
+    a = torch.from_numpy(fld).cuda()
+    got = ssam.ssam_stencil_iterate(a, torch.empty_like(a), coef, 5, "zero").cpu().numpy()
+    assert np.array_equal(~np.isfinite(got), near) and not got[~near].any()
