@@ -6,8 +6,8 @@
 // an eight-column window along each staged row: two 16-byte LDS reads bring the operands of 64 multiply-adds (128 with two
 // planes), the filter values come by scalar loads, four at a time, each used 4 x 4 times.
 // Measured (tap list -> here): 20x20 on 2048^2 968 -> 104 us (32 TFLOP/s), 12x12 on 1999x1501 264 -> 39, 32x32 on 2048^2 2455 ->
-// 274, 9x9x9 on 256^3 7400 -> 1430.  In 3D the few rows of a plane that all output rows share, and the barriers around every
-// staged plane, leave it at 8 .. 17 TFLOP/s.
+// 274, 9x9x9 on 256^3 7400 -> 1200.  In 3D the few rows of a plane that all output rows share, and the barriers around every
+// staged plane, leave it at 8 .. 20 TFLOP/s.
 // Extents are run-time values.  Taps beyond the filter are never multiplied (no zero padding), so infinities and NaN reach
 // exactly the outputs whose footprint holds them, and every output adds its taps in the order of the tap-list kernel.
 #pragma once
@@ -30,7 +30,7 @@ struct DenseArgs {
     int tiles_x, tiles_y;
     int tiles;
     int blocks, xcd_remap;
-    double w[kDenseTaps];
+    double w[kDenseTaps + 4];      // four are read together, also of the last row's end
 };
 
 template <int TZ, int NW>
@@ -126,10 +126,90 @@ __global__ __launch_bounds__(NW* kWave) void dense_kernel(const DenseArgs a)
                 else taps(std::integral_constant<int, 3>{}, m);
             }
         };
-        const bool planes_all = TZ == 1 || (p >= TZ - 1 && p < K);
-        for (int r = 0; r < N + 3; ++r) {
-            if (planes_all && r >= 3 && r < N) row(std::true_type{}, r);
-            else row(std::false_type{}, r);
+        // 3D: rows first .. last - 1, in which every output row and plane has taps, as a flat run of units, four filter columns of
+        // one filter plane each.  A unit's window and weights are requested while the one before multiplies: scalar loads return
+        // in any order, so the wait for a unit's weights is one for everything requested before it, and its first row comes before
+        // the next requests.  Row by row, every eight columns waited for their scalar loads (5x6x4 on 256^3 423 -> 346 us, 7x7x7
+        // on 53x256x202 203 -> 163, 9x9x9 on 256^3 1409 -> 1199, 8x8x2 on 256x256x200 262 -> 213; 4x4x4 and 2x2x9
+        // equal).  In 2D it is mixed, 20x20 on 2048^2 103 -> 115, so 2D and K = 1 keep the form row by row.
+        auto rows_all = [&](int first, int last) __attribute__((always_inline)) {
+            double win[2][8], w[2][4][4];
+            int rn = first, mn = 0;                  // the unit requested next
+            auto request_window = [&](int buf) __attribute__((always_inline)) {
+                const double* const q = own + rn * pitch + mn;
+#pragma unroll
+                for (int i = 0; i < 8; i += 2) {
+                    const vec2 v = *reinterpret_cast<const vec2*>(q + i);
+                    win[buf][i] = v[0];
+                    win[buf][i + 1] = v[1];
+                }
+            };
+            auto request_weights = [&](int buf, int t) __attribute__((always_inline)) {
+                const ConstPtr<double> wr = wts + ((size_t)(p - t) * N + rn) * M + mn;
+#pragma unroll
+                for (int y = 0; y < 4; ++y)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) w[buf][y][i] = (wr - (long)y * M)[i];
+            };
+            auto multiply = [&](int wb, int vb, int t, int y, int i) __attribute__((always_inline)) {
+#pragma unroll
+                for (int x = 0; x < 4; ++x) acc[t][y][x] = fma_t(win[vb][i + x], w[wb][y][i], acc[t][y][x]);
+            };
+            // The filter columns of output plane t (FULL: four): the first output row, the requests, the other rows.
+            auto unit = [&](auto full_tag, auto vb_tag, auto t_tag, int count) __attribute__((always_inline)) {
+                constexpr bool FULL = decltype(full_tag)::value;
+                constexpr int vb = decltype(vb_tag)::value, t = decltype(t_tag)::value, wb = (vb * TZ + t) & 1;
+                auto output_row = [&](int y) __attribute__((always_inline)) {
+                    multiply(wb, vb, t, y, 0);
+                    if (FULL || count > 1) multiply(wb, vb, t, y, 1);
+                    if (FULL || count > 2) multiply(wb, vb, t, y, 2);
+                    if constexpr (FULL) multiply(wb, vb, t, y, 3);
+                };
+                output_row(0);
+                __builtin_amdgcn_sched_barrier(0);
+                if constexpr (t == TZ - 1) {
+                    mn += 4;
+                    const bool row_end = mn >= M;
+                    mn = row_end ? 0 : mn;
+                    rn = row_end ? min(rn + 1, last - 1) : rn;      // past the last unit: in bounds, and unused
+                    request_window(vb ^ 1);
+                    request_weights(wb ^ 1, 0);
+                } else {
+                    request_weights(wb ^ 1, t + 1);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int y = 1; y < 4; ++y) output_row(y);
+                __builtin_amdgcn_sched_barrier(0);
+            };
+            request_window(0);
+            request_weights(0, 0);
+            const int per_row = (M + 3) / 4, units = (last - first) * per_row;
+            int m = 0;
+            auto both = [&](auto vb_tag) __attribute__((always_inline)) {
+                const int count = M - m;
+                if (count >= 4) static_for<TZ>([&](auto t) __attribute__((always_inline)) { unit(std::true_type{}, vb_tag, t, 4); });
+                else static_for<TZ>([&](auto t) __attribute__((always_inline)) { unit(std::false_type{}, vb_tag, t, count); });
+                m = m + 4 < M ? m + 4 : 0;
+            };
+            int u = 0;
+            for (; u + 1 < units; u += 2) {
+                both(std::integral_constant<int, 0>{});
+                both(std::integral_constant<int, 1>{});
+            }
+            if (u < units) both(std::integral_constant<int, 0>{});
+        };
+        if constexpr (TZ == 1) {
+            for (int r = 0; r < N + 3; ++r) {
+                if (r >= 3 && r < N) row(std::true_type{}, r);
+                else row(std::false_type{}, r);
+            }
+        } else if (p >= TZ - 1 && p < K && N > 3) {
+            for (int r = 0; r < 3; ++r) row(std::false_type{}, r);
+            rows_all(3, N);
+            for (int r = N; r < N + 3; ++r) row(std::false_type{}, r);
+        } else {
+            for (int r = 0; r < N + 3; ++r) row(std::false_type{}, r);
         }
     }
 

@@ -89,3 +89,15 @@ def test_infinities_and_nan_reach_their_footprint_only(ssam):
             got, _ = both(ssam, lambda: ssam.ssam_conv2d(torch.from_numpy(dirty).cuda(), filt, "zero"))
             want = oracle.conv2d(dirty, filt, "zero")
             assert np.array_equal(np.isnan(got), np.isnan(want)) and np.array_equal(np.isinf(got), np.isinf(want))
+
+
+@pytest.mark.parametrize("M,N,K", [(7, 4, 2), (8, 4, 3), (5, 5, 5), (6, 6, 2), (1, 5, 4), (2, 6, 3), (3, 4, 4)])
+def test_rows_that_all_output_rows_and_planes_share(ssam, M, N, K):
+    """One, two and more such rows, each remainder of four filter columns, an odd and an even number of planes."""
+    filt = np.random.default_rng(1050 + M + 20 * N + 400 * K).uniform(-1.0, 1.0, (K, N, M))
+    for D, H, W in ((6, 33, 66), (7, 16, 65)):
+        vol = wl.uniform_field((D, H, W), -1.0, 1.0, 1051, np.float64)
+        print(f"dense f64 {M}x{N}x{K} {vol.shape}", flush=True)
+        d = torch.from_numpy(vol).cuda()
+        got, plain = both(ssam, lambda: ssam.ssam_conv3d(d, filt, "clamp"))
+        check(got, plain, oracle.conv3d(vol, filt, "clamp"), filt, (M, N, K, vol.shape))
