@@ -111,10 +111,10 @@ def launches_of(ssam, case):
     single = ssam.ssam_describe(case.kind, case.shape, case_coef(case), case.boundary).split()[0]
     names, t = [], 0
     while t < case.steps:
-        if kind == "iterate2d":
+        if case.steps - t == 1:
+            nm = single
+        else:
             nm = ssam.ssam_describe(kind, case.shape, case_coef(case), case.boundary, remaining=case.steps - t).split()[0]
-        else:   # 3D: pairs of sweeps while two or more remain
-            nm = ssam.ssam_describe(kind, case.shape, case_coef(case), case.boundary).split()[0] if case.steps - t >= 2 else single
         t += int(nm.rsplit("_fused", 1)[1]) if "_fused" in nm else 1
         names.append(nm)
     return len(names), max(set(names), key=names.count), names

@@ -140,7 +140,7 @@ const char *ssam_status_string(int status);
  * on a 2D grid with (a, b) = (rx, ry) while c sweeps remain (c <= 0: many); an instance named
  * "..._fusedS" performs S sweeps; kind 4 = the same for a 3D grid with (a, b, c) = (rx, ry, rz)
  * while two sweeps remain; kind 5 = ssam_conv3d with (a, b, c) = (M, N, K) and the default
- * anchor.  The tile plan follows the paper's overlapped
+ * anchor; kind 6 = kind 4 for a stencil of radius a on every axis while c sweeps remain.  The tile plan follows the paper's overlapped
  * blocking (Sec. 4.5, Sec. 4.7) re-derived for 64 lanes of V columns each. */
 int ssam_describe(int kind, int W, int H, int D, const void *h_coef, int a, int b, int c,
                   int boundary, int dtype, char *buf, int buflen);

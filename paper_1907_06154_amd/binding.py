@@ -257,7 +257,11 @@ def ssam_describe(kind: str, shape, coef, boundary: str = "zero", remaining: int
         H, W = shape
         rx, ry, _ = _radii(coef, 2)
         st = lib().ssam_describe(3, W, H, 1, coef.ctypes.data, rx, ry, int(remaining), BOUNDARY[boundary], code, buf, 512)
-    elif kind == "iterate3d":   # the launch ssam_stencil_iterate issues on a 3D grid while >= 2 sweeps are left
+    elif kind == "iterate3d" and remaining > 0 and len(set(coef.shape)) == 1:
+        D, H, W = shape
+        r, _, _ = _radii(coef, 3)
+        st = lib().ssam_describe(6, W, H, D, coef.ctypes.data, r, 0, int(remaining), BOUNDARY[boundary], code, buf, 512)
+    elif kind == "iterate3d":   # the launch ssam_stencil_iterate issues on a 3D grid while two sweeps are left
         D, H, W = shape
         rx, ry, rz = _radii(coef, 3)
         st = lib().ssam_describe(4, W, H, D, coef.ctypes.data, rx, ry, rz, BOUNDARY[boundary], code, buf, 512)

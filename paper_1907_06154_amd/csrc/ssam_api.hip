@@ -362,9 +362,34 @@ const Instance3D* pick3d(const Problem3D& p, int want_variant, int sweeps = 1)
     return best;
 }
 
-// Several sweeps in one launch, where the shape has a fused instance (zero padding; 3D only when
-// marching along z): the deepest compiled one that does not exceed `max_sweeps` (the sweeps still
-// to do) nor the "fuse_sweeps" cap.  Returns the number of sweeps the launch performs, 0 when the
+// Sweeps of the next launch while `remaining` are to do: the smallest depth with which, the deepest that fits first, the rest
+// takes no more launches than with all depths.  A launch's time grows with its depth at least in proportion beyond the deepest
+// one that is bound by memory, so equal depths are the better split: 8192^2, us, deepest first and like this: nine sweeps of the fp64
+// box of radius 1 459 -> 436 (8 + 1, 6 + 3), eighteen under the clamp rule 925 -> 759; eight of the fp32 box 264 -> 222 (6 + 2, 4 + 4);
+// five of the fp64 box of radius 2 550 -> 501 (4 + 1, 3 + 2), of the fp32 star of radius 3 on 2048x2176 41 -> 32.
+// keep_single: up to this depth a launch is bound by memory and one sweep left over is cheaper than a share of it (five sweeps of the
+// fp64 star of radius 1 on 8192^2: 395 as 4 + 1, 411 as 3 + 2; seven 400 as 6 + 1, 420 as 4 + 3).
+int fused_depth(int remaining, int deepest, int keep_single, const Instance2D* const* by_depth)
+{
+    while (deepest >= 2 && !by_depth[deepest]) --deepest;
+    if (deepest < 2 || remaining > 4 * kMaxFusedSweeps || (remaining == deepest + 1 && deepest <= keep_single)) return deepest;
+    auto launches = [&](int most) {
+        int n = remaining, count = 0;
+        for (; n > 0; ++count) {
+            int d = n < most ? n : most;
+            while (d > 1 && !by_depth[d]) --d;
+            n -= d;
+        }
+        return count;
+    };
+    const int fewest = launches(deepest);
+    for (int d = 2; d < deepest; ++d)
+        if (by_depth[d] && launches(d) == fewest) return d;
+    return deepest;
+}
+
+// Several sweeps in one launch, where the shape has a fused instance (3D only when marching along z): in 3D the deepest compiled
+// one that does not exceed `max_sweeps` (the sweeps still to do) nor the "fuse_sweeps" cap, in 2D see fused_depth.  Returns the number of sweeps the launch performs, 0 when the
 // caller should run a single sweep instead.
 int run_fused(const Problem3D& p, int max_sweeps, Geometry* geo, bool dry, std::string* name, int* rc)
 {
@@ -379,9 +404,6 @@ int run_fused(const Problem3D& p, int max_sweeps, Geometry* geo, bool dry, std::
     // sweeps and more per launch were faster at every size tried (256^2 upwards).
     const bool small = (long long)p.W * p.H * p.D < kFuseTwoMinPoints && tu.fuse_sweeps < 0;
     Problem2D q{p.in, p.out, p.W, p.H, p.c, 2 * p.rx + 1, 2 * p.ry + 1, p.rx, p.ry, p.boundary, p.dtype, p.stream};
-    // the tightest tap shape any multi-sweep instance offers for this stencil: a deeper instance of a
-    // wider shape (a box standing in for a star) is not taken over a shallower one of the exact shape
-    int shape_budget = 0;
     // small grids: the kernel that keeps whole tiles in registers (the tile overrides and variants are the marching kernels')
     if (flat && p.rx == p.ry && tu.rows_per_wave <= 0 && tu.valid_lanes <= 0 && tu.variant < 0) {
         const int budget = p.dtype == SSAM_F32 ? tap_budget<float>((const float*)p.c, q.M, q.N, 1, q.ax, q.ay, 0)
@@ -405,28 +427,34 @@ int run_fused(const Problem3D& p, int max_sweeps, Geometry* geo, bool dry, std::
             return sweeps;
         }
     }
+    const int deepest = max_sweeps < kMaxFusedSweeps ? max_sweeps : kMaxFusedSweeps;
     if (flat) {
         const Instance2D* tight = p.dtype == SSAM_F32 ? pick2d<float>(q, true, 0, 0, true) : pick2d<double>(q, true, 0, 0, true);
         if (!tight) return 0;
-        shape_budget = tight->budget;
+        // of the tightest tap shape any multi-sweep instance offers for this stencil: a deeper instance of a
+        // wider shape (a box standing in for a star) is not taken over a shallower one of the exact shape
+        const Instance2D* by_depth[kMaxFusedSweeps + 1] = {};
+        for (int sweeps = small ? 3 : 2; sweeps <= deepest; ++sweeps)
+            for (int variant : {v, 0}) {
+                const Instance2D* inst = p.dtype == SSAM_F32 ? pick2d<float>(q, true, variant, sweeps) : pick2d<double>(q, true, variant, sweeps);
+                if (!inst || inst->budget != tight->budget || by_depth[sweeps]) continue;
+                if ((long)p.W * p.H >= (p.boundary == SSAM_BOUNDARY_CLAMP ? inst->clamp_from : inst->zero_from)) by_depth[sweeps] = inst;
+            }
+        const bool star = tight->budget == 1;
+        const int keep_single = p.dtype == SSAM_F32 ? (star && p.rx == 1 ? 4 : 0) : p.rx == 1 ? 6 : star && p.rx == 2 ? 4 : 0;
+        const int sweeps = fused_depth(max_sweeps, deepest, keep_single, by_depth);
+        if (sweeps < 2) return 0;
+        if (name) *name = by_depth[sweeps]->name;
+        *rc = status_of(by_depth[sweeps]->launch(q, tu, geo, dry));
+        return sweeps;
     }
-    for (int sweeps = max_sweeps < kMaxFusedSweeps ? max_sweeps : kMaxFusedSweeps; sweeps >= 2; --sweeps) {
+    for (int sweeps = deepest; sweeps >= 2; --sweeps) {
         if (sweeps == 2 && small) break;
-        hipError_t e;
-        if (flat) {
-            const Instance2D* inst = p.dtype == SSAM_F32 ? pick2d<float>(q, true, v, sweeps) : pick2d<double>(q, true, v, sweeps);
-            if ((!inst || inst->budget != shape_budget) && v != 0)
-                inst = p.dtype == SSAM_F32 ? pick2d<float>(q, true, 0, sweeps) : pick2d<double>(q, true, 0, sweeps);
-            if (!inst || inst->budget != shape_budget) continue;
-            if (name) *name = inst->name;
-            e = inst->launch(q, tu, geo, dry);
-        } else {
-            const Instance3D* inst = p.dtype == SSAM_F32 ? pick3d<float>(p, v, sweeps) : pick3d<double>(p, v, sweeps);
-            if (!inst && v != 0) inst = p.dtype == SSAM_F32 ? pick3d<float>(p, 0, sweeps) : pick3d<double>(p, 0, sweeps);
-            if (!inst || (p.boundary == SSAM_BOUNDARY_CLAMP && !inst->fuses_clamp)) continue;
-            if (name) *name = inst->name;
-            e = inst->launch(p, tu, geo, dry);
-        }
+        const Instance3D* inst = p.dtype == SSAM_F32 ? pick3d<float>(p, v, sweeps) : pick3d<double>(p, v, sweeps);
+        if (!inst && v != 0) inst = p.dtype == SSAM_F32 ? pick3d<float>(p, 0, sweeps) : pick3d<double>(p, 0, sweeps);
+        if (!inst || (p.boundary == SSAM_BOUNDARY_CLAMP && !inst->fuses_clamp)) continue;
+        if (name) *name = inst->name;
+        const hipError_t e = inst->launch(p, tu, geo, dry);
         *rc = status_of(e);
         return sweeps;
     }
@@ -788,10 +816,12 @@ int ssam_describe(int kind, int W, int H, int D, const void* h_coef, int a, int 
         if (a < 0 || b < 0 || a > SSAM_MAX_RADIUS || b > SSAM_MAX_RADIUS) return SSAM_ERR_SHAPE;
         Problem3D p{nullptr, out, W, H, 1, h_coef, a, b, 0, boundary, dtype, nullptr};
         int rc = SSAM_OK;
-        if (run_fused(p, c > 0 ? c : kMaxFusedSweeps, &g, true, &name, &rc)) return describe(rc, name, g, buf, buflen);
+        if (run_fused(p, c > 0 ? c : 3 * kMaxFusedSweeps, &g, true, &name, &rc)) return describe(rc, name, g, buf, buflen);
         return describe(run3d(p, &g, true, &name), name, g, buf, buflen);
     }
-    if (kind == 4) {   // the launch ssam_stencil_iterate uses on a 3D grid while two sweeps remain
+    if (kind == 4 || kind == 6) {   // the launch ssam_stencil_iterate uses on a 3D grid while two, or c, sweeps remain
+        const int remaining = kind == 6 ? c : 2;
+        if (kind == 6) b = c = a;
         if (!h_coef) return SSAM_ERR_NULL;
         if (int e = check_enums(boundary, dtype)) return e;
         if (int e = check_dims(W, H, D)) return e;
@@ -799,7 +829,7 @@ int ssam_describe(int kind, int W, int H, int D, const void* h_coef, int a, int 
             return SSAM_ERR_SHAPE;
         Problem3D p{nullptr, out, W, H, D, h_coef, a, b, c, boundary, dtype, nullptr};
         int rc = SSAM_OK;
-        if (run_fused(p, 2, &g, true, &name, &rc)) return describe(rc, name, g, buf, buflen);
+        if (remaining > 1 && run_fused(p, remaining, &g, true, &name, &rc)) return describe(rc, name, g, buf, buflen);
         return describe(run3d(p, &g, true, &name), name, g, buf, buflen);
     }
     if (kind == 5) {   // ssam_conv3d with (a, b, c) = (M, N, K) and the default anchor

@@ -81,7 +81,8 @@ struct Instance2D {
     int dtype, M, N, AX, budget;  // budget 2 = dense box, 1 = star
     int variant;                  // 0 = default instance for the shape
     Launch2DFn launch;
-    int sweeps = 1;               // Jacobi sweeps one launch performs (2: the fused kernel, zero padding only)
+    int sweeps = 1;               // Jacobi sweeps one launch performs (from 2 on: the fused kernel)
+    long zero_from = 0, clamp_from = 0;   // points of the smallest grid it is taken for, by boundary rule
 };
 
 struct Instance3D {

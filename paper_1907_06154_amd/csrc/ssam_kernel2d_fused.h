@@ -339,11 +339,13 @@ hipError_t launch2d_fused(const Problem2D& pr, const Tuning& tu, Geometry* geo, 
     return hipGetLastError();
 }
 
-// Registers the S-sweep kernel for the centred (2R+1)x(2R+1) stencil of the given budget.
-#define SSAM_INSTANCE_2D_FUSED(T, DT, V, P, R, BUDGET, S, NT, VARIANT)                                          \
+// Registers the S-sweep kernel for the centred (2R+1)x(2R+1) stencil of the given budget; the second form for grids of at least
+// ZERO_FROM points with zero padding and CLAMP_FROM points under the clamp rule.
+#define SSAM_INSTANCE_2D_FUSED(T, DT, V, P, R, BUDGET, S, NT, VARIANT) SSAM_INSTANCE_2D_FUSED_FROM(T, DT, V, P, R, BUDGET, S, NT, VARIANT, 0, 0)
+#define SSAM_INSTANCE_2D_FUSED_FROM(T, DT, V, P, R, BUDGET, S, NT, VARIANT, ZERO_FROM, CLAMP_FROM)              \
     static ::ssam::Register2D SSAM_CAT(reg2df_, __COUNTER__)(::ssam::Instance2D{                                 \
         #T "_R" #R "_b" #BUDGET "_v" #V "p" #P "nt" #NT "_fused" #S, DT, 2 * (R) + 1, 2 * (R) + 1, R, BUDGET,    \
         VARIANT,                                                                                                 \
-        &::ssam::launch2d_fused<T, V, P, ::ssam::TapMask<2 * (R) + 1, 2 * (R) + 1, R, R, BUDGET>, S, NT>, S})
+        &::ssam::launch2d_fused<T, V, P, ::ssam::TapMask<2 * (R) + 1, 2 * (R) + 1, R, R, BUDGET>, S, NT>, S, ZERO_FROM, CLAMP_FROM})
 
 }  // namespace ssam

@@ -1,0 +1,94 @@
+"""How many sweeps of a 2D iteration one launch of the marching kernels does: the plan on the CPU, the deepest instances against the
+CPU oracle on the GPU."""
+import re
+
+import numpy as np
+import pytest
+
+import oracle
+import workloads as wl
+from parity_util import assert_parity
+
+torch = pytest.importorskip("torch")
+import paper_1907_06154_amd.binding as ssam  # noqa: E402
+
+
+def coefficients(kind, r, dtype, seed=1100):
+    mask = wl.mask_box(r, r) if kind == "box" else wl.mask_star(r, r)
+    return wl.seeded_coefficients(mask, seed + r, dtype)[0]
+
+
+def depth(shape, coef, boundary, remaining):
+    m = re.search(r"_fused(\d+)$", ssam.ssam_describe("iterate2d", shape, coef, boundary, remaining=remaining).split()[0])
+    return int(m.group(1)) if m else 1
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("kind,r", [("box", 1), ("star", 1), ("box", 2), ("star", 2), ("star", 3), ("star", 4), ("star", 5), ("star", 6)])
+def test_depths_take_no_more_launches_than_the_deepest_first(dtype, kind, r):
+    coef = coefficients(kind, r, dtype)
+    for shape in ((8192, 8192), (8191, 8001), (6000, 4100)):
+        for boundary in ("zero", "clamp"):
+            depths = {s for s in range(2, 9) if depth(shape, coef, boundary, s) == s}
+            for steps in list(range(1, 34)) + [50, 100]:
+                got, t = [], 0
+                while t < steps:
+                    got.append(depth(shape, coef, boundary, steps - t))
+                    t += got[-1]
+                assert t == steps and all(d == 1 or d in depths for d in got)
+                count, n = 0, steps
+                while n:
+                    n -= max([d for d in depths if d <= n], default=1)
+                    count += 1
+                assert len(got) == count, (kind, r, shape, boundary, steps, got)
+
+
+def check(shape, coef, boundary, steps, rows):
+    fld = wl.uniform_field(shape, -1.0, 1.0, 1110 + shape[0], np.float64)
+    print(f"depth {coef.shape} {shape} {boundary} rows {rows} steps {steps}", flush=True)
+    ssam.ssam_set_tuning("rows_per_wave", rows)
+    try:
+        a = torch.from_numpy(fld).cuda()
+        res = ssam.ssam_stencil_iterate(a, torch.full_like(a, float("nan")), coef, steps, boundary)
+    finally:
+        ssam.ssam_set_tuning("rows_per_wave", -1)
+    assert_parity(res.cpu().numpy(), oracle.iterate(fld, coef, steps, boundary), coef, 1.0, f"{coef.shape} {shape} {boundary} {rows} {steps}")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape", [(5, 9), (33, 112), (61, 257), (97, 450), (130, 301)])
+def test_eight_sweeps_two_rows_a_group(shape):
+    """Tiles of a few rows, tails, rows that are not whole vectors, grids smaller than the halo."""
+    coef = coefficients("star", 1, np.float64)
+    for boundary in ("zero", "clamp"):
+        for rows in (2, 24, 64):
+            for steps in (8, 9):
+                check(shape, coef, boundary, steps, rows)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("r,S", [(2, 6), (3, 4), (5, 3)])
+@pytest.mark.parametrize("shape,boundary", [((3001, 3007), "zero"), ((2999, 3202), "zero"), ((7001, 7203), "clamp"), ((7103, 7202), "clamp")])
+def test_deepest_instances_on_the_smallest_grids_that_take_them(r, S, shape, boundary):
+    coef = coefficients("star", r, np.float64)
+    assert (depth(shape, coef, boundary, S) == S) == (boundary == "zero" or r != 2)
+    for rows in (-1, 8):
+        if boundary == "zero" or rows < 0:
+            check(shape, coef, boundary, S, rows)
+
+
+def test_smaller_grids_keep_the_shallower_instances():
+    for r, S in ((2, 6), (3, 4), (5, 3)):
+        coef = coefficients("star", r, np.float64)
+        assert depth((2999, 2999), coef, "zero", S) < S and depth((7000, 7001), coef, "clamp", S) < S
+
+
+@pytest.mark.parametrize("steps,want", [(1, [1]), (2, [2]), (3, [3]), (4, [2, 2]), (10, [3, 3, 2, 2])])
+def test_plan_of_a_3d_iteration(steps, want):
+    coef = wl.seeded_coefficients(wl.mask_star(1, 1, 1), 1130, np.float64)
+    got, t = [], 0
+    while t < steps:
+        m = re.search(r"_fused(\d+)$", ssam.ssam_describe("iterate3d", (512, 512, 512), coef, "zero", remaining=steps - t).split()[0])
+        got.append(int(m.group(1)) if m else 1)
+        t += got[-1]
+    assert got == want
