@@ -439,7 +439,7 @@ int run_fused(const Problem3D& p, int max_sweeps, Geometry* geo, bool dry, std::
             for (int variant : {v, 0}) {
                 const Instance2D* inst = p.dtype == SSAM_F32 ? pick2d<float>(q, true, variant, sweeps) : pick2d<double>(q, true, variant, sweeps);
                 if (!inst || inst->budget != tight->budget || by_depth[sweeps]) continue;
-                if ((long)p.W * p.H >= (p.boundary == SSAM_BOUNDARY_CLAMP ? inst->clamp_from : inst->zero_from)) by_depth[sweeps] = inst;
+                if ((long)p.W * p.H >= 1000000L * (p.boundary == SSAM_BOUNDARY_CLAMP ? inst->clamp_from : inst->zero_from)) by_depth[sweeps] = inst;
             }
         const bool star = tight->budget == 1;
         const int keep_single = p.dtype == SSAM_F32 ? (p.rx == 1 ? 4 : 0) : p.rx == 1 ? 6 : star && p.rx == 2 ? 4 : 0;

@@ -82,7 +82,7 @@ struct Instance2D {
     int variant;                  // 0 = default instance for the shape
     Launch2DFn launch;
     int sweeps = 1;               // Jacobi sweeps one launch performs (from 2 on: the fused kernel)
-    long zero_from = 0, clamp_from = 0;   // points of the smallest grid it is taken for, by boundary rule
+    short zero_from = 0, clamp_from = 0;   // million points of the smallest grid it is taken for, by boundary rule
 };
 
 struct Instance3D {

@@ -340,7 +340,7 @@ hipError_t launch2d_fused(const Problem2D& pr, const Tuning& tu, Geometry* geo, 
 }
 
 // Registers the S-sweep kernel for the centred (2R+1)x(2R+1) stencil of the given budget; the second form for grids of at least
-// ZERO_FROM points with zero padding and CLAMP_FROM points under the clamp rule.
+// ZERO_FROM million points with zero padding and CLAMP_FROM under the clamp rule.
 #define SSAM_INSTANCE_2D_FUSED(T, DT, V, P, R, BUDGET, S, NT, VARIANT) SSAM_INSTANCE_2D_FUSED_FROM(T, DT, V, P, R, BUDGET, S, NT, VARIANT, 0, 0)
 #define SSAM_INSTANCE_2D_FUSED_FROM(T, DT, V, P, R, BUDGET, S, NT, VARIANT, ZERO_FROM, CLAMP_FROM)              \
     static ::ssam::Register2D SSAM_CAT(reg2df_, __COUNTER__)(::ssam::Instance2D{                                 \
