@@ -24,21 +24,21 @@ hipError_t allow_lds(const void* kernel, int index)
     return e;
 }
 
-struct TilePlan {
-    const Tile2DKernel* k = nullptr;
-    int waves = 0, sweeps = 0, tiles_x = 0, tiles_y = 0;
-};
-
 int tiles_along(int extent, int tile, int step) { return ceil_div(extent - tile, step) + 1; }
 
-// The plan of least expected time for all of max_sweeps sweeps.  The expectation is fitted to 3400 measured launches (256^2 ..
+constexpr int kTileDepth = 32;       // sweeps of a launch, at most: beyond, the halo is the tile
+constexpr int kTileHorizon = 64;     // with more sweeps to do, the depth of least time per sweep, whatever their number
+
+// The plan of least expected time for the sweeps that remain.  The expectation is fitted to 3400 measured launches (256^2 ..
 // 4096^2, both types, stars of radius 1, 2, 4, 6, boxes of radius 1, 2, 4, one to sixteen sweeps; 12 % off in the quadratic mean, and
 // the plan it picks 1.5 % slower than the best in the mean, 22 % at worst).  A launch costs 3.4 us and never less than 5; a sweep
 // of a compute unit's blocks their instructions, four cycles each, or 0.16 us of latency, whichever dominates; a block's loads and
 // stores 0.033 us per wave and four-byte column.
-TilePlan plan_tiles(int W, int H, int R, bool star, int elem, const Tile2DKernel* list, int max_sweeps)
+// Depths are tried, not numbers of launches, so that planning takes no longer the more sweeps remain (1023x1025 fp32 star r1, ten
+// thousand left: 716 us by launches, 6 by depths; 5000 sweeps 18.6 ms and 5.1, of which the launches take 5).
+Tile2DPlan plan_tiles(int W, int H, int R, bool star, int elem, const Tile2DKernel* list, int remaining)
 {
-    TilePlan best;
+    Tile2DPlan best;
     double best_us = 1e30;
     const int taps = star ? 4 * R + 1 : (2 * R + 1) * (2 * R + 1), pub = 2 * R < kTileRows ? 2 * R : kTileRows;
     for (const Tile2DKernel* k = list; k->kernel; ++k) {
@@ -50,16 +50,16 @@ TilePlan plan_tiles(int W, int H, int R, bool star, int elem, const Tile2DKernel
             if (H < TH) continue;
             const int fit = min(2 * kTileWaves / waves, (160 << 10) / (2 * waves * pub * kWave * k->V * elem));   // blocks a unit holds at once
             double last = 1e30;
-            for (int launches = 1; launches <= max_sweeps; ++launches) {
-                const int sweeps = ceil_div(max_sweeps, launches);
+            for (int depth = min(min(remaining, kTileDepth), (min(TW, TH) - 1) / (2 * R)); depth > 0; --depth) {
+                const int launches = ceil_div(remaining, depth), sweeps = remaining > kTileHorizon ? depth : ceil_div(remaining, launches);
+                if (sweeps < depth) continue;                     // as many launches as with that depth
                 const int step_x = TW - 2 * sweeps * R, step_y = TH - 2 * sweeps * R;
-                if (step_x < 1 || step_y < 1) continue;
                 const int tx = tiles_along(W, TW, step_x), ty = tiles_along(H, TH, step_y);
                 if ((long)tx * ty > 1L << 20) continue;
                 const int share = ceil_div(tx * ty, kCUs);        // blocks of the busiest unit
                 const double issue = share * waves * work / 2200, latency = 0.16 * ceil_div(share, fit < 1 ? 1 : fit);
                 const double one = 3.4 + sweeps * std::sqrt(issue * issue + latency * latency) + 0.033 * share * waves * k->V * (elem / 4);
-                const double us = launches * (one > 5.0 ? one : 5.0);
+                const double us = (one > 5.0 ? one : 5.0) * (remaining > kTileHorizon ? 1.0 / sweeps : launches);
                 if (us < best_us) {
                     best_us = us;
                     best.k = k;
@@ -96,7 +96,7 @@ long most_points(bool f32, bool star, int R)
 }
 
 template <typename T, class Mask>
-hipError_t launch_tile(const Problem2D& pr, const TilePlan& plan, size_t lds)
+hipError_t launch_tile(const Problem2D& pr, const Tile2DPlan& plan, size_t lds)
 {
     ArgsTile2D<T, Mask::kNW> a;
     a.in = static_cast<const T*>(pr.in);
@@ -117,7 +117,7 @@ hipError_t launch_tile(const Problem2D& pr, const TilePlan& plan, size_t lds)
 }
 
 template <typename T, int BUDGET>
-hipError_t launch_tile(const Problem2D& pr, const TilePlan& plan, size_t lds)
+hipError_t launch_tile(const Problem2D& pr, const Tile2DPlan& plan, size_t lds)
 {
     switch (pr.ax) {
 #define SSAM_R(R) case R: return launch_tile<T, TapMask<2 * R + 1, 2 * R + 1, R, R, BUDGET>>(pr, plan, lds);
@@ -129,16 +129,18 @@ hipError_t launch_tile(const Problem2D& pr, const TilePlan& plan, size_t lds)
 
 }  // namespace
 
-int launch2d_tile(const Problem2D& pr, bool star, int max_sweeps, Geometry* geo, bool dry_run, hipError_t* err)
+int launch2d_tile(const Problem2D& pr, bool star, int remaining, Tile2DPlan* kept, Geometry* geo, bool dry_run, hipError_t* err)
 {
     const bool f32 = pr.dtype == SSAM_F32;
-    if (pr.M != pr.N || pr.ax != pr.ay || pr.M != 2 * pr.ax + 1 || max_sweeps < 2) return 0;
+    if (pr.M != pr.N || pr.ax != pr.ay || pr.M != 2 * pr.ax + 1 || remaining < 2) return 0;
     const Tile2DKernel* list = star ? (f32 ? tile2d_kernels<float, true>(pr.ax) : tile2d_kernels<double, true>(pr.ax))
                                     : (f32 ? tile2d_kernels<float, false>(pr.ax) : tile2d_kernels<double, false>(pr.ax));
     if (!list || (long)pr.W * pr.H > most_points(f32, star, pr.ax)) return 0;
     const int elem = f32 ? 4 : 8, R = pr.ax;
-    const TilePlan plan = plan_tiles(pr.W, pr.H, R, star, elem, list, max_sweeps);
+    const bool far = remaining > kTileHorizon;
+    const Tile2DPlan plan = far && kept && kept->k ? *kept : plan_tiles(pr.W, pr.H, R, star, elem, list, remaining);
     if (!plan.k) return 0;
+    if (far && kept) *kept = plan;
     const size_t row = (size_t)kWave * plan.k->V * elem;
     const size_t lds = (2 * plan.waves * (size_t)(2 * R < kTileRows ? 2 * R : kTileRows) + 1) * row;
     if (geo) {

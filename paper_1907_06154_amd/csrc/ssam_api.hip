@@ -390,9 +390,9 @@ int fused_depth(int remaining, int deepest, int keep_single, const Instance2D* c
 }
 
 // Several sweeps in one launch, where the shape has a fused instance (3D only when marching along z): in 3D the deepest compiled
-// one that does not exceed `max_sweeps` (the sweeps still to do) nor the "fuse_sweeps" cap, in 2D see fused_depth.  Returns the number of sweeps the launch performs, 0 when the
-// caller should run a single sweep instead.
-int run_fused(const Problem3D& p, int max_sweeps, Geometry* geo, bool dry, std::string* name, int* rc)
+// one that does not exceed `max_sweeps` (the sweeps still to do) nor the "fuse_sweeps" cap, in 2D see fused_depth.  Returns the
+// number of sweeps the launch performs, 0 when the caller should run a single sweep instead.  kept: see launch2d_tile.
+int run_fused(const Problem3D& p, int max_sweeps, Geometry* geo, bool dry, std::string* name, int* rc, Tile2DPlan* kept = nullptr)
 {
     const Tuning tu = current_tuning();
     if (tu.fuse_sweeps == 0 || tu.fuse_sweeps == 1 || tu.force_generic > 0) return 0;
@@ -410,7 +410,7 @@ int run_fused(const Problem3D& p, int max_sweeps, Geometry* geo, bool dry, std::
         const int budget = p.dtype == SSAM_F32 ? tap_budget<float>((const float*)p.c, q.M, q.N, 1, q.ax, q.ay, 0)
                                                : tap_budget<double>((const double*)p.c, q.M, q.N, 1, q.ax, q.ay, 0);
         hipError_t e = hipSuccess;
-        if (const int sweeps = launch2d_tile(q, budget <= 1, max_sweeps, geo, dry, &e)) {
+        if (const int sweeps = launch2d_tile(q, budget <= 1, max_sweeps, kept, geo, dry, &e)) {
             if (name)
                 *name = std::string(p.dtype == SSAM_F32 ? "float" : "double") + "_R" + std::to_string(p.rx) + (budget <= 1 ? "_b1" : "_b2") +
                         "_tile_fused" + std::to_string(sweeps);
@@ -716,11 +716,12 @@ int ssam_stencil_iterate(void* d_a, void* d_b, int W, int H, int D, const void* 
     void* src = d_a;
     void* dst = d_b;
     const bool cached = steps > 1 && 2 * (size_t)W * H * D * (dtype == SSAM_F32 ? 4 : 8) <= (size_t)192 << 20;   // of 256 MiB
+    Tile2DPlan kept;
     for (int t = 0; t < steps;) {
         Problem3D p{src, dst, W, H, D, h_coef, rx, ry, rz, boundary, dtype, (hipStream_t)hip_stream};
         p.reread = cached;
         int rc = SSAM_OK;
-        if (const int fused = run_fused(p, steps - t, nullptr, false, nullptr, &rc)) {
+        if (const int fused = run_fused(p, steps - t, nullptr, false, nullptr, &rc, &kept)) {
             if (rc) return rc;
             t += fused;
         } else {

@@ -219,8 +219,14 @@ constexpr int tile2d_index(int elem, int V, int R, int budget) { return (((elem 
     {reinterpret_cast<const void*>(&ssam2d_tile_kernel<T, V, kTileRows, TapMask<2 * (R) + 1, 2 * (R) + 1, R, R, BUDGET>>), V,           \
      tile2d_index(sizeof(T), V, R, BUDGET)}
 
-// Launches up to max_sweeps sweeps of a centred square stencil (a star or a box of radius pr.ax) on a grid small enough for it;
-// returns how many, 0: the grid is left to the other kernels.
-int launch2d_tile(const Problem2D& pr, bool star, int max_sweeps, Geometry* geo, bool dry_run, hipError_t* err);
+struct Tile2DPlan {
+    const Tile2DKernel* k = nullptr;
+    int waves = 0, sweeps = 0, tiles_x = 0, tiles_y = 0;
+};
+
+// Launches some of the remaining sweeps of a centred square stencil (a star or a box of radius pr.ax) on a grid small enough for
+// it; returns how many, 0: the grid is left to the other kernels.  kept (may be null): the plan of the launches of one iteration
+// while many sweeps remain, which does not depend on their number; empty before the first.
+int launch2d_tile(const Problem2D& pr, bool star, int remaining, Tile2DPlan* kept, Geometry* geo, bool dry_run, hipError_t* err);
 
 }  // namespace ssam

@@ -1,6 +1,7 @@
 """Small 2D grids, many sweeps a launch on tiles held in registers: grids of exactly one tile, one point more, and tiles moved back
 from the grid's end, in every vector width; buffers aligned to the element only; against the CPU oracle."""
 import re
+import time
 
 import numpy as np
 import pytest
@@ -36,6 +37,39 @@ def test_plans():
             done = int((re.search(r"_fused(\d+)$", name(shape, star, left)) or [0, 1])[1])
             assert 1 <= done <= left
             left -= done
+
+
+def test_planning_takes_no_longer_the_more_sweeps_remain():
+    """Long iterations: the plan is found among depths, and with many sweeps left it is the same whatever their number."""
+    import paper_1907_06154_amd as ssam
+    coef = coefficients("star", 1, np.float32)
+
+    def plan(shape, remaining):
+        best, text = float("inf"), ""
+        for _ in range(20):
+            t = time.perf_counter()
+            text = ssam.ssam_describe("iterate2d", shape, coef, "clamp", remaining=remaining)
+            best = min(best, time.perf_counter() - t)
+        return best, text
+
+    for shape in ((512, 512), (1023, 1025), (4096, 4096)):
+        short, long, longer = (plan(shape, n) for n in (24, 1000, 10 ** 6))
+        assert "_tile_" in short[1] and long[1] == longer[1]
+        assert longer[0] < 4 * short[0] + 5e-5, (shape, short[0], longer[0])     # 10^6 by numbers of launches: 40 ms and more
+
+
+@pytest.mark.gpu
+def test_many_sweeps():
+    """A plan kept for the launches of one iteration, and the plans of its rest."""
+    import paper_1907_06154_amd as ssam
+    for dtype, shape, steps in ((np.float32, (131, 449), 200), (np.float64, (70, 129), 131)):
+        coef = coefficients("star", 1, dtype)
+        fld = wl.uniform_field(shape, -1.0, 1.0, 77, dtype)
+        for boundary in ("zero", "clamp"):
+            print(f"many sweeps {np.dtype(dtype).name} {shape} {boundary} {steps}", flush=True)
+            a = torch.from_numpy(fld).cuda()
+            got = ssam.ssam_stencil_iterate(a, torch.empty_like(a), coef, steps, boundary)
+            assert_parity(got.cpu().numpy(), oracle.iterate(fld, coef, steps, boundary), coef, 1.0, f"{shape} {boundary} {steps}")
 
 
 @pytest.mark.gpu
