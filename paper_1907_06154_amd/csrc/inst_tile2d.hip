@@ -50,10 +50,14 @@ Tile2DPlan plan_tiles(int W, int H, int R, bool star, int elem, const Tile2DKern
             if (H < TH) continue;
             const int fit = min(2 * kTileWaves / waves, (160 << 10) / (2 * waves * pub * kWave * k->V * elem));   // blocks a unit holds at once
             double last = 1e30;
-            for (int depth = min(min(remaining, kTileDepth), (min(TW, TH) - 1) / (2 * R)); depth > 0; --depth) {
+            // an axis that one tile covers has no halo (16 rows, zero padding, us: fp32 star r3, three sweeps, 11 -> 5, fp64 star r4,
+            // seventeen or eighteen, 64 -> 17; blocks of 12 and 16 waves are better off with several tiles, up to 1.3 with 48 rows)
+            const bool all_x = W == TW, all_y = H == TH && waves <= 8;
+            const int most_x = all_x ? kTileDepth : (TW - 1) / (2 * R), most_y = all_y ? kTileDepth : (TH - 1) / (2 * R);
+            for (int depth = min(min(remaining, kTileDepth), min(most_x, most_y)); depth > 0; --depth) {
                 const int launches = ceil_div(remaining, depth), sweeps = remaining > kTileHorizon ? depth : ceil_div(remaining, launches);
                 if (sweeps < depth) continue;                     // as many launches as with that depth
-                const int step_x = TW - 2 * sweeps * R, step_y = TH - 2 * sweeps * R;
+                const int step_x = all_x ? TW : TW - 2 * sweeps * R, step_y = all_y ? TH : TH - 2 * sweeps * R;
                 const int tx = tiles_along(W, TW, step_x), ty = tiles_along(H, TH, step_y);
                 if ((long)tx * ty > 1L << 20) continue;
                 const int share = ceil_div(tx * ty, kCUs);        // blocks of the busiest unit
@@ -65,6 +69,8 @@ Tile2DPlan plan_tiles(int W, int H, int R, bool star, int elem, const Tile2DKern
                     best.k = k;
                     best.waves = waves;
                     best.sweeps = sweeps;
+                    best.step_x = step_x;
+                    best.step_y = step_y;
                     best.tiles_x = tx;
                     best.tiles_y = ty;
                 }
@@ -95,6 +101,20 @@ long most_points(bool f32, bool star, int R)
     return R == 2 ? 1100000 : R == 3 ? 1L << 22 : 160000;
 }
 
+// Whether a plan of less than all that remains a launch is kept.  Grids of less than two blocks' rows (17 .. 31) have tiles of 16
+// rows that are mostly halo, and with zero padding the marching kernels do three sweeps of stars up to radius 4, or four up to
+// radius 2, in one launch: ratio of the times, this kernel to those, star r3 three sweeps 1.13 .. 1.52 (six and more at most 1.0),
+// fp64 star r4 three 1.3 .. 1.44, six and nine 1.1 .. 1.2 (others at most 0.99; fp32 three 1.2, others 0.46 .. 0.99, and a rest of
+// three costs more there), r2 four 1.26; under the clamp rule 0.8 and less.  A sweep a launch of the box of radius 4 is 1.0 ..
+// 1.1 of its own kernel's; of that of radius 3, which happens from 3 million points on, 0.70 .. 1.17, 0.92 in the middle; of the stars
+// of radius 5 and 6 0.31 .. 0.98.
+bool keeps_plan(int sweeps, bool f32, bool star, int R, int H, bool zero, int remaining)
+{
+    if (!star) return sweeps > 1 || R != 4;
+    if (!zero || H >= 2 * 4 * kTileRows || sweeps >= remaining) return true;
+    return !(R == 2 ? remaining == 4 : R == 3 ? remaining == 3 : R == 4 && !f32 && remaining % 3 == 0);
+}
+
 template <typename T, class Mask>
 hipError_t launch_tile(const Problem2D& pr, const Tile2DPlan& plan, size_t lds)
 {
@@ -106,8 +126,8 @@ hipError_t launch_tile(const Problem2D& pr, const Tile2DPlan& plan, size_t lds)
     a.boundary = pr.boundary;
     a.sweeps = plan.sweeps;
     a.tiles_x = plan.tiles_x;
-    a.step_x = kWave * plan.k->V - 2 * plan.sweeps * Mask::kAX;
-    a.step_y = plan.waves * kTileRows - 2 * plan.sweeps * Mask::kAX;
+    a.step_x = plan.step_x;
+    a.step_y = plan.step_y;
     const T* w = static_cast<const T*>(pr.w);
     for (int n = 0; n < Mask::kN; ++n)
         for (int m = 0; m < Mask::kM; ++m)
@@ -139,7 +159,7 @@ int launch2d_tile(const Problem2D& pr, bool star, int remaining, Tile2DPlan* kep
     const int elem = f32 ? 4 : 8, R = pr.ax;
     const bool far = remaining > kTileHorizon;
     const Tile2DPlan plan = far && kept && kept->k ? *kept : plan_tiles(pr.W, pr.H, R, star, elem, list, remaining);
-    if (!plan.k) return 0;
+    if (!plan.k || !keeps_plan(plan.sweeps, f32, star, R, pr.H, pr.boundary == SSAM_BOUNDARY_ZERO, remaining)) return 0;
     if (far && kept) *kept = plan;
     const size_t row = (size_t)kWave * plan.k->V * elem;
     const size_t lds = (2 * plan.waves * (size_t)(2 * R < kTileRows ? 2 * R : kTileRows) + 1) * row;

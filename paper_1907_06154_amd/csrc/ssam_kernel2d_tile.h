@@ -29,7 +29,7 @@ struct ArgsTile2D {
     T* out;
     int W, H;
     int boundary, sweeps;
-    int tiles_x, step_x, step_y;   // tiles start step_x columns, step_y rows apart (the last ones end with the grid)
+    int tiles_x, step_x, step_y;   // tiles start step_x columns, step_y rows apart (the last ones end with the grid; a tile's extent: one covers that axis)
     T w[NWTS];
 };
 
@@ -221,7 +221,7 @@ constexpr int tile2d_index(int elem, int V, int R, int budget) { return (((elem 
 
 struct Tile2DPlan {
     const Tile2DKernel* k = nullptr;
-    int waves = 0, sweeps = 0, tiles_x = 0, tiles_y = 0;
+    int waves = 0, sweeps = 0, step_x = 0, step_y = 0, tiles_x = 0, tiles_y = 0;
 };
 
 // Launches some of the remaining sweeps of a centred square stencil (a star or a box of radius pr.ax) on a grid small enough for

@@ -58,6 +58,44 @@ def test_planning_takes_no_longer_the_more_sweeps_remain():
         assert longer[0] < 4 * short[0] + 5e-5, (shape, short[0], longer[0])     # 10^6 by numbers of launches: 40 ms and more
 
 
+def test_plans_of_thin_grids():
+    """An axis that one tile covers has no halo, so depth costs nothing there; with 17 to 31 rows tiles of 16 rows are mostly halo."""
+    import paper_1907_06154_amd as ssam
+
+    def depth(shape, coef, boundary, remaining):
+        name = ssam.ssam_describe("iterate2d", shape, coef, boundary, remaining=remaining).split()[0]
+        return "_tile_" in name, int((re.search(r"_fused(\d+)$", name) or [0, 1])[1])
+
+    for dtype in (np.float32, np.float64):
+        for r in (1, 3, 4, 6):
+            coef = coefficients("star", r, dtype)
+            for shape in ((16, 64), (16, 256), (16, 4096)):
+                for boundary in ("zero", "clamp"):
+                    tile, n = depth(shape, coef, boundary, 20)
+                    assert tile and n >= (20 if shape[1] <= 256 and r < 4 else 5), (shape, r, n)
+        for r in (3, 4) if dtype == np.float64 else (3,):
+            for H in (17, 24, 31):
+                assert depth((H, 2000), coefficients("star", r, dtype), "zero", 3) == (False, 3)
+    assert not depth((20, 2000), coefficients("box", 4, np.float64), "zero", 20)[0]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+def test_one_tile_along_an_axis(dtype):
+    import paper_1907_06154_amd as ssam
+    for kind, r in (("star", 1), ("star", 3), ("star", 6), ("box", 2)):
+        coef = coefficients(kind, r, dtype)
+        for shape in ((16, 64), (16, 500), (32, 256), (48, 300), (64, 128), (300, 64), (200, 128), (150, 256)):
+            fld = wl.uniform_field(shape, -1.0, 1.0, 710 + shape[1], dtype)
+            for boundary in ("zero", "clamp"):
+                for steps in (3, 17, 40):
+                    print(f"one tile {np.dtype(dtype).name} {kind} r{r} {shape} {boundary} steps {steps}", flush=True)
+                    a = torch.from_numpy(fld).cuda()
+                    got = ssam.ssam_stencil_iterate(a, torch.full_like(a, float("nan")), coef, steps, boundary)
+                    assert_parity(got.cpu().numpy(), oracle.iterate(fld, coef, steps, boundary), coef, 1.0,
+                                  f"{kind} r{r} {shape} {boundary} steps {steps}")
+
+
 @pytest.mark.gpu
 def test_many_sweeps():
     """A plan kept for the launches of one iteration, and the plans of its rest."""
