@@ -82,22 +82,35 @@ Tile2DPlan plan_tiles(int W, int H, int R, bool star, int elem, const Tile2DKern
     return best;
 }
 
-// The largest grid, in points, that a shape's sweeps run on here instead of in the marching kernels (several sweeps a launch, or
-// one).  The halo costs more the wider the stencil, and the marching kernels' latency less the larger the grid.  Ratio of the
-// times, this kernel to those, over 2, 4, 10 and 20 sweeps and both boundary rules:
-//   radius 1: 0.17 .. 0.8 up to 2048^2, 4096^2 0.58 .. 0.92, 8192^2 1.25 (fp64 box)
-//   fp32: box r2 0.29 .. 0.92 up to 2048x1500, 2048^2 0.81 .. 1.19; star r2 0.27 .. 0.76 up to 1500x1300, 2048x1500 0.89 .. 1.1;
-//     star r3 0.18 .. 0.94 up to 2048^2, 4096^2 1.02 .. 1.1; star r4 0.3 .. 0.79 up to 1500x1300, 2048x1500 0.99 .. 1.18; star r6
-//     0.2 .. 0.62 up to 1500x1300, 2048x1500 1.03.  Boxes from radius 3 on: single sweeps on the split kernel, with less error.
-//   fp64: box r2 0.49 .. 0.75 up to 1023x1025, 1500x1300 0.9 .. 1.04; box r3, which has single sweeps only, 0.45 .. 0.89 up to
-//     2048^2; box r4 0.8 .. 0.95 up to 300x512, 512^2 1.01 .. 1.07; star r2 0.42 .. 0.88 up to 1023x1025, 1500x1300 0.84 .. 1.07;
-//     star r3 0.36 .. 0.86 up to 2048x1500, 2048^2 0.79 .. 1.07; star r4 0.38 .. 0.76 up to 1023x1025, 1500x1300 0.86 .. 0.98,
-//     2048^2 1.07; star r6 0.28 .. 0.93 up to 1023x1025, 1500x1300 1.2
-long most_points(bool f32, bool star, int R)
+// The largest grid, in points, that the remaining sweeps run on here instead of in the marching kernels (several sweeps a launch, or
+// one).  The halo costs more the wider the stencil, and the marching kernels' latency less the larger the grid; and they are at their
+// best with as many sweeps as one launch of theirs does.  Both were timed on 16000 random grids of 64 .. 8192 rows and columns, 2 .. 24
+// sweeps; the lines are those with the least time lost against the better of both, 0 .. 2.8 % in the mean.  Ratio of the times, this
+// kernel to those (middle of a range of sizes; single grids are up to a fifth off, as tiles fit them):
+//   radius 1, five sweeps, seven and more: 0.23 .. 0.7 at every size; six 0.3 .. 0.96 but for the fp64 star with zero padding, 0.56 .. 0.88
+//     up to 3 million points and 0.96 .. 1.1 beyond.
+//   radius 1, two: 0.42 .. 0.85 up to 4 million points, where the others begin to pair them; beyond fp64 star 1.0 .. 1.15, fp64 box 1.03 ..
+//     1.08 with zero padding and 0.98 .. 1.05 under the clamp rule, fp32 star 0.84 .. 1.3, fp32 box 0.81 .. 1.1.
+//   radius 1, three: fp32 with zero padding 0.81 .. 1.0 up to 3.7 million, 0.95 .. 1.11 beyond, clamp star 0.76 .. 0.98 up to 5, 1.0 beyond,
+//     box 0.69 .. 0.99; fp64 with zero padding 0.92 .. 1.0 up to 1.1 million, 1.05 .. 1.33 beyond, clamp 0.74 .. 1.0 up to 2.5, 1.0 .. 1.1 beyond.
+//   radius 1, four, fp64 with zero padding: star 0.72 .. 0.99 up to 1.5 million, box 0.65 .. 0.94 up to 2; 1.02 .. 1.3 beyond; else 0.46 .. 1.0.
+//   fp32: box r2 0.3 .. 0.78 up to 3 million, star r2 0.28 .. 0.8 up to two, star r3 0.2 .. 1.0 up to four, star r4 .. r6 0.18 .. 0.8 up to
+//     two.  Boxes from radius 3 on: single sweeps on the split kernel, with less error.
+//   fp64: box r2 0.36 .. 0.8 and star r2 0.35 .. 0.95 up to 1.1 million, star r4 and r5 0.28 .. 0.89, star r6 0.31 .. 1.2; star r3 0.4 .. 1.0
+//     up to 3 million, but with zero padding three sweeps, six, nine .. 0.6 .. 1.1 up to two and 1.1 .. 1.29 beyond, and three under the
+//     clamp rule 1.1 from 2.5 on; box r3, which has single sweeps only, 0.5 .. 0.95 up to 1.2 million, 0.7 .. 1.1 up to two, 0.63 .. 1.05 up
+//     to four; box r4 0.61 .. 0.99 up to 160000 (five sweeps under the clamp rule 1.1).
+long most_points(bool f32, bool star, int R, bool zero, int remaining)
 {
-    if (R == 1) return 1L << 24;
-    if (f32) return star && R == 3 ? 1L << 22 : star ? 2000000 : 3200000;
-    if (star) return R == 3 ? 3100000 : 1100000;
+    constexpr long M = 1000000, most = 1L << 24;
+    if (R == 1 && remaining == 2) return star ? (f32 ? 5 * M : (1L << 22) - 1) : !f32 && zero ? (1L << 22) - 1 : most;
+    if (R == 1 && remaining == 3) return f32 ? (zero ? 3700000 : star ? 5 * M : most) : zero ? 1100000 : 2500000;
+    if (R == 1 && remaining == 4 && !f32 && zero) return star ? 1500000 : 2 * M;
+    if (R == 1 && remaining == 6 && !f32 && zero && star) return 3 * M;
+    if (R == 1) return most;
+    if (f32) return star && R == 3 ? 1L << 22 : star ? 2 * M : 3200000;
+    if (star && R == 3) return zero && remaining % 3 == 0 ? 2 * M : remaining == 3 ? 2500000 : 3100000;
+    if (star) return 1100000;
     return R == 2 ? 1100000 : R == 3 ? 1L << 22 : 160000;
 }
 
@@ -155,11 +168,12 @@ int launch2d_tile(const Problem2D& pr, bool star, int remaining, Tile2DPlan* kep
     if (pr.M != pr.N || pr.ax != pr.ay || pr.M != 2 * pr.ax + 1 || remaining < 2) return 0;
     const Tile2DKernel* list = star ? (f32 ? tile2d_kernels<float, true>(pr.ax) : tile2d_kernels<double, true>(pr.ax))
                                     : (f32 ? tile2d_kernels<float, false>(pr.ax) : tile2d_kernels<double, false>(pr.ax));
-    if (!list || (long)pr.W * pr.H > most_points(f32, star, pr.ax)) return 0;
     const int elem = f32 ? 4 : 8, R = pr.ax;
+    const bool zero = pr.boundary == SSAM_BOUNDARY_ZERO;
+    if (!list || (long)pr.W * pr.H > most_points(f32, star, R, zero, remaining)) return 0;
     const bool far = remaining > kTileHorizon;
     const Tile2DPlan plan = far && kept && kept->k ? *kept : plan_tiles(pr.W, pr.H, R, star, elem, list, remaining);
-    if (!plan.k || !keeps_plan(plan.sweeps, f32, star, R, pr.H, pr.boundary == SSAM_BOUNDARY_ZERO, remaining)) return 0;
+    if (!plan.k || !keeps_plan(plan.sweeps, f32, star, R, pr.H, zero, remaining)) return 0;
     if (far && kept) *kept = plan;
     const size_t row = (size_t)kWave * plan.k->V * elem;
     const size_t lds = (2 * plan.waves * (size_t)(2 * R < kTileRows ? 2 * R : kTileRows) + 1) * row;

@@ -79,6 +79,23 @@ def test_plans_of_thin_grids():
     assert not depth((20, 2000), coefficients("box", 4, np.float64), "zero", 20)[0]
 
 
+@pytest.mark.parametrize("dtype,kind,r,shape,boundary,remaining,tile", [
+    (np.float64, "star", 1, (3940, 980), "zero", 3, False), (np.float64, "star", 1, (980, 980), "zero", 3, True),
+    (np.float64, "box", 1, (1312, 3054), "zero", 3, False), (np.float64, "star", 1, (1500, 2000), "clamp", 3, False),
+    (np.float64, "star", 1, (1300, 1300), "zero", 4, False), (np.float64, "star", 1, (1300, 1300), "clamp", 4, True),
+    (np.float64, "star", 1, (2000, 2000), "zero", 6, False), (np.float64, "star", 1, (2000, 2000), "zero", 7, True),
+    (np.float64, "star", 1, (2048, 2048), "zero", 2, False), (np.float64, "star", 1, (2047, 2048), "zero", 2, True),
+    (np.float32, "star", 1, (2000, 2000), "zero", 3, False), (np.float32, "star", 1, (1900, 1900), "zero", 3, True),
+    (np.float64, "star", 3, (911, 2881), "zero", 3, False), (np.float64, "star", 3, (911, 2881), "zero", 9, False),
+    (np.float64, "star", 3, (911, 2881), "zero", 10, True), (np.float64, "star", 3, (911, 2881), "clamp", 3, False),
+])
+def test_few_sweeps_on_larger_grids(dtype, kind, r, shape, boundary, remaining, tile):
+    """Where the marching kernels do all that remains in launches of their best depth."""
+    import paper_1907_06154_amd as ssam
+    name = ssam.ssam_describe("iterate2d", shape, coefficients(kind, r, dtype), boundary, remaining=remaining).split()[0]
+    assert ("_tile_" in name) == tile
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("dtype", [np.float32, np.float64])
 def test_one_tile_along_an_axis(dtype):
