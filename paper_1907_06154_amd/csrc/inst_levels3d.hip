@@ -138,7 +138,7 @@ hipError_t launch_levels(const Problem3D& pr, const LevelsKernel& k, const Level
 
 }  // namespace
 
-int launch3d_levels(const Problem3D& pr, int budget, int remaining, Geometry* geo, bool dry_run, hipError_t* err)
+int launch3d_levels(const Problem3D& pr, int budget, int remaining, int deepest, Geometry* geo, bool dry_run, hipError_t* err)
 {
     const bool f32 = pr.dtype == SSAM_F32, clamp = pr.boundary == SSAM_BOUNDARY_CLAMP, star = budget <= 1;
     const int V16 = f32 ? 4 : 2, elem = f32 ? 4 : 8;
@@ -155,7 +155,7 @@ int launch3d_levels(const Problem3D& pr, int budget, int remaining, Geometry* ge
     // filled (255x256x256 fp32 box 30 us a sweep, here 41); off their best, on ragged rows or in the caches, they take a quarter more.
     const double others = others_us(pr, star);
     const bool leave = plan.V != 0 && points >= (4L << 20) && plan.us / 2 > (stream && pieces ? 1.0 : star ? 1e9 : 1.25) * others;
-    if (star && remaining >= 3 && (remaining != 4 || (leave && clamp))) {            // else four sweeps are two launches either way
+    if (star && remaining >= 3 && deepest >= 3 && (remaining != 4 || (leave && clamp))) {            // else four sweeps are two launches either way
         const LevelsPlan three = plan_levels(pr, 1, 3);
         if (remaining == 3 || leave || three.us / 3 < plan.us / 2) plan = three;
     }

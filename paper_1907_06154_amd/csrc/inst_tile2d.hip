@@ -36,7 +36,7 @@ constexpr int kTileHorizon = 64;     // with more sweeps to do, the depth of lea
 // stores 0.033 us per wave and four-byte column.
 // Depths are tried, not numbers of launches, so that planning takes no longer the more sweeps remain (1023x1025 fp32 star r1, ten
 // thousand left: 716 us by launches, 6 by depths; 5000 sweeps 18.6 ms and 5.1, of which the launches take 5).
-Tile2DPlan plan_tiles(int W, int H, int R, bool star, int elem, const Tile2DKernel* list, int remaining)
+Tile2DPlan plan_tiles(int W, int H, int R, bool star, int elem, const Tile2DKernel* list, int remaining, int deepest)
 {
     Tile2DPlan best;
     double best_us = 1e30;
@@ -54,7 +54,7 @@ Tile2DPlan plan_tiles(int W, int H, int R, bool star, int elem, const Tile2DKern
             // seventeen or eighteen, 64 -> 17; blocks of 12 and 16 waves are better off with several tiles, up to 1.3 with 48 rows)
             const bool all_x = W == TW, all_y = H == TH && waves <= 8;
             const int most_x = all_x ? kTileDepth : (TW - 1) / (2 * R), most_y = all_y ? kTileDepth : (TH - 1) / (2 * R);
-            for (int depth = min(min(remaining, kTileDepth), min(most_x, most_y)); depth > 0; --depth) {
+            for (int depth = min(min(deepest, kTileDepth), min(most_x, most_y)); depth > 0; --depth) {
                 const int launches = ceil_div(remaining, depth), sweeps = remaining > kTileHorizon ? depth : ceil_div(remaining, launches);
                 if (sweeps < depth) continue;                     // as many launches as with that depth
                 const int step_x = all_x ? TW : TW - 2 * sweeps * R, step_y = all_y ? TH : TH - 2 * sweeps * R;
@@ -162,7 +162,7 @@ hipError_t launch_tile(const Problem2D& pr, const Tile2DPlan& plan, size_t lds)
 
 }  // namespace
 
-int launch2d_tile(const Problem2D& pr, bool star, int remaining, Tile2DPlan* kept, Geometry* geo, bool dry_run, hipError_t* err)
+int launch2d_tile(const Problem2D& pr, bool star, int remaining, int deepest, Tile2DPlan* kept, Geometry* geo, bool dry_run, hipError_t* err)
 {
     const bool f32 = pr.dtype == SSAM_F32;
     if (pr.M != pr.N || pr.ax != pr.ay || pr.M != 2 * pr.ax + 1 || remaining < 2) return 0;
@@ -172,7 +172,7 @@ int launch2d_tile(const Problem2D& pr, bool star, int remaining, Tile2DPlan* kep
     const bool zero = pr.boundary == SSAM_BOUNDARY_ZERO;
     if (!list || (long)pr.W * pr.H > most_points(f32, star, R, zero, remaining)) return 0;
     const bool far = remaining > kTileHorizon;
-    const Tile2DPlan plan = far && kept && kept->k ? *kept : plan_tiles(pr.W, pr.H, R, star, elem, list, remaining);
+    const Tile2DPlan plan = far && kept && kept->k && kept->sweeps <= deepest ? *kept : plan_tiles(pr.W, pr.H, R, star, elem, list, remaining, deepest);
     if (!plan.k || !keeps_plan(plan.sweeps, f32, star, R, pr.H, zero, remaining)) return 0;
     if (far && kept) *kept = plan;
     const size_t row = (size_t)kWave * plan.k->V * elem;

@@ -390,13 +390,13 @@ int fused_depth(int remaining, int deepest, int keep_single, const Instance2D* c
 }
 
 // Several sweeps in one launch, where the shape has a fused instance (3D only when marching along z): in 3D the deepest compiled
-// one that does not exceed `max_sweeps` (the sweeps still to do) nor the "fuse_sweeps" cap, in 2D see fused_depth.  Returns the
+// one that does not exceed `remaining` (the sweeps still to do) nor the "fuse_sweeps" cap, in 2D see fused_depth.  Returns the
 // number of sweeps the launch performs, 0 when the caller should run a single sweep instead.  kept: see launch2d_tile.
-int run_fused(const Problem3D& p, int max_sweeps, Geometry* geo, bool dry, std::string* name, int* rc, Tile2DPlan* kept = nullptr)
+int run_fused(const Problem3D& p, int remaining, Geometry* geo, bool dry, std::string* name, int* rc, Tile2DPlan* kept = nullptr)
 {
     const Tuning tu = current_tuning();
     if (tu.fuse_sweeps == 0 || tu.fuse_sweeps == 1 || tu.force_generic > 0) return 0;
-    if (tu.fuse_sweeps > 1 && tu.fuse_sweeps < max_sweeps) max_sweeps = tu.fuse_sweeps;
+    const int cap = tu.fuse_sweeps > 1 && tu.fuse_sweeps < remaining ? tu.fuse_sweeps : remaining;     // sweeps of one launch
     const int v = tu.variant > 0 ? tu.variant : 0;
     const bool flat = p.D == 1 && p.rz == 0;
     if (!flat && tu.march_axis == 1) return 0;   // 3D: z march only
@@ -410,7 +410,7 @@ int run_fused(const Problem3D& p, int max_sweeps, Geometry* geo, bool dry, std::
         const int budget = p.dtype == SSAM_F32 ? tap_budget<float>((const float*)p.c, q.M, q.N, 1, q.ax, q.ay, 0)
                                                : tap_budget<double>((const double*)p.c, q.M, q.N, 1, q.ax, q.ay, 0);
         hipError_t e = hipSuccess;
-        if (const int sweeps = launch2d_tile(q, budget <= 1, max_sweeps, kept, geo, dry, &e)) {
+        if (const int sweeps = launch2d_tile(q, budget <= 1, remaining, cap, kept, geo, dry, &e)) {
             if (name)
                 *name = std::string(p.dtype == SSAM_F32 ? "float" : "double") + "_R" + std::to_string(p.rx) + (budget <= 1 ? "_b1" : "_b2") +
                         "_tile_fused" + std::to_string(sweeps);
@@ -421,14 +421,14 @@ int run_fused(const Problem3D& p, int max_sweeps, Geometry* geo, bool dry, std::
     if (!flat && p.rx == 1 && p.ry == 1 && p.rz == 1 && tu.planes_per_wave <= 0 && tu.valid_lanes <= 0 && tu.variant < 0) {     // sweeps as levels of one march (the overrides are the other kernels')
         const int budget = p.dtype == SSAM_F32 ? tap_budget<float>((const float*)p.c, 3, 3, 3, 1, 1, 1) : tap_budget<double>((const double*)p.c, 3, 3, 3, 1, 1, 1);
         hipError_t e = hipSuccess;
-        if (const int sweeps = launch3d_levels(p, budget, max_sweeps, geo, dry, &e)) {
+        if (const int sweeps = launch3d_levels(p, budget, remaining, cap, geo, dry, &e)) {
             if (name)
                 *name = std::string(p.dtype == SSAM_F32 ? "float" : "double") + "_r111_b" + std::to_string(budget < 1 ? 1 : budget) + "_levels_fused" + std::to_string(sweeps);
             *rc = status_of(e);
             return sweeps;
         }
     }
-    const int deepest = max_sweeps < kMaxFusedSweeps ? max_sweeps : kMaxFusedSweeps;
+    const int deepest = cap < kMaxFusedSweeps ? cap : kMaxFusedSweeps;
     if (flat) {
         const Instance2D* tight = p.dtype == SSAM_F32 ? pick2d<float>(q, true, 0, 0, true) : pick2d<double>(q, true, 0, 0, true);
         if (!tight) return 0;
@@ -443,7 +443,7 @@ int run_fused(const Problem3D& p, int max_sweeps, Geometry* geo, bool dry, std::
             }
         const bool star = tight->budget == 1;
         const int keep_single = p.dtype == SSAM_F32 ? (p.rx == 1 ? 4 : 0) : p.rx == 1 ? 6 : star && p.rx == 2 ? 4 : 0;
-        const int sweeps = fused_depth(max_sweeps, deepest, keep_single, by_depth);
+        const int sweeps = fused_depth(remaining, deepest, keep_single, by_depth);
         if (sweeps < 2) return 0;
         if (name) *name = by_depth[sweeps]->name;
         *rc = status_of(by_depth[sweeps]->launch(q, tu, geo, dry));

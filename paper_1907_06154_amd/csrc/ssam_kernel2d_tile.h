@@ -224,9 +224,9 @@ struct Tile2DPlan {
     int waves = 0, sweeps = 0, step_x = 0, step_y = 0, tiles_x = 0, tiles_y = 0;
 };
 
-// Launches some of the remaining sweeps of a centred square stencil (a star or a box of radius pr.ax) on a grid small enough for
-// it; returns how many, 0: the grid is left to the other kernels.  kept (may be null): the plan of the launches of one iteration
+// Launches some of the remaining sweeps, at most `deepest`, of a centred square stencil (a star or a box of radius pr.ax) on a grid
+// small enough for it; returns how many, 0: the grid is left to the other kernels.  kept (may be null): the plan of the launches of one iteration
 // while many sweeps remain, which does not depend on their number; empty before the first.
-int launch2d_tile(const Problem2D& pr, bool star, int remaining, Tile2DPlan* kept, Geometry* geo, bool dry_run, hipError_t* err);
+int launch2d_tile(const Problem2D& pr, bool star, int remaining, int deepest, Tile2DPlan* kept, Geometry* geo, bool dry_run, hipError_t* err);
 
 }  // namespace ssam

@@ -375,7 +375,8 @@ LevelsKernel levels_pick(int waves, int sweeps, bool clamp, bool stream)
                         : levels_pick<T, BUDGET, W16 / 2>(waves, sweeps, clamp, stream);                            \
     }
 
-// Launches two or three of the `remaining` sweeps of a radius-1 3D stencil; returns how many, 0: the grid is left to the other kernels.
-int launch3d_levels(const Problem3D& pr, int budget, int remaining, Geometry* geo, bool dry_run, hipError_t* err);
+// Launches two or three of the `remaining` sweeps of a radius-1 3D stencil, at most `deepest`; returns how many, 0: the grid is left to
+// the other kernels.
+int launch3d_levels(const Problem3D& pr, int budget, int remaining, int deepest, Geometry* geo, bool dry_run, hipError_t* err);
 
 }  // namespace ssam

@@ -43,6 +43,22 @@ def test_depths_take_no_more_launches_than_the_deepest_first(dtype, kind, r):
                 assert len(got) == count, (kind, r, shape, boundary, steps, got)
 
 
+@pytest.mark.parametrize("kind,r,dtype,depths", [("box", 2, np.float64, (2, 3, 4)), ("star", 1, np.float64, (2, 3, 4, 6, 8)),
+                                                 ("star", 3, np.float32, (2, 3, 4)), ("star", 4, np.float64, (2, 3))])
+def test_a_cap_limits_the_depth_and_not_the_sweeps_that_remain(kind, r, dtype, depths):
+    coef = coefficients(kind, r, dtype)
+    try:
+        for cap in range(2, 10):
+            ssam.ssam_set_tuning("fuse_sweeps", cap)
+            assert depth((8192, 8192), coef, "zero", 100) == max(d for d in depths if d <= cap), cap
+            assert depth((300, 400), coef, "zero", 100) <= cap                      # tiles
+            star = wl.seeded_coefficients(wl.mask_star(1, 1, 1), 1131, np.float64)
+            m = re.search(r"_levels_fused(\d+)$", ssam.ssam_describe("iterate3d", (200, 200, 200), star, "zero", remaining=100).split()[0])
+            assert int(m.group(1)) == min(cap, 3)
+    finally:
+        ssam.ssam_set_tuning("fuse_sweeps", -1)
+
+
 def check(shape, coef, boundary, steps, rows):
     fld = wl.uniform_field(shape, -1.0, 1.0, 1110 + shape[0], np.float64)
     print(f"depth {coef.shape} {shape} {boundary} rows {rows} steps {steps}", flush=True)
