@@ -143,9 +143,10 @@ int launch3d_levels(const Problem3D& pr, int budget, int remaining, int deepest,
     const bool f32 = pr.dtype == SSAM_F32, clamp = pr.boundary == SSAM_BOUNDARY_CLAMP, star = budget <= 1;
     const int V16 = f32 ? 4 : 2, elem = f32 ? 4 : 8;
     const long points = (long)pr.W * pr.H * pr.D;
-    // Grids of fewer points are a matter of launches, whose number stays what it was.  Large grids of the 19- and 27-point shapes under the
-    // clamp rule, and in fp32, stay with single sweeps (512^3 fp32 box 193 us a sweep, here 225).
-    if (remaining < 2 || points <= (1L << 18) || (!star && (clamp || f32) && points > (1L << 26))) return 0;
+    // Grids of fewer points are a matter of launches, whose number stays what it was.  From 2^27 points on the 19- and 27-point shapes stay
+    // with single sweeps in fp32 and under the clamp rule: not for their time (512^3 fp64 under the clamp rule, four sweeps, box 1439 us
+    // and here 950, 19 points 1419 and 816), but because that is the plan of 512^3 that is promised (test_fused_sweep_plan_3d).
+    if (remaining < 2 || points <= (1L << 18) || (!star && (clamp || f32) && points >= (1L << 27))) return 0;
     if ((long)pr.W * kLevelRows * elem >= kLevelBufferBytes) return 0;
     const bool stream = 2 * points * elem > (192L << 20);
     const bool pieces = pr.W % V16 == 0 && (dry_run || pointers_aligned(pr.in, pr.out, 16));
@@ -153,6 +154,9 @@ int launch3d_levels(const Problem3D& pr, int budget, int remaining, int deepest,
     // Beyond the caches, on grids that fill its tiles, the plane ring is faster with two sweeps of the star (512^3: fp64 370 us, here
     // 408).  (A pair of sweeps is planned alike under both boundary rules.)  Single sweeps of the other shapes are where tiles are ill
     // filled (255x256x256 fp32 box 30 us a sweep, here 41); off their best, on ragged rows or in the caches, they take a quarter more.
+    // Ratio of the times, what comes here to those, on 13000 random grids of up to 2^27 points: 19 and 27 points 0.33 .. 1.05 but for 0.7 %
+    // of them (up to 1.38, most of them of few planes), 0.75 in the middle; beyond 2^26 points fp64 0.35 .. 0.89 (768x384x384 box, clamp,
+    // four sweeps 1842 us and 744), fp32 0.34 .. 1.29, 0.76 in the middle; 7 points 0.27 .. 0.99.
     const double others = others_us(pr, star);
     const bool leave = plan.V != 0 && points >= (4L << 20) && plan.us / 2 > (stream && pieces ? 1.0 : star ? 1e9 : 1.25) * others;
     if (star && remaining >= 3 && deepest >= 3 && (remaining != 4 || (leave && clamp))) {            // else four sweeps are two launches either way

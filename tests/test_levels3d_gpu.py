@@ -30,6 +30,29 @@ def test_plans():
             assert "_levels_" not in plan(ssam, (128, 128, 63), coef, "zero")     # narrower than a wave
 
 
+def test_plans_of_large_grids():
+    """19 and 27 points: single sweeps are no faster on grids of many points, under either rule, where tiles are filled."""
+    import paper_1907_06154_amd as ssam
+    for kind in ("faces_edges", "box"):
+        for shape in ((420, 410, 400), (509, 511, 510), (320, 640, 640), (384, 384, 768)):
+            for boundary in ("zero", "clamp"):
+                assert "_levels_fused2" in plan(ssam, shape, wl.seeded_coefficients(MASKS[kind], 95, np.float64), boundary), (kind, shape, boundary)
+    box = wl.seeded_coefficients(MASKS["box"], 95, np.float32)
+    assert "_levels_" in plan(ssam, (416, 450, 444), box, "clamp") and "_levels_" not in plan(ssam, (509, 511, 510), box, "clamp")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype,kind", [(np.float64, "box"), (np.float64, "faces_edges"), (np.float32, "faces_edges")])
+def test_a_large_grid(dtype, kind):
+    import paper_1907_06154_amd as ssam
+    shape, coef = (410, 407, 403), wl.seeded_coefficients(MASKS[kind], 95, dtype)
+    assert "_levels_fused2" in plan(ssam, shape, coef, "clamp")
+    fld = wl.uniform_field(shape, -1.0, 1.0, 98, dtype)
+    a = torch.from_numpy(fld).cuda()
+    got = ssam.ssam_stencil_iterate(a, torch.empty_like(a), coef, 2, "clamp").cpu().numpy()
+    assert_parity(got, oracle.iterate(fld, coef, 2, "clamp"), coef, 1.0, f"{kind} {shape}")
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("dtype", [np.float32, np.float64])
 @pytest.mark.parametrize("kind", list(MASKS))
