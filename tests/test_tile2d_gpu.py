@@ -149,6 +149,73 @@ def test_matches_oracle(dtype, kind, r):
                 assert torch.isnan(guard).all()
 
 
+# grids of up to one and a half million points: blocks of twelve and sixteen waves, more than 64 KB of LDS
+TALL = [(1437, 191), (903, 913), (145, 105), (2995, 371), (271, 1511), (390, 263), (1792, 751), (2219, 593), (2901, 505)]
+ALL_SHAPES = [("star", r) for r in range(1, 7)] + [("box", r) for r in range(1, 5)]
+
+
+def tall_blocks(kind, r, dtype):
+    """(V, waves, boundary) of a launch -> the first of those grids, and the number of sweeps, that has it."""
+    import paper_1907_06154_amd as ssam
+    found = {}
+    for shape in TALL:
+        for steps, boundary in ((5, "zero"), (12, "clamp"), (5, "clamp"), (12, "zero")):
+            text = ssam.ssam_describe("iterate2d", shape, coefficients(kind, r, dtype), boundary, remaining=steps)
+            if "_tile_" in text:
+                V, tiles, blocks = (int(re.search(rf" {name}=(\d+)", text).group(1)) for name in ("V", "tiles", "blocks"))
+                found.setdefault((V, tiles // blocks, boundary), (shape, steps))
+    return found
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("kind,r", ALL_SHAPES)
+def test_tall_blocks_are_reached(dtype, kind, r):
+    found = tall_blocks(kind, r, dtype)
+    if kind == "box" and r > 2 and dtype == np.float32:      # single sweeps on the split kernel
+        assert not found
+        return
+    widths = [1] if (kind, r) == ("box", 4) else [1, 2] if dtype == np.float64 else [1, 2, 4]
+    assert set(found) >= {(V, waves, boundary) for V in widths for waves in (12, 16) for boundary in ("zero", "clamp")}
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("kind,r", ALL_SHAPES)
+def test_tall_blocks(dtype, kind, r):
+    import paper_1907_06154_amd as ssam
+    coef = coefficients(kind, r, dtype)
+    for (V, waves, boundary), (shape, steps) in tall_blocks(kind, r, dtype).items():
+        print(f"tall {np.dtype(dtype).name} {kind} r{r} {shape} {boundary} steps {steps} V {V} waves {waves}", flush=True)
+        fld = wl.uniform_field(shape, -1.0, 1.0, 750 + shape[1], dtype)
+        a = torch.from_numpy(fld).cuda()
+        got = ssam.ssam_stencil_iterate(a, torch.full_like(a, float("nan")), coef, steps, boundary)
+        assert_parity(got.cpu().numpy(), oracle.iterate(fld, coef, steps, boundary), coef, 1.0, f"{kind} r{r} {shape} {boundary} steps {steps}")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("kind,r", [("star", 1), ("star", 2), ("star", 4), ("star", 6), ("box", 1), ("box", 2)])
+@pytest.mark.parametrize("boundary", ["zero", "clamp"])
+def test_infinities_and_nan_stay_apart(dtype, kind, r, boundary):
+    """They reach the points the sweeps carry them to and no others, at the grid's edges, which the clamp rule repeats, and beside a
+    tile's rim, which every tile sees repeated."""
+    import paper_1907_06154_amd as ssam
+    coef, shape, steps = coefficients(kind, r, dtype), (150, 700), 6
+    assert "_tile_" in ssam.ssam_describe("iterate2d", shape, coef, boundary, remaining=steps)
+    ys, xs = np.mgrid[0:shape[0], 0:shape[1]]
+    for value in (np.inf, np.nan):
+        for at in ([(0, 0), (75, 350), (149, 699)], [(0, 300), (60, 0)], [(149, 128), (100, 699), (33, 64)]):
+            fld = np.zeros(shape, dtype=dtype)
+            near = np.zeros(shape, dtype=bool)
+            for y, x in at:
+                fld[y, x] = value
+                dy, dx = (-(-np.abs(d) // r) for d in (ys - y, xs - x))      # sweeps to cover the distance along each axis
+                near |= (dy + dx if kind == "star" else np.maximum(dy, dx)) <= steps
+            a = torch.from_numpy(fld).cuda()
+            got = ssam.ssam_stencil_iterate(a, torch.empty_like(a), coef, steps, boundary).cpu().numpy()
+            assert np.array_equal(~np.isfinite(got), near) and not got[~near].any(), (value, at)
+
+
 @pytest.mark.gpu
 def test_zero_padding_keeps_infinities_apart():
     """An infinity reaches the points the sweeps carry it to and no others, at the grid's edge and beside a tile's rim."""
