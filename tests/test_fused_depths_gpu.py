@@ -72,6 +72,38 @@ def check(shape, coef, boundary, steps, rows):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("kind,r", [("box", 1), ("star", 1), ("box", 2), ("star", 2), ("star", 3), ("star", 4), ("star", 5), ("star", 6)])
+def test_marching_kernels_on_small_grids(dtype, kind, r):
+    """The tile kernel takes these grids by itself; variant 0 names the marching kernels' own default: every depth, several tiles,
+    ragged tails, rows that are not whole vectors."""
+    coef = coefficients(kind, r, dtype)
+    for shape in ((33, 224), (37, 113), (37, 449), (70, 300), (131, 449), (150, 1000), (260, 96)):
+        fld = wl.uniform_field(shape, -1.0, 1.0, 1120 + shape[0], dtype)
+        for boundary in ("zero", "clamp"):
+            for steps in (2, 3, 4, 6, 7, 9):
+                want = oracle.iterate(fld, coef, steps, boundary)
+                for fuse in (-1, 2, 3):
+                    print(f"marching {np.dtype(dtype).name} {kind} r{r} {shape} {boundary} steps {steps} fuse {fuse}", flush=True)
+                    ssam.ssam_set_tuning("variant", 0)
+                    ssam.ssam_set_tuning("fuse_sweeps", fuse)
+                    try:
+                        left, depths = steps, []
+                        while left:
+                            name = ssam.ssam_describe("iterate2d", shape, coef, boundary, remaining=left).split()[0]
+                            depths.append(int((re.search(r"_fused(\d+)$", name) or [0, 1])[1]))
+                            assert "_tile_" not in name
+                            left -= depths[-1]
+                        a = torch.from_numpy(fld).cuda()
+                        res = ssam.ssam_stencil_iterate(a, torch.full_like(a, float("nan")), coef, steps, boundary)
+                    finally:
+                        ssam.ssam_set_tuning("variant", -1)
+                        ssam.ssam_set_tuning("fuse_sweeps", -1)
+                    assert fuse < 0 and (steps == 2 or r > 4) or max(depths) > 1, (shape, boundary, steps, fuse, depths)
+                    assert_parity(res.cpu().numpy(), want, coef, 1.0, f"{kind} r{r} {shape} {boundary} steps {steps} fuse {fuse}")
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("shape", [(5, 9), (33, 112), (61, 257), (97, 450), (130, 301)])
 def test_eight_sweeps_two_rows_a_group(shape):
     """Tiles of a few rows, tails, rows that are not whole vectors, grids smaller than the halo."""
