@@ -84,9 +84,10 @@ Tile2DPlan plan_tiles(int W, int H, int R, bool star, int elem, const Tile2DKern
 
 // The largest grid, in points, that the remaining sweeps run on here instead of in the marching kernels (several sweeps a launch, or
 // one).  The halo costs more the wider the stencil, and the marching kernels' latency less the larger the grid; and they are at their
-// best with as many sweeps as one launch of theirs does.  Both were timed on 16000 random grids of 64 .. 8192 rows and columns, 2 .. 24
-// sweeps; the lines are those with the least time lost against the better of both, 0 .. 2.8 % in the mean.  Ratio of the times, this
-// kernel to those (middle of a range of sizes; single grids are up to a fifth off, as tiles fit them):
+// best with as many sweeps as one launch of theirs does, on rows of whole 16-byte pieces.  Both were timed on 16000 random grids of 64 ..
+// 8192 rows and columns, 2 .. 24 sweeps, and on 20000 of such rows; the lines are those with the least time lost against the better of
+// both, 0 .. 1.3 % in the mean.  Ratio of the times, this kernel to those (middle of a range of sizes; single grids are up to a fifth off,
+// as tiles fit them), first rows of any length:
 //   radius 1, five sweeps, seven and more: 0.23 .. 0.7 at every size; six 0.3 .. 0.96 but for the fp64 star with zero padding, 0.56 .. 0.88
 //     up to 3 million points and 0.96 .. 1.1 beyond.
 //   radius 1, two: 0.42 .. 0.85 up to 4 million points, where the others begin to pair them; beyond fp64 star 1.0 .. 1.15, fp64 box 1.03 ..
@@ -98,19 +99,34 @@ Tile2DPlan plan_tiles(int W, int H, int R, bool star, int elem, const Tile2DKern
 //     two.  Boxes from radius 3 on: single sweeps on the split kernel, with less error.
 //   fp64: box r2 0.36 .. 0.8 and star r2 0.35 .. 0.95 up to 1.1 million, star r4 and r5 0.28 .. 0.89, star r6 0.31 .. 1.2; star r3 0.4 .. 1.0
 //     up to 3 million, but with zero padding three sweeps, six, nine .. 0.6 .. 1.1 up to two and 1.1 .. 1.29 beyond, and three under the
-//     clamp rule 1.1 from 2.5 on; box r3, which has single sweeps only, 0.5 .. 0.95 up to 1.2 million, 0.7 .. 1.1 up to two, 0.63 .. 1.05 up
-//     to four; box r4 0.61 .. 0.99 up to 160000 (five sweeps under the clamp rule 1.1).
-long most_points(bool f32, bool star, int R, bool zero, int remaining)
+//     clamp rule 1.1 from 2.5 on; box r3, which has single sweeps only, see single_box3_us; box r4 0.61 .. 0.99 up to 160000 (five sweeps
+//     under the clamp rule 1.1).
+// On rows of whole pieces (the range, and its middle, beyond the line):
+//   two sweeps: from 4.2 million on fp32 with zero padding star 1.12 .. 1.52 (1.22), box 1.01 .. 1.61 (1.20), clamp star 0.90 .. 1.26 (0.98),
+//     fp64 box clamp 0.90 .. 1.27 (1.04); from 5.1 on fp32 box clamp 0.90 .. 1.32 (1.06).
+//   three: fp32 with zero padding star from 0.3 million on 0.78 .. 1.44 (1.02), box from 2.5 on 0.84 .. 1.31 (1.11), clamp star from 4.3 on
+//     0.88 .. 1.27 (1.05), box from 4.6 on 0.78 .. 1.14 (1.02); fp64 clamp from 2.2 on 0.96 .. 1.21 (1.04).
+//   four: fp32 with zero padding star from 3.4 million on 0.91 .. 1.30 (1.12), box from 4.7 on 0.75 .. 1.20 (1.02).
+//   six and eight, fp64 box with zero padding: from 10 million on 1.02 .. 1.10 (1.05), from 8 on 0.95 .. 1.31 (1.03).
+//   fp64 star r3 with zero padding, three, six, nine ..: from 1.4 million on 1.0 .. 1.12 (1.09); star r6 from one million on 0.7 .. 1.18 (1.08).
+long most_points(bool f32, bool star, int R, bool zero, bool pieces, int remaining)
 {
-    constexpr long M = 1000000, most = 1L << 24;
-    if (R == 1 && remaining == 2) return star ? (f32 ? 5 * M : (1L << 22) - 1) : !f32 && zero ? (1L << 22) - 1 : most;
+    constexpr long M = 1000000, most = 1L << 24, pairs = (1L << 22) - 1;      // pairs: where the marching kernels begin to pair sweeps
+    if (pieces && R == 1) {
+        if (remaining == 2) return f32 && !star && !zero ? 5100000 : pairs;
+        if (remaining == 3 && f32) return zero ? (star ? 300000 : 2500000) : star ? 4300000 : 4600000;
+        if (remaining == 3 && !zero) return 2200000;
+        if (remaining == 4 && f32 && zero) return star ? 3400000 : 4700000;
+        if (!f32 && zero && !star && (remaining == 6 || remaining == 8)) return remaining == 6 ? 10 * M : 8 * M;
+    }
+    if (R == 1 && remaining == 2) return star ? (f32 ? 5 * M : pairs) : !f32 && zero ? pairs : most;
     if (R == 1 && remaining == 3) return f32 ? (zero ? 3700000 : star ? 5 * M : most) : zero ? 1100000 : 2500000;
     if (R == 1 && remaining == 4 && !f32 && zero) return star ? 1500000 : 2 * M;
     if (R == 1 && remaining == 6 && !f32 && zero && star) return 3 * M;
     if (R == 1) return most;
     if (f32) return star && R == 3 ? 1L << 22 : star ? 2 * M : 3200000;
-    if (star && R == 3) return zero && remaining % 3 == 0 ? 2 * M : remaining == 3 ? 2500000 : 3100000;
-    if (star) return 1100000;
+    if (star && R == 3) return zero && remaining % 3 == 0 ? (pieces ? 1400000 : 2 * M) : remaining == 3 ? 2500000 : 3100000;
+    if (star) return R == 6 && pieces ? M : 1100000;
     return R == 2 ? 1100000 : R == 3 ? 1L << 22 : 160000;
 }
 
@@ -170,7 +186,7 @@ int launch2d_tile(const Problem2D& pr, bool star, int remaining, int deepest, Ti
                                     : (f32 ? tile2d_kernels<float, false>(pr.ax) : tile2d_kernels<double, false>(pr.ax));
     const int elem = f32 ? 4 : 8, R = pr.ax;
     const bool zero = pr.boundary == SSAM_BOUNDARY_ZERO;
-    if (!list || (long)pr.W * pr.H > most_points(f32, star, R, zero, remaining)) return 0;
+    if (!list || (long)pr.W * pr.H > most_points(f32, star, R, zero, pr.W % (16 / elem) == 0, remaining)) return 0;
     const bool far = remaining > kTileHorizon;
     const Tile2DPlan plan = far && kept && kept->k && kept->sweeps <= deepest ? *kept : plan_tiles(pr.W, pr.H, R, star, elem, list, remaining, deepest);
     if (!plan.k || !keeps_plan(plan.sweeps, f32, star, R, pr.H, zero, remaining)) return 0;
