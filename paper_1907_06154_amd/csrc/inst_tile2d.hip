@@ -66,6 +66,7 @@ Tile2DPlan plan_tiles(int W, int H, int R, bool star, int elem, const Tile2DKern
                 const double us = (one > 5.0 ? one : 5.0) * (remaining > kTileHorizon ? 1.0 / sweeps : launches);
                 if (us < best_us) {
                     best_us = us;
+                    best.us = us / (remaining > kTileHorizon ? 1 : remaining);
                     best.k = k;
                     best.waves = waves;
                     best.sweeps = sweeps;
@@ -130,6 +131,17 @@ long most_points(bool f32, bool star, int R, bool zero, bool pieces, int remaini
     return R == 2 ? 1100000 : R == 3 ? 1L << 22 : 160000;
 }
 
+// The expected time of a sweep here up to which the fp64 box of radius 3 stays, whose other kernel does single sweeps: what those take,
+// less what the expectation of a plan falls short of the time by (0.16 in the mean).  Their time goes up in steps, as waves of 120 columns
+// and 8, 16 or 24 rows fill the chip: 6.0 .. 7.5 us a sweep up to 1024 waves of 8 rows (rows of odd length a tenth more), 8.7 .. 10 up to
+// 2048, 12.5 .. 20 with 16 rows, 23 with 24.  On 2900 grids of up to 4.2 million points 0.1 % of the time is lost against the better of
+// both; without this 0.6 %, and up to 1.30 of the time on grids of 1.4 to 2 million points (5810x289, nine sweeps, 81 us and 105).
+double single_box3_us(int W, int H)
+{
+    const long waves = (long)ceil_div(W, 120) * ceil_div(H, 8);
+    return waves <= 1024 ? 1e30 : waves <= 2048 ? 8.2 : waves <= 4096 ? 15.5 : 1e30;
+}
+
 // Whether a plan of less than all that remains a launch is kept.  Grids of less than two blocks' rows (17 .. 31) have tiles of 16
 // rows that are mostly halo, and with zero padding the marching kernels do three sweeps of stars up to radius 4, or four up to
 // radius 2, in one launch: ratio of the times, this kernel to those, star r3 three sweeps 1.13 .. 1.52 (six and more at most 1.0),
@@ -190,6 +202,7 @@ int launch2d_tile(const Problem2D& pr, bool star, int remaining, int deepest, Ti
     const bool far = remaining > kTileHorizon;
     const Tile2DPlan plan = far && kept && kept->k && kept->sweeps <= deepest ? *kept : plan_tiles(pr.W, pr.H, R, star, elem, list, remaining, deepest);
     if (!plan.k || !keeps_plan(plan.sweeps, f32, star, R, pr.H, zero, remaining)) return 0;
+    if (!f32 && !star && R == 3 && plan.us > single_box3_us(pr.W, pr.H)) return 0;
     if (far && kept) *kept = plan;
     const size_t row = (size_t)kWave * plan.k->V * elem;
     const size_t lds = (2 * plan.waves * (size_t)(2 * R < kTileRows ? 2 * R : kTileRows) + 1) * row;

@@ -222,6 +222,7 @@ constexpr int tile2d_index(int elem, int V, int R, int budget) { return (((elem 
 struct Tile2DPlan {
     const Tile2DKernel* k = nullptr;
     int waves = 0, sweeps = 0, step_x = 0, step_y = 0, tiles_x = 0, tiles_y = 0;
+    double us = 0;                 // expected time of a sweep
 };
 
 // Launches some of the remaining sweeps, at most `deepest`, of a centred square stencil (a star or a box of radius pr.ax) on a grid

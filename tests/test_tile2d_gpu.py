@@ -104,6 +104,16 @@ def test_few_sweeps_on_larger_grids(dtype, kind, r, shape, boundary, remaining, 
     assert ("_tile_" in name) == tile
 
 
+@pytest.mark.parametrize("shape,remaining,tile", [((860, 1954), 3, False), ((289, 5810), 9, False), ((774, 2240), 4, False), ((1510, 1120), 8, False),
+                                                  ((900, 900), 4, True), ((1200, 1000), 4, True), ((1500, 1400), 4, True), ((2000, 2000), 3, True),
+                                                  ((1500, 1400), 200, True), ((774, 2240), 200, False)])
+def test_plans_of_the_fp64_box_of_radius_3(shape, remaining, tile):
+    """Single sweeps where their waves fill the chip once."""
+    import paper_1907_06154_amd as ssam
+    name = ssam.ssam_describe("iterate2d", shape, coefficients("box", 3, np.float64), "zero", remaining=remaining).split()[0]
+    assert ("_tile_" in name) == tile
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("dtype", [np.float32, np.float64])
 def test_one_tile_along_an_axis(dtype):
