@@ -362,8 +362,8 @@ const Instance3D* pick3d(const Problem3D& p, int want_variant, int sweeps = 1)
     return best;
 }
 
-// Sweeps of the next launch while `remaining` are to do: the smallest depth with which, the deepest that fits first, the rest
-// takes no more launches than with all depths.  A launch's time grows with its depth at least in proportion beyond the deepest
+// Sweeps of the next launch while `remaining` are to do: the smallest of the depths with which, the deepest that fits first, the rest
+// takes the fewest launches.  (Without the depth of two, on small grids, a smaller depth can take fewer: six as 3 + 3, not 4 + 1 + 1.)  A launch's time grows with its depth at least in proportion beyond the deepest
 // one that is bound by memory, so equal depths are the better split: 8192^2, us, deepest first and like this: nine sweeps of the fp64
 // box of radius 1 459 -> 436 (8 + 1, 6 + 3), eighteen under the clamp rule 925 -> 759; eight of the fp32 box 264 -> 222 (6 + 2, 4 + 4);
 // five of the fp64 box of radius 2 550 -> 501 (4 + 1, 3 + 2), of the fp32 star of radius 3 on 2048x2176 41 -> 32.
@@ -383,10 +383,10 @@ int fused_depth(int remaining, int deepest, int keep_single, const Instance2D* c
         }
         return count;
     };
-    const int fewest = launches(deepest);
-    for (int d = 2; d < deepest; ++d)
-        if (by_depth[d] && launches(d) == fewest) return d;
-    return deepest;
+    int best = deepest, fewest = launches(deepest);
+    for (int d = deepest - 1; d > 1; --d)
+        if (by_depth[d] && launches(d) <= fewest) best = d, fewest = launches(d);
+    return best;
 }
 
 // Several sweeps in one launch, where the shape has a fused instance (3D only when marching along z): in 3D the deepest compiled

@@ -43,6 +43,22 @@ def test_depths_take_no_more_launches_than_the_deepest_first(dtype, kind, r):
                 assert len(got) == count, (kind, r, shape, boundary, steps, got)
 
 
+@pytest.mark.parametrize("kind,r,dtype", [("box", 2, np.float64), ("star", 2, np.float32), ("star", 3, np.float32), ("box", 2, np.float32)])
+def test_depths_without_pairs(kind, r, dtype):
+    """Below 2^22 points pairs of sweeps have no launch of their own: the fewest launches are not always those of the deepest first."""
+    coef = coefficients(kind, r, dtype)
+    ssam.ssam_set_tuning("variant", 0)             # the marching kernels
+    try:
+        for steps, want in ((5, [4, 1]), (6, [3, 3]), (9, [3, 3, 3]), (10, [3, 4, 3]), (13, [4, 3, 3, 3])):
+            got, t = [], 0
+            while t < steps:
+                got.append(depth((1500, 2500), coef, "zero", steps - t))
+                t += got[-1]
+            assert got == want, (steps, got)
+    finally:
+        ssam.ssam_set_tuning("variant", -1)
+
+
 @pytest.mark.parametrize("kind,r,dtype,depths", [("box", 2, np.float64, (2, 3, 4)), ("star", 1, np.float64, (2, 3, 4, 6, 8)),
                                                  ("star", 3, np.float32, (2, 3, 4)), ("star", 4, np.float64, (2, 3))])
 def test_a_cap_limits_the_depth_and_not_the_sweeps_that_remain(kind, r, dtype, depths):
