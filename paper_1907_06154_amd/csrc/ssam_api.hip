@@ -369,7 +369,8 @@ const Instance3D* pick3d(const Problem3D& p, int want_variant, int sweeps = 1)
 // five of the fp64 box of radius 2 550 -> 501 (4 + 1, 3 + 2), of the fp32 star of radius 3 on 2048x2176 41 -> 32.
 // keep_single: up to this depth a launch is bound by memory and one sweep left over is cheaper than a share of it (five sweeps of the
 // fp64 star of radius 1 on 8192^2: 395 as 4 + 1, 411 as 3 + 2; seven 400 as 6 + 1, 420 as 4 + 3;
-// nine of the star of radius 2 under the clamp rule 661 as 4 + 4 + 1, 687 as 3 + 3 + 3).
+// nine of the star of radius 2 under the clamp rule 661 as 4 + 4 + 1, 687 as 3 + 3 + 3; seven of the fp32 star of radius 1 with zero
+// padding on 3239x7168 84 as 6 + 1, 92 as 4 + 3).
 int fused_depth(int remaining, int deepest, int keep_single, const Instance2D* const* by_depth)
 {
     while (deepest >= 2 && !by_depth[deepest]) --deepest;
@@ -442,7 +443,7 @@ int run_fused(const Problem3D& p, int remaining, Geometry* geo, bool dry, std::s
                 if ((long)p.W * p.H >= 1000000L * (p.boundary == SSAM_BOUNDARY_CLAMP ? inst->clamp_from : inst->zero_from)) by_depth[sweeps] = inst;
             }
         const bool star = tight->budget == 1;
-        const int keep_single = p.dtype == SSAM_F32 ? (p.rx == 1 ? 4 : 0) : p.rx == 1 ? 6 : star && p.rx == 2 ? 4 : 0;
+        const int keep_single = p.dtype == SSAM_F32 ? (p.rx != 1 ? 0 : star && p.boundary == SSAM_BOUNDARY_ZERO ? 6 : 4) : p.rx == 1 ? 6 : star && p.rx == 2 ? 4 : 0;
         const int sweeps = fused_depth(remaining, deepest, keep_single, by_depth);
         if (sweeps < 2) return 0;
         if (name) *name = by_depth[sweeps]->name;

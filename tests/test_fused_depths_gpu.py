@@ -43,6 +43,17 @@ def test_depths_take_no_more_launches_than_the_deepest_first(dtype, kind, r):
                 assert len(got) == count, (kind, r, shape, boundary, steps, got)
 
 
+@pytest.mark.parametrize("kind,r,dtype,boundary,steps,want", [("star", 1, np.float32, "zero", 7, [6, 1]), ("star", 1, np.float32, "zero", 13, [6, 6, 1]),
+                                                               ("star", 1, np.float32, "clamp", 7, [4, 3]), ("star", 1, np.float64, "zero", 7, [6, 1]),
+                                                               ("star", 2, np.float64, "clamp", 9, [4, 4, 1])])
+def test_a_single_sweep_left_over(kind, r, dtype, boundary, steps, want):
+    """Where launches are bound by memory one sweep left over is cheaper than a share of a launch."""
+    coef, got = coefficients(kind, r, dtype), []
+    while sum(got) < steps:
+        got.append(depth((7168, 3239), coef, boundary, steps - sum(got)))
+    assert got == want
+
+
 @pytest.mark.parametrize("kind,r,dtype", [("box", 2, np.float64), ("star", 2, np.float32), ("star", 3, np.float32), ("box", 2, np.float32)])
 def test_depths_without_pairs(kind, r, dtype):
     """Below 2^22 points pairs of sweeps have no launch of their own: the fewest launches are not always those of the deepest first."""
