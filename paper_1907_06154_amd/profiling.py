@@ -149,44 +149,66 @@ def summarize(prefix: str, out_md: str, title: str, bench_args: str) -> None:
 def sweeps_of(kernel: str) -> int:
     if "ssam2d_fused" in kernel:
         return int(re.search(r">, (\d+), \d+>$", kernel).group(1))
+    if "ssam3d_levels" in kernel:
+        return int(kernel.split(", ")[5])
     return 2 if "ssam3d_fused" in kernel or "ssam3d_star2" in kernel else 1
 
 
+def timed_case(name: str):
+    """(grid points, sweeps of a pass) of a case of perf/cases.py."""
+    sys.path.insert(0, ROOT)
+    import perf.cases as cases
+    case = next(c for c in cases.listed() if c["name"] == name)
+    return case.get("n") or case["W"] * case["H"] * case.get("D", 1), case.get("steps", 1)
+
+
 def sq(dirs, out_md: str) -> None:
-    """VALU utilisation per kernel from one pass of 8 SQ counters per directory."""
+    """VALU utilisation per kernel from one pass of 8 SQ counters per directory.  sq_<case>: four passes of a case of
+    perf/cases.py; any other name: a bench.py run, its output beside it in <dir>.json."""
     ctrs = "SQ_WAVE_CYCLES SQ_BUSY_CYCLES SQ_INSTS_MFMA SQ_ACTIVE_INST_VALU SQ_VALU_MFMA_BUSY_CYCLES SQ_INSTS_VALU SQ_INSTS_LDS SQ_WAIT_ANY"
+    rocprof = f"    rocprofv3 --pmc {ctrs} --kernel-trace --output-format csv -d <dir> -o c -- "
     out = ["# VALU utilisation of the benchmark kernels (rocprofv3 SQ counters)\n",
            "One MI355X, one counter pass per configuration (8 SQ counters):\n",
-           f"    rocprofv3 --pmc {ctrs} --kernel-trace --output-format csv -d <dir> -o c -- python3 bench.py --workload <workload> "
-           "--no-cpu-baseline --steps 1 --warmup 0\n",
+           rocprof + "python3 bench.py --workload <workload> --no-cpu-baseline --steps 1 --warmup 0\n",
+           "(`sq_c4s` with `--fuse-sweeps 0`) and per case of perf/cases.py, four passes each:\n",
+           rocprof + "python3 -c \"import sys, torch, perf.cases as p; c = [x for x in p.listed() if x['name'] == sys.argv[1]][0]; "
+           "s = p.prepare(c, 1); [p.run(s) for _ in range(4)]; torch.cuda.synchronize()\" <case>\n",
            "Per dispatch, mean over the dispatches of a kernel.  `VALU instr / point / sweep` = SQ_INSTS_VALU x 64 lanes / (grid "
            "points x sweeps of the launch): what one output costs in lane-instructions, halo lanes and warm-up rows included.  "
-           "`VALU busy` = (SQ_ACTIVE_INST_VALU + SQ_INSTS_MFMA) x 4 cycles / (1024 SIMDs x dispatch duration x 2.4 GHz): the "
-           "fraction of all VALU issue slots of the chip the kernel used.  `MFMA share` = SQ_INSTS_MFMA / SQ_INSTS_VALU.  "
+           "`VALU issue` = SQ_INSTS_VALU x 4 cycles / (1024 SIMDs x dispatch duration x 2.4 GHz): the fraction of all issue slots of the "
+           "chip's vector units the kernel used, matrix instructions among them with one slot each; `without MFMA` the same for the others.  "
+           "`MFMA share` = SQ_INSTS_MFMA / SQ_INSTS_VALU.  "
            "`matrix busy` = SQ_VALU_MFMA_BUSY_CYCLES / (1024 SIMDs x dispatch duration x 2.4 GHz).  "
            "`waiting` = SQ_WAIT_ANY / SQ_WAVE_CYCLES: share of wave-cycles spent waiting on any counter (memory, LDS).  "
+           "`clock` = SQ_BUSY_CYCLES / 32 shader engines / duration: what the chip ran at, less the time an engine is idle at the end; as "
+           "shares of the cycles that there were, the three columns before `LDS` are 2.4 / clock times higher.  "
            "Durations are those of the counter run (serialised dispatches), a few per cent above the timed runs.\n",
-           "| run | kernel | dispatches | duration us | sweeps | VALU instr / point / sweep | VALU busy | MFMA share | matrix busy | "
-           "LDS instr / VALU instr | waiting |\n|---|---|---|---|---|---|---|---|---|---|---|"]
+           "| run | kernel | dispatches | duration us | sweeps | VALU instr / point / sweep | VALU issue | without MFMA | MFMA share | matrix busy | "
+           "LDS instr / VALU instr | waiting | clock GHz |\n|---|---|---|---|---|---|---|---|---|---|---|---|---|"]
     for d in dirs:
-        bench = json.load(open(d.rstrip("/") + ".json"))
-        pts = 1
-        for s in bench["config"]["grid"].split("x"):
-            pts *= int(s)
+        run = os.path.basename(d.rstrip("/"))
         agg = collections.OrderedDict()
         for k, c, us in counter_dispatches(d):
             if ours(k):
                 agg.setdefault(k, []).append((c, us))
+        case = run[3:] if len(run) > 12 else None
+        if case:
+            pts, steps = timed_case(case)
+        else:
+            pts = 1
+            for s in json.load(open(d.rstrip("/") + ".json"))["config"]["grid"].split("x"):
+                pts *= int(s)
         for k, rows in agg.items():
             m = {name: sum(r[0].get(name, 0.0) for r in rows) / len(rows) for name in ctrs.split()}
             us = sum(r[1] for r in rows) / len(rows)
-            sw = sweeps_of(k)
-            out.append(f"| {os.path.basename(d.rstrip('/'))} | `{k}` | {len(rows)} | {us:.1f} | {sw} | "
+            sw = steps * 4 // len(rows) if "ssam2d_tile" in k else sweeps_of(k)
+            slots = 1024 * us * 1e-6 * 2.4e9
+            out.append(f"| {run} | `{k}` | {len(rows)} | {us:.1f} | {sw} | "
                        f"{m['SQ_INSTS_VALU'] * 64 / pts / sw:.1f} | "
-                       f"{(m['SQ_ACTIVE_INST_VALU'] + m['SQ_INSTS_MFMA']) * 4 / (1024 * us * 1e-6 * 2.4e9):.2f} | "
+                       f"{m['SQ_INSTS_VALU'] * 4 / slots:.2f} | {(m['SQ_INSTS_VALU'] - m['SQ_INSTS_MFMA']) * 4 / slots:.2f} | "
                        f"{m['SQ_INSTS_MFMA'] / max(m['SQ_INSTS_VALU'], 1):.2f} | "
-                       f"{m['SQ_VALU_MFMA_BUSY_CYCLES'] / (1024 * us * 1e-6 * 2.4e9):.2f} | {m['SQ_INSTS_LDS'] / max(m['SQ_INSTS_VALU'], 1):.3f} | "
-                       f"{m['SQ_WAIT_ANY'] / max(m['SQ_WAVE_CYCLES'], 1):.2f} |")
+                       f"{m['SQ_VALU_MFMA_BUSY_CYCLES'] / slots:.2f} | {m['SQ_INSTS_LDS'] / max(m['SQ_INSTS_VALU'], 1):.3f} | "
+                       f"{m['SQ_WAIT_ANY'] / max(m['SQ_WAVE_CYCLES'], 1):.2f} | {m['SQ_BUSY_CYCLES'] / 32 / us / 1e3:.2f} |")
     open(out_md, "w").write("\n".join(out) + "\n")
     print("\n".join(out))
 
@@ -360,7 +382,7 @@ def scan_summary(prefix: str, out_md: str) -> None:
         per = {}
         copy = {}
         for kind, ctr in (("fetch", "FETCH_SIZE"), ("write", "WRITE_SIZE")):
-            out.append(f"    rocprofv3 --pmc {ctr} --kernel-trace --output-format csv -d {prefix}/{tag}_{kind} -o c -- {cmd}")
+            out.append(f"    rocprofv3 --pmc {ctr} --kernel-trace --output-format csv -d {prefix}/{tag}_{kind} -o c -- {cmd} --min-case-seconds 0.1")
             for k, c, _ in counter_dispatches(os.path.join(prefix, f"{tag}_{kind}")):
                 if is_copy(k):
                     copy.setdefault(kind, []).append(c[ctr])
