@@ -81,7 +81,8 @@ hipError_t launch2d_split(const Problem2D& pr, const Tuning& tu, Geometry* geo, 
     const int pieces = bands * groups + (tail ? (bands + 1) / 2 : 0);
 
     // Tile plan: 64 nx columns (nx = 1, 2, 3) by `rows` rows per wave, chosen by a model of the cycles a SIMD spends.  Its
-    // matrix and vector instructions add up (they were not seen to overlap): a step of four output rows issues 96 cycles
+    // matrix and vector instructions add up, which fits the times (20x20 on 8192^2: matrix pipe busy for 0.70 of the cycles, other
+    // vector instructions 0.14; 9x9 0.44 and 0.29, more of the waves' time in waits): a step of four output rows issues 96 cycles
     // of matrix instructions per table piece and 64 columns, staging four input rows about 60 + 46 (nx + 1) vector
     // instructions, the bands - 1 steps above a tile included, and every workgroup builds the table once.  Four waves per
     // SIMD, which one strip and a small table leave room for, hide more than two.  A partly filled last round costs what its

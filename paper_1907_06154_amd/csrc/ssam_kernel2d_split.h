@@ -24,7 +24,7 @@
 // a piece of eight rows by four columns, from two bands (TAIL: 13 pieces instead of 15 at 15x15, 5 instead of 6 at 9x9).
 // Measured on 8192^2 (fp32 matrix instructions -> this kernel, us): 9x9 165 -> 143, 11x11 226 -> 172, 15x15 361 -> 247, 20x20
 // 605 -> 319, 25x25 (direct kernel) 20400 -> 590; 1024^2: 9x9 15.7 -> 9.0, 20x20 123 -> 16.  In the 20x20 launch the matrix
-// pipe is busy for 0.54 of a 2.4 GHz clock's cycles, the vector unit for 0.38.
+// pipe is busy for 0.70 of the cycles (at the 1.86 GHz the chip then runs at), the other vector instructions take 0.14.
 #pragma once
 #include "ssam_device.h"
 #include "ssam_host.h"

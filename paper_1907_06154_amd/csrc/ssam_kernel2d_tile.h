@@ -12,6 +12,7 @@
 // and the halo takes it.)
 // Four rows per wave: with eight, 128 registers hold less beside them and the plans are coarser (0.9 .. 1.0 of the time for radius
 // 1 on 2048^2, more on all others).  Sixteen waves of 64 x {1, 2, 4} columns; one element per lane on the smallest grids.
+// (With four, the fp64 stars of radius 4, 5 and 6 spill 5, 9 and 28 registers at V = 2, the fp32 star of radius 6 two at V = 4.)
 // Measured, us, ten sweeps, from the marching kernels to this one: 1023x1025 fp32 star r1, clamp 29 -> 9.9, star r6 145 -> 56, box r2
 // 73 -> 28; 512^2 fp32 star r1 23 -> 6.0, star r6 96 -> 29, box r2 36 -> 14, fp64 star r1 20 -> 7.6, box r2 27 -> 18; 2048^2 star
 // r1 fp32 42 -> 22, fp64 58 -> 30.

@@ -8,7 +8,9 @@
 //     columns; rows go between waves through LDS (each wave's first and last), columns by lane shifts;
 //   - a level consumes the plane that the level before completed in the step before: one barrier a step serves all levels, and
 //     nothing waits for a plane of its own step.  A level holds three values a point (the plane, the one before or the sums
-//     begun): three levels of the star are 254 registers with eight points a lane, two of the other shapes 220;
+//     begun): three levels of the star are 256 registers with eight points a lane, two of the other shapes 220.  In fp64 three
+//     levels spill 18 (clamp 13) of them, in fp32 with eight waves six: 64-bit addresses of parts of pieces, loaded again only
+//     by waves that store such parts, on ragged rows;
 //   - tiles lie inside the grid, as in ssam_kernel2d_tile.h: no ragged tiles, and the boundary rule in x and y is what a wave sees
 //     beyond the tile.  In z the levels see zeros, or the first and last plane again;
 //   - loads and stores are buffer accesses with uniform plane bases; what a lane does not store is dropped by the bounds check.

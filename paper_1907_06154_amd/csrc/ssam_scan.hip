@@ -2,7 +2,7 @@
 // holds V consecutive elements, partial sums move between lanes with DPP shifts (a Kogge-Stone
 // network inside each row of 16 lanes, two row broadcasts across the rows), and a wave walks its
 // contiguous segment of the array with the running total carried in a register.  No LDS and no
-// barrier is used by the streaming kernels.
+// barrier is used where elements stream.
 //
 // Two schedules share the wave-level code.
 //
@@ -75,7 +75,10 @@ constexpr int chain_rounds(int dtype, bool aligned)
 }
 constexpr int kChainFan = 64;                                      // items summed per level = lanes
 constexpr long long kChainMaxSegments = 64LL * 64 * 64;            // three levels
-constexpr long long kChainMinBytes = 128LL << 20;                  // shorter arrays take the two launches (as fast or faster on arrays that the caches hold)
+// Shorter arrays take the two launches.  That is for arrays that the memory-side cache holds (two launches and one pass, us, fp32: 32 MiB
+// 19.6 and 19.8, 96 MiB 48.6 and 48.9, 128 MiB 65.0 and 57.9; fp64 35.0 and 39.3 at 64 MiB, 64.4 and 64.0 at 128); from memory, arrays
+// in turn, one pass is ahead from 24 to 48 MiB on (fp32 64 MiB 42.8 and 34.1, 120 MiB 74.4 and 55.9, fp64 74.5 and 62.8).
+constexpr long long kChainMinBytes = 128LL << 20;
 constexpr int kChainSpinLimit = 1 << 16;                           // polls before a wave gives up
 using Word = unsigned long long;
 // Workspace of the one-pass schedule, in 8-byte words: ticket counter, flag, SP, G, A.  The ticket counter (one atomic per workgroup) and
