@@ -184,6 +184,7 @@ int launch3d_levels(const Problem3D& pr, int budget, int remaining, int deepest,
     if (dry_run) return plan.sweeps;
     *err = f32 ? (star ? launch_levels<float, 1>(pr, k, plan, g) : budget == 2 ? launch_levels<float, 2>(pr, k, plan, g) : launch_levels<float, 3>(pr, k, plan, g))
                : (star ? launch_levels<double, 1>(pr, k, plan, g) : budget == 2 ? launch_levels<double, 2>(pr, k, plan, g) : launch_levels<double, 3>(pr, k, plan, g));
+    if (*err != hipSuccess) (void)hipGetLastError();     // returned here: not left for the next call to find
     return plan.sweeps;
 }
 

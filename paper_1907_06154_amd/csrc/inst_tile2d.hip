@@ -225,6 +225,7 @@ int launch2d_tile(const Problem2D& pr, bool star, int remaining, int deepest, Ti
     if (*err == hipSuccess)
         *err = star ? (f32 ? launch_tile<float, 1>(pr, plan, lds) : launch_tile<double, 1>(pr, plan, lds))
                     : (f32 ? launch_tile<float, 2>(pr, plan, lds) : launch_tile<double, 2>(pr, plan, lds));
+    if (*err != hipSuccess) (void)hipGetLastError();     // returned here: not left for the next call to find
     return plan.sweeps;
 }
 
