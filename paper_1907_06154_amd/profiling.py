@@ -8,6 +8,7 @@ profiles/measured_traffic.json, the HBM bytes per launch that bench.py reports a
     python -m paper_1907_06154_amd.profiling catalogue <single.json> <default.json> <out.md>
     python -m paper_1907_06154_amd.profiling sweep <default.json> <variant5.json> <out.md>
     python -m paper_1907_06154_amd.profiling scan <dir> <out.md>
+    python -m paper_1907_06154_amd.profiling against <other libssam.so> <commit it was built from> <out.md>
 
 `summarize` expects three rocprofv3 runs of the same bench.py command (the commands are written
 into the summary), each with its bench.py output saved beside it:
@@ -21,6 +22,9 @@ bench.py lists per case ("launch_names").
 
 `resources` compiles every translation unit for gfx950 with -Rpass-analysis=kernel-resource-usage
 (no GPU needed) and tabulates registers, LDS, scratch and waves per SIMD of every kernel.
+
+`against` loads another build of the library beside this one and times iterations, fp64 volume filters and scans with both in
+turn, on a GPU: a list of calls, then random ones.
 """
 from __future__ import annotations
 
@@ -411,6 +415,158 @@ def scan_summary(prefix: str, out_md: str) -> None:
     print("\n".join(out))
 
 
+# Iterations that `against` lists: grid, element type, shape, radius, boundary rule, sweeps.
+LISTED = """512x512x512 f64 star 1 zero 12; 512x512x512 f64 box 1 zero 10; 512x512x512 f32 star 1 zero 12; 400x448x330 f64 box 1 zero 10;
+400x448x330 f64 star 1 zero 10; 201x203x199 f64 star 1 zero 10; 201x203x199 f64 box 1 zero 4; 201x203x199 f32 star 1 zero 10;
+201x203x199 f32 box 1 zero 4; 256x256x256 f32 star 1 zero 10; 100x200x128 f64 box 1 zero 10; 128x200x100 f64 box 1 zero 10;
+64x205x64 f64 star 1 zero 10; 512x512x512 f64 star 1 clamp 10; 768x384x384 f64 box 1 clamp 4; 1023x1025 f32 star 1 clamp 10;
+1023x1025 f32 star 6 zero 10; 1023x1025 f32 box 2 zero 10; 512x512 f32 star 1 zero 10; 512x512 f32 star 6 zero 10; 512x512 f32 box 2 zero 10;
+512x512 f64 star 1 zero 10; 512x512 f64 box 2 zero 10; 2048x2048 f32 star 1 zero 10; 2048x2048 f64 star 1 zero 10;
+8192x8192 f64 star 1 zero 8; 8192x8192 f64 star 1 clamp 8; 8192x8192 f64 star 2 zero 6; 8192x8192 f64 star 3 zero 4;
+8192x8192 f64 star 5 zero 3; 8192x8192 f64 star 1 zero 24; 8192x8192 f64 star 2 zero 24; 8192x8192 f64 star 3 zero 24;
+8192x8192 f64 star 5 zero 24; 8192x8192 f64 box 1 zero 9; 8192x8192 f64 box 1 clamp 18; 8192x8192 f32 box 1 zero 8;
+8192x8192 f64 box 2 zero 5; 2048x2176 f32 star 3 zero 5; 8192x8192 f64 star 1 zero 5; 8192x8192 f64 star 1 zero 7;
+8192x8192 f64 star 2 clamp 9; 512x512 f32 star 1 clamp 5000; 1023x1025 f32 star 1 clamp 5000; 2048x2048 f32 star 1 clamp 5000;
+4096x4096 f32 star 1 clamp 5000"""
+FILTERS = "5x6x4 on 256x256x256, 7x7x7 on 53x256x202, 7x7x7 on 202x256x53, 9x9x9 on 256x256x256, 8x8x2 on 256x256x200, 8x8x2 on 200x256x256, " \
+          "4x4x4 on 256x256x256, 2x2x9 on 256x256x256"
+
+
+def against(other: str, commit: str, out_md: str, seconds: float = 40.0) -> None:
+    """The tables of `against`; a grid is named columns x rows (x planes)."""
+    import ctypes
+    import math
+    import random
+    import time
+
+    import numpy as np
+    import torch
+    sys.path.insert(0, ROOT)
+    import workloads as wl
+
+    from . import binding
+    here = binding.lib()
+    before = ctypes.CDLL(os.path.abspath(other))
+    for name in ("ssam_stencil_iterate", "ssam_conv3d", "ssam_scan"):
+        getattr(before, name).argtypes = getattr(here, name).argtypes
+    rng = random.Random(1)
+    stream = torch.cuda.current_stream().cuda_stream
+    buffers = {t: [torch.rand(1 << 27, device="cuda", dtype=t) for _ in range(2)] for t in (torch.float32, torch.float64)}
+    pointers = {c: [b.data_ptr() for b in buffers[t]] for c, t in ((0, torch.float32), (1, torch.float64))}
+    work = torch.empty(16 << 20, dtype=torch.uint8, device="cuda")
+
+    def clock(call):
+        """us per call of the other library and of this one: the least of four batches of at least 4 ms, in turn."""
+        e = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+
+        def batch(L, n):
+            e[0].record()
+            for _ in range(n):
+                if call(L):
+                    raise RuntimeError("a call failed")
+            e[1].record()
+            e[1].synchronize()
+            return e[0].elapsed_time(e[1]) / n
+
+        best, n = [1e30, 1e30], [0, 0]
+        for i, L in enumerate((before, here)):
+            batch(L, 1)
+            n[i] = max(1, min(1000, math.ceil(4.0 / max(batch(L, 3), 1e-3))))
+        for _ in range(4):
+            for i, L in enumerate((before, here)):
+                best[i] = min(best[i], batch(L, n[i]))
+        return best[0] * 1e3, best[1] * 1e3
+
+    def coefficients(dims, code, kind, r):
+        mask = (wl.mask_star if kind == "star" else wl.mask_box)(r, r, r if dims == 3 else 0)
+        return wl.seeded_coefficients(mask, r, np.float64 if code else np.float32)
+
+    def iteration(shape, code, kind, r, boundary, steps):
+        c, rz = coefficients(len(shape), code, kind, r), r if len(shape) == 3 else 0
+        D, H, W = (1, *shape)[-3:]
+        a, b = pointers[code]
+        return lambda L: L.ssam_stencil_iterate(a, b, W, H, D, c.ctypes.data, r, r, rz, binding.BOUNDARY[boundary], code, steps, stream, None)
+
+    def volume_filter(shape, taps):
+        K, N, M = taps
+        w = np.full((K, N, M), 1.0 / (K * N * M))
+        D, H, W = shape
+        a, b = pointers[1]
+        return lambda L: L.ssam_conv3d(a, b, W, H, D, w.ctypes.data, M, N, K, -1, -1, -1, 1, 1, stream)
+
+    def plan(shape, code, kind, r, boundary, steps):
+        c = coefficients(len(shape), code, kind, r)
+        return binding.ssam_describe("iterate3d" if len(shape) == 3 else "iterate2d", shape, c if len(shape) == 3 else c[0], boundary, remaining=steps)
+
+    def size(lo, hi):
+        return int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+
+    def some(extents, points, radii, sweeps, whole=0.5, takes=""):
+        """A random iteration, whole: the share of widths that are multiples of 32; only grids whose plan names `takes`."""
+        while True:
+            shape = tuple(size(*x) for x in extents)
+            if rng.random() < whole:
+                shape = (*shape[:-1], max(32, shape[-1] // 32 * 32))
+            case = shape, rng.randint(0, 1), rng.choice(("star", "box")), rng.choice(radii), rng.choice(("zero", "clamp")), rng.randint(*sweeps)
+            if points[0] <= math.prod(shape) <= points[1] and takes in plan(*case):
+                return iteration(*case)
+
+    def some_filter():
+        shape = tuple(size(4, 400) for _ in range(3))
+        return volume_filter(shape, tuple(rng.randint(1, min(10, n)) for n in shape))
+
+    def some_scan():
+        code = rng.randint(0, 1)
+        n, (a, b) = size(80e3, 480e6) // (8 if code else 4), pointers[code]
+        out = a if rng.random() < 0.5 else b
+        return lambda L: L.ssam_scan(a, out, n, code, work.data_ptr(), work.numel(), stream)
+
+    out = ["# Iterations, fp64 volume filters and scans against an earlier build of the library\n",
+           f"One MI355X, one process: the library of commit {commit} and this one, loaded side by side and called in turn through the C entry "
+           "points (`ssam_stencil_iterate`, `ssam_conv3d`, `ssam_scan`) on the same buffers.  \u00b5s per call, the least of four batches of at "
+           "least 4 ms each, by events on the stream; buffers are used again, so small grids are in the caches.  A grid is named columns \u00d7 rows (\u00d7 planes).\n",
+           f"    git archive {commit} | tar -x -C before && (cd before && python -m paper_1907_06154_amd.build)\n"
+           f"    python -m paper_1907_06154_amd.profiling against {other} {commit} {os.path.relpath(out_md, ROOT)}\n",
+           "| grid | stencil | sweeps | before | now | now / before | now, \u00b5s a sweep |\n|---|---|---|---|---|---|---|"]
+    for text in LISTED.split(";"):
+        grid, elem, kind, r, boundary, steps = text.split()
+        t = clock(iteration(tuple(map(int, grid.split("x")))[::-1], int(elem == "f64"), kind, int(r), boundary, int(steps)))
+        out.append(f"| {grid} | {elem} {kind} r{r}, {boundary} | {steps} | {t[0]:.1f} | {t[1]:.1f} | {t[1] / t[0]:.2f} | {t[1] / int(steps):.2f} |")
+        print(out[-1], flush=True)
+    out.append("\n| fp64 filter, clamp | before | now | now / before |\n|---|---|---|---|")
+    for text in FILTERS.split(", "):
+        taps, grid = (tuple(map(int, x.split("x")))[::-1] for x in text.split(" on "))
+        t = clock(volume_filter(grid, taps))
+        out.append(f"| {text} | {t[0]:.1f} | {t[1]:.1f} | {t[1] / t[0]:.2f} |")
+        print(out[-1], flush=True)
+    out.append(f"\nRandom calls, {seconds:.0f} seconds of each kind (now / before; sizes uniform over their logarithm, half of the widths multiples of 32; what "
+               "differs by more than 5 % is timed again, since the host disturbs short calls, and the second time counts):\n\n"
+               "| calls | number | least | 5 % | middle | 95 % | most | slower by more than 5 % |\n|---|---|---|---|---|---|---|---|")
+    M = 10 ** 6
+    kinds = [("2D iterations, 64 .. 8192 a side, radius 1 to 3, 2 .. 50 sweeps", lambda: some([(64, 8192)] * 2, (1, 67 * M), (1, 2, 3), (2, 50))),
+             ("2D iterations of radius 1 on tiles, rows of whole pieces, 0.3 to 17 million points, 2 .. 12 sweeps",
+              lambda: some([(64, 8192)] * 2, (0.3 * M, 17 * M), (1,), (2, 12), 1.0, "_tile_")),
+             ("2D iterations of radius 2 to 6 on tiles, 0.1 to 4 million points, 2 .. 12 sweeps",
+              lambda: some([(64, 8192)] * 2, (0.1 * M, 4.2 * M), (2, 3, 4, 5, 6), (2, 12), 0.5, "_tile_")),
+             ("3D iterations of radius 1, 4 .. 640 a side, 2 .. 10 sweeps", lambda: some([(4, 640)] * 3, (1, 134 * M), (1,), (2, 10))),
+             ("3D iterations of radius 1 as levels, 2 .. 16 planes, 2 .. 10 sweeps",
+              lambda: some([(2, 16), (16, 640), (64, 640)], (1, 134 * M), (1,), (2, 10), 0.5, "_levels_")),
+             ("fp64 3D filters, 1 .. 10 a side, on 4 .. 400 a side", some_filter),
+             ("scans of 80 KB to 480 MB, in place and not", some_scan)]
+    for name, draw in kinds:
+        ratios, end = [], time.monotonic() + seconds
+        while time.monotonic() < end:
+            call = draw()
+            t = clock(call)
+            if not 0.95 < t[1] / t[0] < 1.05:
+                t = clock(call)
+            ratios.append(t[1] / t[0])
+        q = np.percentile(ratios, [0, 5, 50, 95, 100])
+        out.append(f"| {name} | {len(ratios)} | " + " | ".join(f"{x:.2f}" for x in q) + f" | {sum(x > 1.05 for x in ratios)} |")
+        print(out[-1], flush=True)
+    open(out_md, "w").write("\n".join(out) + "\n")
+
+
 def main(argv) -> int:
     if len(argv) >= 3 and argv[0] == "summarize":
         title = argv[argv.index("--title") + 1]
@@ -426,6 +582,8 @@ def main(argv) -> int:
         sweep(argv[1], argv[2], argv[3])
     elif len(argv) == 3 and argv[0] == "scan":
         scan_summary(argv[1], argv[2])
+    elif len(argv) == 4 and argv[0] == "against":
+        against(argv[1], argv[2], argv[3])
     elif len(argv) == 2 and argv[0] == "resources":
         resources(argv[1])
     else:
