@@ -64,7 +64,7 @@ def check(L, a, what):
 
 # (first call, second and smaller call); "scan_chained" 1 makes every out-of-place array that the
 # one-pass schedule can hold take it (ticket counter, flag and published sums live in the workspace),
-# -1 leaves the built-in choice: three launches at these sizes (segment sums in the workspace)
+# -1 leaves the built-in choice: two launches at these sizes (segment sums in the workspace)
 CASES = [(-1, 3_000_017, 1_000_003), (1, 5_000_011, 2_500_007), (1, 4_200_000, 70_001), (-1, 300_000, 40_000)]
 
 
